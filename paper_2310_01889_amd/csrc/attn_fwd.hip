@@ -1,7 +1,7 @@
-// Ring-attention forward step kernels for gfx950.
+// Ring-attention forward kernels for gfx950.
 //
-// One launch folds, for every host listed in the step, the key/value block that host
-// holds into its running state -- running row maximum m, running denominator l and
+// One launch folds either every block of the ring, or, for every host listed in one ring
+// step, the key/value block that host holds, into the hosts' running state -- running row maximum m, running denominator l and
 // unnormalised output (numerator) acc -- as the online-softmax recurrence of the
 // paper's blockwise attention (Section 2 "Blockwise Parallel Transformers"; Section 3;
 // the carry of the Appendix A forward scan):
@@ -10,6 +10,12 @@
 // with s = q k^T / sqrt(D), masked (causal, by global position) keys giving p = 0.
 // On a host's first active step the state starts from (m=-inf, l=0, acc=0) in
 // registers; on its last it is finalised into o = acc / l and lse = m + ln l.
+//
+// The bf16 whole-ring launch is bound by the matrix cores at the board's power limit and the
+// key/value tile loads.  Against one launch a step (state saved and loaded in float32, blocks
+// copied from host to host, a grid tail each step) it takes, in us: 32768 tokens x 32 heads,
+// 8 hosts 7490 (steps 7919; 1.18 PFLOP/s); 16384 x 16, 8 hosts 955 (1120); 4 x 2048 x 12 heads
+// of 64, bidirectional, 4 hosts 63 (110); 2048 x 8, 4 hosts 35 (71).
 #include <type_traits>
 
 #include "ra_common.h"
@@ -44,10 +50,14 @@ constexpr float kSumMax = 65536.f;  // overflow test: a lane's row sum over a ti
 // bit 2 flipped on odd s.  Tiles are filled with direct-to-LDS loads (no registers):
 // lane i of a 1 KB load lands at byte 16 i of its destination, so each lane fetches the
 // logical chunk that the swizzle puts there.
-template <int D, int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(const FwdStep p) {
+// RING: the whole ring in one launch.  A workgroup walks the tiles of every block its host
+// folds, in ring order -- its own block first, then its predecessors' -- reading them where
+// they lie, so the state never leaves the registers.  Otherwise one ring step: the tiles of
+// the one block the slot names.
+template <int D, int NW, bool RING>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
+    const typename std::conditional<RING, FwdRing, FwdStep>::type p) {
   constexpr int BM = 32 * NW;  // queries per workgroup (32 per wave)
-  constexpr int NT = 64 * NW;  // threads per workgroup
   constexpr int NKK = D / 16;  // 16-wide reduction steps of q.k
   constexpr int NDT = D / 32;  // 32-row output tiles of O^T
   constexpr int CPR = D / 8;   // 16-byte chunks per row
@@ -68,64 +78,109 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   auto vbuf = [&](auto Bc) __attribute__((always_inline)) -> bf16* {
     if constexpr (decltype(Bc)::value == 0) return sV0; else return sV1;
   };
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
 
-  const int n_qt = p.c / BM;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_qt;
-  const int L = xcd_swizzle(blockIdx.x, total);
-  const int grp = L / n_qt;
-  const int qt = n_qt - 1 - (L % n_qt);  // longest causal rows first
-  const int slot = grp / BH, bh = grp % BH;
+  // ---- the workgroup's query rows and the blocks it folds ----------------------------
+  int bh, q_tile_row;     // (batch, head); first q-space row of the workgroup
+  int tile_first_q;       // its global position
+  int k_pos0;             // global position of the first block's first key
+  int host = 0;           // RING: the host that owns the rows
+  int flags = kFirst | kLast;
+  int kv_rows;            // key rows that exist, from kbase (reads past them give zero)
+  int nt, n_full;         // key tiles visited; tiles [n_full, n_own) need the causal mask
+  int n_own;              // tiles of the first block
+  const int blk_tiles = p.c / kBN;
+  const bf16 *kbase, *vbase;
+  if constexpr (RING) {
+    const int n_qt = (p.S + BM - 1) / BM;
+    int qt;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, bh, qt)) return;
+    q_tile_row = tile_first_q = qt * BM;
+    host = q_tile_row / p.c;
+    k_pos0 = host * p.c;
+    kv_rows = p.S;
+    const long long off = (long long)(bh / p.H) * p.bstride + (bh % p.H) * D;
+    kbase = (const bf16*)p.k + off;
+    vbase = (const bf16*)p.v + off;
+  } else {
+    const int n_qt = p.c / BM;
+    const int BH = p.B * p.H;
+    const int L = xcd_swizzle(blockIdx.x, p.n_slots * BH * n_qt);
+    const int grp = L / n_qt;
+    const int qt = n_qt - 1 - (L % n_qt);  // longest causal rows first
+    const StepHost& hs = p.host[grp / BH];
+    bh = grp % BH;
+    q_tile_row = hs.q_row0 + qt * BM;
+    tile_first_q = hs.q_pos0 + qt * BM;
+    k_pos0 = hs.k_pos0;
+    kv_rows = hs.kv_rows;
+    flags = hs.flags;
+    const long long off = (long long)(bh / p.H) * hs.kv_bstride + (bh % p.H) * D;
+    kbase = (const bf16*)hs.k + off;
+    vbase = (const bf16*)hs.v + off;
+    if (q_tile_row >= p.Sq) return;
+  }
   const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // uniform: LDS destinations in scalar registers
   const int l32 = lane & 31, hi = lane >> 5;
   const int rs = p.H * D;  // row stride of q / k / v / o (elements)
+  const int q_rows = [&] { if constexpr (RING) return p.S; else return p.Sq; }();  // query rows that exist
+  const long long q_bs = [&] { if constexpr (RING) return p.bstride; else return p.q_bstride; }();
 
-  const int q_tile_row = hs.q_row0 + qt * BM;       // first q-space row of the workgroup
   const int qr = q_tile_row + wave * 32 + l32;       // this lane's query row
-  const int qpos = hs.q_pos0 + qt * BM + wave * 32 + l32;
-  const int tile_first_q = hs.q_pos0 + qt * BM;
+  const int qpos = tile_first_q + wave * 32 + l32;
+  const bf16* qbase = (const bf16*)p.q + (long long)b * q_bs + h * D;
 
-  const bf16* qbase = (const bf16*)p.q + (long long)b * p.q_bstride + h * D;
-  const bf16* kbase = (const bf16*)hs.k + (long long)b * hs.kv_bstride + h * D;
-  const bf16* vbase = (const bf16*)hs.v + (long long)b * hs.kv_bstride + h * D;
-
-  // key tiles with at least one visible key; the first n_full need no mask
-  int nt = p.c / kBN, n_full = nt;
+  // key tiles of the first block with at least one visible key; the first n_full need no mask
+  n_own = n_full = blk_tiles;
   if (p.causal) {
-    const int vis = tile_first_q + BM - hs.k_pos0;  // keys visible to the last row
-    nt = min(nt, max(0, (vis + kBN - 1) / kBN));
-    n_full = min(nt, max(0, (tile_first_q - hs.k_pos0 + 1) / kBN));
+    const int vis = tile_first_q + BM - k_pos0;  // keys visible to the last row
+    n_own = min(n_own, max(0, (vis + kBN - 1) / kBN));
+    n_own = min(n_own, (max(0, RING ? kv_rows - k_pos0 : kv_rows) + kBN - 1) / kBN);
+    n_full = min(n_own, max(0, (tile_first_q - k_pos0 + 1) / kBN));
   }
+  nt = n_own;
+  if constexpr (RING) nt += (p.causal ? host : p.N - 1) * blk_tiles;
+  // Walk over the key tiles: row of the next tile (from kbase) and the tiles left in its
+  // block.  The blocks follow one another in ring order, host, host - 1, ... (mod N).
+  struct Walk { int row, left, blk; };
+  auto next_row = [&](Walk& w) __attribute__((always_inline)) -> int {
+    const int r = w.row;
+    w.row += kBN;
+    if constexpr (RING) {
+      if (--w.left == 0) {
+        w.blk = w.blk == 0 ? p.N - 1 : w.blk - 1;
+        w.row = w.blk * p.c;
+        w.left = blk_tiles;
+      }
+    }
+    return r;
+  };
+  Walk wk{RING ? k_pos0 : 0, n_own, host}, wv = wk;
 
   // ---- running state -------------------------------------------------------------
   f32x16 oacc[NDT];
-  float m_run, l_run;
-  const long long st_row = (long long)bh * p.Sq + qr;
-  float* acc_tile = p.acc + ((long long)bh * (p.Sq / BM) + q_tile_row / BM) * (BM * D);
-  if (hs.flags & kFirst) {
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+  for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
-    m_run = -INFINITY;
-    l_run = 0.f;
-  } else {
+    for (int i = 0; i < 16; ++i) oacc[dt][i] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+  if constexpr (!RING) {
+    if (!(flags & kFirst)) {
+      const f32x4* acc_tile = (const f32x4*)(p.acc + ((long long)bh * (p.Sp / BM) + q_tile_row / BM) * (BM * D));
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+      for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 t = ((const f32x4*)acc_tile)[((wave * NDT + dt) * 4 + g) * 64 + lane];
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 t = acc_tile[((wave * NDT + dt) * 4 + g) * 64 + lane];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) oacc[dt][4 * g + e] = t[e];
-      }
-    m_run = p.m[st_row];
-    l_run = hi ? 0.f : p.l[st_row];
+          for (int e = 0; e < 4; ++e) oacc[dt][4 * g + e] = t[e];
+        }
+      const long long st_row = (long long)bh * p.Sp + qr;
+      m_run = p.m[st_row];
+      l_run = p.l[2 * st_row + hi];
+    }
   }
 
   // ---- Q in registers: B operand of S^T = K Q^T (n = query, k = dim) ---------------
@@ -135,7 +190,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   const float sl2 = p.scale * kLog2e;
   bf16x8 qreg[NKK];
   {
-    const bf16* qrow = qbase + (long long)qr * rs;
+    const bf16* qrow = qbase + (long long)min(qr, q_rows - 1) * rs;  // rows past the end: any row
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) qreg[kk] = *(const bf16x8*)(qrow + 16 * kk + 8 * hi);
   }
@@ -161,14 +216,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
                         8 * ((lane % CPR) ^ swz<D>(wave * ROWS_PER_LOAD + lane / CPR)));
   // buffer loads with the LDS flag: the tile base is a wave-uniform descriptor, so the
   // per-tile address update is scalar work; reads past the tile return zero
-  auto dload = [&](const bf16* src_tile, bf16* dst_tile) __attribute__((always_inline)) {
+  auto dload = [&](const bf16* src, int row, bf16* dst_tile) __attribute__((always_inline)) {
+    const bf16* src_tile = src + (long long)row * rs;
+    const int bytes = min(kBN, kv_rows - row) * rs * 2;
 #pragma unroll
     for (int j = 0; j < LOADS; ++j)
-      buffer_load_lds16_so(src_tile, kBN * rs * 2, dst_tile + (j * NW + wave_u) * ROWS_PER_LOAD * D, goff,
+      buffer_load_lds16_so(src_tile, bytes, dst_tile + (j * NW + wave_u) * ROWS_PER_LOAD * D, goff,
                            j * 2 * NW * ROWS_PER_LOAD * rs);
   };
-  auto load_k = [&](int it, auto Bc) __attribute__((always_inline)) { dload(kbase + (long long)it * kBN * rs, kbuf(Bc)); };
-  auto load_v = [&](int it, auto Bc) __attribute__((always_inline)) { dload(vbase + (long long)it * kBN * rs, vbuf(Bc)); };
+  // the next tile of the walk (called once per tile, in order)
+  auto load_k = [&](auto Bc) __attribute__((always_inline)) { dload(kbase, next_row(wk), kbuf(Bc)); };
+  auto load_v = [&](auto Bc) __attribute__((always_inline)) { dload(vbase, next_row(wv), vbuf(Bc)); };
 
   // ---- per-lane LDS read offsets (elements), fixed across tiles ----------------------
   // row reads of K: row 32 mt + swap_bits23(l32), logical chunk 2 kk + hi
@@ -207,7 +265,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   float l_tile = 0.f;            // this lane's row sum of tile t's probabilities
 
   auto mask_tile = [&](f32x16* sc, int it) __attribute__((always_inline)) {
-    const int kpos0 = hs.k_pos0 + it * kBN;
+    const int kpos0 = k_pos0 + it * kBN;
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -263,17 +321,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   // operand reads PF steps ahead, and the vector work of pair u = s * 16 / NSTEP of tile t:
   // its exponentials at that step, its packing one step later, its row-sum term two steps
   // later.
-  auto region = [&](auto Bc, auto NXc, auto PVc, auto MCc, int it, bool RTMASK = false) __attribute__((always_inline)) {
+  auto region = [&](auto Bc, auto NXc, auto PVc, int it) __attribute__((always_inline)) {
     constexpr int B = decltype(Bc)::value;
-    constexpr bool NX = decltype(NXc)::value, PV = decltype(PVc)::value, MC = decltype(MCc)::value;
-    if (NX && it + 2 < nt) load_k(it + 2, Bc);
-    load_v(it, Bc);  // read by region t+1 or, after the last region, by the final products
+    constexpr bool NX = decltype(NXc)::value, PV = decltype(PVc)::value;
+    if (NX && it + 2 < nt) load_k(Bc);
+    load_v(Bc);  // read by region t+1 or, after the last region, by the final products
     const bf16* kt = kbuf(std::integral_constant<int, B ^ 1>{});
     const bf16* vt = vbuf(std::integral_constant<int, B ^ 1>{});
-    if constexpr (MC) mask_tile(s_cur, it);
-    if constexpr (!MC) {
-      if (RTMASK && it >= n_full) mask_tile(s_cur, it);
-    }
+    if (it >= n_full && it < n_own) mask_tile(s_cur, it);
     bf16x8 kop[NS], vop[NP];
     uint32_t w[16];
     float pe[16][2];
@@ -330,30 +385,30 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   };
 
   // regions [a, e) that have a successor and a predecessor, two at a time so that the
-  // buffer parity is a constant; MC: their tiles need the mask
-  auto run = [&](auto MCc, int a, int e) __attribute__((always_inline)) {
+  // buffer parity is a constant
+  auto run = [&](int a, int e) __attribute__((always_inline)) {
     int it = a;
-    if ((it & 1) && it < e) region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, MCc, it++);
+    if ((it & 1) && it < e) region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, it++);
     for (; it + 1 < e; it += 2) {
-      region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, MCc, it);
-      region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, MCc, it + 1);
+      region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, it);
+      region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, it + 1);
     }
-    if (it < e) region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, MCc, it);
+    if (it < e) region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, it);
   };
   // the last region (no successor): one instance for any parity, mask and predecessor,
   // its two buffers chosen at run time (the compiler then waits for the in-flight load of
   // V(t) before reading V(t-1) from the other buffer: once per workgroup)
   auto last = [&](int it) __attribute__((always_inline)) {
-    if (it >= n_full) mask_tile(s_cur, it);
+    if (it >= n_full && it < n_own) mask_tile(s_cur, it);
     bf16* vld = (it & 1) ? sV1 : sV0;
     const bf16* vt = (it & 1) ? sV0 : sV1;
-    dload(vbase + (long long)it * kBN * rs, vld);  // V(t) for the final products
+    dload(vbase, next_row(wv), vld);  // V(t) for the final products
     uint32_t w[16];
-    float r0 = 0.f, r1 = 0.f;
+    float rs2[4] = {0.f, 0.f, 0.f, 0.f};  // row sums in the order of the other regions
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       w[u] = expo_pair(s_cur, u);
-      if (u & 1) r1 = dot2_bf16_ones(w[u], r1); else r0 = dot2_bf16_ones(w[u], r0);
+      rs2[u % 4] = dot2_bf16_ones(w[u], rs2[u % 4]);
     }
     if (it > 0) {
 #pragma unroll
@@ -363,14 +418,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
         oacc[q % NDT] = mfma32(bf16x8{lo[0], lo[1], lo[2], lo[3], up[0], up[1], up[2], up[3]}, pprev[q / NDT], oacc[q % NDT]);
       }
     }
-    l_tile = r0 + r1;
+    l_tile = (rs2[0] + rs2[1]) + (rs2[2] + rs2[3]);
     close_tile(s_cur, w);
   };
 
   if (nt > 0) {
     // K(0) and K(1); the scores of tile 0
-    load_k(0, std::integral_constant<int, 0>{});
-    if (nt > 1) load_k(1, std::integral_constant<int, 1>{});
+    load_k(std::integral_constant<int, 0>{});
+    if (nt > 1) load_k(std::integral_constant<int, 1>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 #pragma unroll
@@ -383,10 +438,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
     if (nt > 2) __syncthreads();
     if (nt > 1) {
       // region 0: no predecessor
-      region(std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{}, std::false_type{}, 0, true);
-      const int split = max(1, min(nt - 1, n_full));  // regions from here on mask their tile
-      run(std::false_type{}, 1, split);
-      run(std::true_type{}, split, nt - 1);
+      region(std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{}, 0);
+      run(1, nt - 1);
     }
     last(nt - 1);
     // O^T += V^T P^T of the last tile, from V(nt-1) in buffer (nt-1) % 2
@@ -408,59 +461,40 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(cons
   asm volatile("" : "+v"(tid_e));
   const int lane_e = tid_e & 63, wave_e = tid_e >> 6, hi_e = lane_e >> 5;
   const int qr_e = q_tile_row + wave_e * 32 + (lane_e & 31);
-  const long long st_row_e = (long long)bh * p.Sq + qr_e;
-  const float l_tot = pair_sum(l_run);
-  if (hs.flags & kLast) {
+  if (flags & kLast) {
+    const float l_tot = pair_sum(l_run);
     const float inv = 1.f / l_tot;
-    bf16* orow = (bf16*)p.o + (long long)b * p.q_bstride + (long long)qr_e * rs + h * D;
+    if (qr_e < q_rows) {
+      bf16* orow = (bf16*)p.o + (long long)b * q_bs + (long long)qr_e * rs + h * D;
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
+      for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int d = 32 * dt + 8 * g + 4 * hi_e;
-        u32x2 w = {pack_bf16x2(oacc[dt][4 * g] * inv, oacc[dt][4 * g + 1] * inv),
-                   pack_bf16x2(oacc[dt][4 * g + 2] * inv, oacc[dt][4 * g + 3] * inv)};
-        *(u32x2*)(orow + d) = w;
+        for (int g = 0; g < 4; ++g) {
+          const int d = 32 * dt + 8 * g + 4 * hi_e;
+          u32x2 w = {pack_bf16x2(oacc[dt][4 * g] * inv, oacc[dt][4 * g + 1] * inv),
+                     pack_bf16x2(oacc[dt][4 * g + 2] * inv, oacc[dt][4 * g + 3] * inv)};
+          *(u32x2*)(orow + d) = w;
+        }
+      if (!hi_e) {
+        float ln_l = logf(l_tot);
+        asm volatile("" : "+v"(ln_l));  // no contraction into the logarithm: the same bits in every instance
+        p.lse[(long long)bh * q_rows + qr_e] = fmaf(m_run, kLn2, ln_l);
       }
-    if (!hi_e) p.lse[st_row_e] = m_run * kLn2 + logf(l_tot);
-  } else {
+    }
+  } else if constexpr (!RING) {
+    // the two half sums of a row's denominator go out as they are, so that a call made of
+    // several launches adds them up in the order of a call made of one
+    f32x4* acc_tile = (f32x4*)(p.acc + ((long long)bh * (p.Sp / BM) + q_tile_row / BM) * (BM * D));
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const f32x4 t = {oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]};
-        ((f32x4*)acc_tile)[((wave_e * NDT + dt) * 4 + g) * 64 + lane_e] = t;
+        acc_tile[((wave_e * NDT + dt) * 4 + g) * 64 + lane_e] = t;
       }
-    if (!hi_e) {
-      p.m[st_row_e] = m_run;
-      p.l[st_row_e] = l_tot;
-    }
-  }
-
-  // ---- send: rows 128 qt .. 128 qt + 127 of (b, h) of this host's block to the host
-  // that needs the block at the next step (the ring's exchange, done by the workgroups
-  // as they finish instead of by copies between the steps)
-  const int fto = p.fwd.to[slot] - 1;  // destination slot, or -1
-  if (fto >= 0 && p.fwd.k0 != nullptr && p.fwd.v0 != nullptr) {
-    constexpr int PER = BM * CPR / NT;  // 16-byte chunks per thread per operand
-    const long long doff = (long long)fto * p.fwd.blk_bytes + 2 * ((long long)b * p.c * rs + h * D);
-    bf16* kdst = (bf16*)((char*)p.fwd.k0 + doff);
-    bf16* vdst = (bf16*)((char*)p.fwd.v0 + doff);
-    u32x4 kx[PER], vx[PER];
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = e * NT + tid_e;
-      const long long off = (long long)(qt * BM + idx / CPR) * rs + 8 * (idx % CPR);
-      kx[e] = *(const u32x4*)(kbase + off);
-      vx[e] = *(const u32x4*)(vbase + off);
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = e * NT + tid_e;
-      const long long off = (long long)(qt * BM + idx / CPR) * rs + 8 * (idx % CPR);
-      *(u32x4*)(kdst + off) = kx[e];
-      *(u32x4*)(vdst + off) = vx[e];
-    }
+    const long long st_row = (long long)bh * p.Sp + qr_e;
+    if (!hi_e) p.m[st_row] = m_run;
+    p.l[2 * st_row + hi_e] = l_run;
   }
 }
 
@@ -567,25 +601,34 @@ __global__ __launch_bounds__(64) void fwd_f32_kernel(const FwdStep p) {
 
 // Long blocks (D = 128, at least 16384 keys, a multiple of 256) run the eight-wave kernel:
 // 256 queries per workgroup, so each key/value tile is loaded once for twice the queries
-// (one workgroup per CU instead of two; at 4096-8192 keys the longer start and end of each
-// workgroup outweigh the saved loads).  The choice depends only on (D, c), so every step
-// of a call uses the same kernel and the float32 state keeps one layout.
+// (one workgroup per CU instead of two).  One ring step at a time its longer start and end
+// outweigh the saved loads at 4096-8192 keys; over the whole ring in one launch the two are
+// within 2 % of each other at 16384 tokens x 16 heads (4 waves 955 us, 8 waves 943) and 65536
+// x 8 (7288, 7244), the four-wave kernel ahead at 32768 x 32 (7490, 7860) and wherever the
+// workgroups are few (2048 x 8: 35.5, 52.7; 16384 x 12: 776, 840).  The choice depends only on
+// (D, c), so a call cut into steps uses one kernel and the float32 state keeps one layout.
 static bool fwd_bf16_wide(int D, int c) { return D == 128 && c % 256 == 0 && c >= 16384; }
 
 hipError_t launch_fwd_bf16(const FwdStep& s, int D, hipStream_t st) {
   const int total = s.n_slots * s.B * s.H * (s.c / kBM);
   if (total == 0) return hipSuccess;
-  const bool wide = fwd_bf16_wide(D, s.c);
-  // a forwarding destination needs both receive bases and a slot size
-  for (int n = 0; n < s.n_slots; ++n)
-    if (s.fwd.to[n] != 0 && (s.fwd.to[n] < 0 || s.fwd.k0 == nullptr || s.fwd.v0 == nullptr || s.fwd.blk_bytes <= 0))
-      return hipErrorInvalidValue;
-  if (wide)
-    hipLaunchKernelGGL((fwd_bf16_kernel<128, 8>), dim3(total / 2), dim3(512), 0, st, s);
+  if (fwd_bf16_wide(D, s.c))
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, 8, false>), dim3(total / 2), dim3(512), 0, st, s);
   else if (D == 128)
-    hipLaunchKernelGGL((fwd_bf16_kernel<128, 4>), dim3(total), dim3(kThreads), 0, st, s);
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, 4, false>), dim3(total), dim3(kThreads), 0, st, s);
   else
-    hipLaunchKernelGGL((fwd_bf16_kernel<64, 4>), dim3(total), dim3(kThreads), 0, st, s);
+    hipLaunchKernelGGL((fwd_bf16_kernel<64, 4, false>), dim3(total), dim3(kThreads), 0, st, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd_ring_bf16(const FwdRing& s, int D, hipStream_t st) {
+  const int G = s.B * s.H;
+  if (fwd_bf16_wide(D, s.c))
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, 8, true>), dim3(ring_grid(G, (s.S + 255) / 256)), dim3(512), 0, st, s);
+  else if (D == 128)
+    hipLaunchKernelGGL((fwd_bf16_kernel<128, 4, true>), dim3(ring_grid(G, (s.S + kBM - 1) / kBM)), dim3(kThreads), 0, st, s);
+  else
+    hipLaunchKernelGGL((fwd_bf16_kernel<64, 4, true>), dim3(ring_grid(G, (s.S + kBM - 1) / kBM)), dim3(kThreads), 0, st, s);
   return hipGetLastError();
 }
 

@@ -114,6 +114,26 @@ __device__ __forceinline__ int xcd_swizzle(int id, int total) {
   return xcd * per + (xcd < rem ? xcd : rem) + n;
 }
 
+// Work items of a launch over G (batch, head) groups of n tiles each, whose length grows with
+// the tile index under the causal mask.  Workgroups go round-robin over the 8 XCDs; each XCD
+// gets whole groups (the tiles of a group share keys and values in its L2) or, where G is not
+// a multiple of 8, every s-th tile of a group, so that all XCDs get the same share of long and
+// short tiles.  Inside a group the long tiles come first.  ring_grid: workgroups to launch;
+// ring_item: the group and tile of one of them, false for the few that have none.
+__host__ __device__ inline int ring_split(int G) { return G % 8 == 0 ? 1 : G % 4 == 0 ? 2 : G % 2 == 0 ? 4 : 8; }
+__host__ __device__ inline int ring_grid(int G, int n) {
+  const int s = ring_split(G);
+  return G * s * ((n + s - 1) / s);
+}
+__device__ __forceinline__ bool ring_item(int id, int G, int n, int& group, int& tile) {
+  const int s = ring_split(G), per = (n + s - 1) / s;  // tiles of one share
+  const int xcd = id & 7, k = id >> 3;
+  const int share = xcd * (G * s / 8) + k / per;
+  group = share / s;
+  tile = n - 1 - ((k % per) * s + share % s);
+  return tile >= 0;
+}
+
 // Row index with bits 2 and 3 swapped.  Loading the A operand of a 32x32x16 MFMA from
 // row swap_bits23(l % 32) puts, in each lane half h, the 8 consecutive rows 8h..8h+7 of
 // every 16-row group into registers 0..7 and 8..15 of the result -- the k layout of a

@@ -13,9 +13,8 @@ constexpr int kLast = 2;             // host's last active step: finalize o = ac
 
 // Forwarding of the key/value block a host holds to the host that needs it at the next
 // ring step (host i at step t holds block j = (i - t) mod N, which host i+1 holds at step
-// t+1).  The bf16 step kernels copy the block's rows into that host's receive slot for the
-// next step (the backward's dK/dV kernel from the rows it has in hand; the forward kernel
-// after its own work, each workgroup its 128-row slice): slot s of the next step's half of
+// t+1).  The bf16 dK/dV kernel copies the block's rows, as it loads them, into that host's
+// receive slot for the next step: slot s of the next step's half of
 // the receive buffers starts at k0 + s * blk_bytes (v0 for values), in the layout
 // [B, c, H, D].  to[n] is 1 + the destination slot of launch slot n, or 0 for none, so
 // that a zero-initialised descriptor forwards nothing.
@@ -34,6 +33,7 @@ struct StepHost {
   int q_row0;             // first row of the host's queries in q / o / lse / state rows
   int q_pos0;             // global position of that row (causal mask)
   int k_pos0;             // global position of the key block's first row
+  int kv_rows;            // rows of the block that exist (the rest read as zero)
   int flags;              // kFirst | kLast
 };
 
@@ -43,13 +43,24 @@ struct FwdStep {
   const void* q;          // [B, Sq, H, D]
   void* o;                // [B, Sq, H, D]
   float* lse;             // [B, H, Sq]
-  float* acc;             // running numerator, float32, B*H*Sq*D
-  float* m;               // running max (log2 units of the scaled scores), [B, H, Sq]
-  float* l;               // running denominator, [B, H, Sq]
+  float* acc;             // running numerator, float32, B*H*Sp*D
+  float* m;               // running max (log2 units of the scaled scores), [B, H, Sp]
+  float* l;               // running denominator, [B, H, Sp] (bf16: its two halves, [B, H, Sp, 2])
   long long q_bstride;    // Sq * H * D
   int n_slots, B, H, Sq, c, causal;
+  int Sp;                 // rows of the state: the hosts' blocks in full (Sq, rounded up to blocks)
   float scale;            // 1 / sqrt(D)
-  StepForward fwd;        // bf16 kernel only: forward each slot's block to the next host
+};
+
+// Forward over the whole ring in one launch: every host's queries against every block, read
+// where the blocks lie (rows [j c, (j + 1) c) of k and v).
+struct FwdRing {
+  const void *q, *k, *v;  // [B, S, H, D]
+  void* o;                // [B, S, H, D]
+  float* lse;             // [B, H, S]
+  long long bstride;      // S * H * D
+  int B, H, S, c, N, causal;  // causal: S need not fill the N blocks of c rows
+  float scale;            // 1 / sqrt(D)
 };
 
 // Backward step: one key/value block per host; dq accumulates per host, dk/dv per block.
@@ -81,6 +92,7 @@ struct BwdStep {
 };
 
 hipError_t launch_fwd_bf16(const FwdStep& s, int D, hipStream_t st);
+hipError_t launch_fwd_ring_bf16(const FwdRing& s, int D, hipStream_t st);
 hipError_t launch_fwd_f32(const FwdStep& s, int D, hipStream_t st);
 // -Delta = -rowsum(dO * o) and -lse * sqrt(D), both [B, H, S] (for the bf16 step kernels)
 hipError_t launch_bwd_pre_bf16(const void* o, const void* dO, const float* lse, float* ndelta, float* nlse_s,

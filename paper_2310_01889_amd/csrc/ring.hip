@@ -1,16 +1,19 @@
 // Virtual-ring scheduler and the C ABI of the attention entry points.
 //
 // The ring of Section 3 is emulated on one device.  Every host's query block and every
-// key/value block live in device memory.  A call runs n_hosts steps; at step t, host i
-// folds in key/value block order(i, t) -- (i - t) mod n_hosts for the ring -- and every
-// host with work at that step is one slot of a single kernel launch.  Step 0 reads each
+// key/value block live in device memory; host i folds key/value block order(i, t) --
+// (i - t) mod n_hosts for the ring -- at step t.
+//
+// The bf16 forward over the whole ring in ring order runs as one launch that walks every query
+// tile over its host's blocks, read where they lie.  Every other call runs n_hosts steps,
+// every host with work at a step being one slot of a single kernel launch.  Step 0 reads each
 // host's block where it lies (a host's own block needs no transfer).  For t >= 1 the
 // block comes from that host's receive buffer: two slots used alternately (the
 // double buffer of the paper's memory accounting: current and receiving key/value
 // blocks).  The slot for step t+1 is filled while step t computes (the ppermute of the
 // paper's code, overlapped with the blockwise computation): by the step-t kernels
-// themselves when a bf16 call covers the whole ring in ring order, otherwise by copies on
-// a library-owned side stream, with events ordering every copy after the last reader of
+// themselves when a bf16 backward call covers the whole ring in ring order, otherwise by copies
+// on a library-owned side stream, with events ordering every copy after the last reader of
 // its slot and every step after its copy (see run_ring).
 #include <stdarg.h>
 #include <stdio.h>
@@ -121,10 +124,13 @@ static bool env_flag(const char* name) {
 struct RingProblem {
   const void *q, *k, *v;
   int B, H, S, D, N, causal, elt;   // elt: bytes per element (2 = bf16, 4 = float32)
+  int blk_rows;                     // c: rows of a block; S <= N c, the last blocks short or empty
   int Sq;                           // rows of q / o / lse: S (all hosts) or c (one host)
   std::vector<int> hosts;           // hosts evaluated by this call
   std::vector<int> order;           // order[i * N + t] (empty: ring order (i - t) mod N)
-  int c() const { return S / N; }
+  int c() const { return blk_rows; }
+  int rows(int j) const { return std::max(0, std::min(blk_rows, S - j * blk_rows)); }  // of block j
+  bool whole() const { return (int)hosts.size() == N && order.empty(); }  // every host, ring order
   int blk(int i, int t) const { return order.empty() ? ((i - t) % N + N) % N : order[i * N + t]; }
   bool active(int i, int j) const { return !causal || j <= i; }  // block j not fully masked
   int q_row0(int i) const { return Sq == S ? i * c() : 0; }
@@ -142,12 +148,13 @@ struct RecvBuffers {
 
 static int copy_block(const RingProblem& P, const void* src_all, char* dst, int j, hipStream_t st) {
   const size_t rowb = (size_t)P.H * P.D * P.elt;
-  const size_t blkb = (size_t)P.c() * rowb;
+  const size_t blkb = (size_t)P.c() * rowb, width = (size_t)P.rows(j) * rowb;
   const char* src = (const char*)src_all + (size_t)j * blkb;
+  if (width == 0) return RA_OK;
   if (P.B == 1) {
-    RA_HIP(hipMemcpyAsync(dst, src, blkb, hipMemcpyDeviceToDevice, st));
+    RA_HIP(hipMemcpyAsync(dst, src, width, hipMemcpyDeviceToDevice, st));
   } else {
-    RA_HIP(hipMemcpy2DAsync(dst, blkb, src, (size_t)P.S * rowb, blkb, P.B, hipMemcpyDeviceToDevice, st));
+    RA_HIP(hipMemcpy2DAsync(dst, blkb, src, (size_t)P.S * rowb, width, P.B, hipMemcpyDeviceToDevice, st));
   }
   return RA_OK;
 }
@@ -156,16 +163,22 @@ static int copy_block(const RingProblem& P, const void* src_all, char* dst, int 
 // per step with, for every active host, (host, block, kv pointers, batch stride, first/last
 // flags); `contiguous` says that nothing was enqueued on the stream since the previous step.
 //
-// The block a host needs at step t+1 is the one its predecessor holds at step t.  In bf16,
-// when the call covers every host of the ring in ring order, the step-t kernels write that
-// block into the successor's receive slot themselves (the forward kernel's workgroups as
-// they finish, the backward's dK/dV kernel from the rows it loads anyway) -- the send half
-// of the ring's exchange, with no separate copy and no wait between the steps.  Otherwise
+// The block a host needs at step t+1 is the one its predecessor holds at step t.  In the bf16
+// backward, when the call covers every host of the ring in ring order, the step-t dK/dV kernels
+// write that block into the successor's receive slot themselves, from the rows they load
+// anyway -- the send half of the ring's exchange, with no separate copy and no wait between
+// the steps.  Otherwise
 // (one host's share; a custom order; float32; or RINGATTN_SERIAL_COPY set) each step's
 // blocks are copied from their home rows into the receive slots by device-to-device
 // copies, on a side stream two steps ahead (or serially on the caller stream).
+enum class Exchange {
+  kInPlace,  // none: every step reads the blocks where they lie
+  kKernels,  // the step kernels write each block into the next host's receive slot
+  kCopies    // device-to-device copies into the receive slots
+};
 template <class Launch>
-static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, Launch&& launch) {
+static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, Exchange how,
+                    Launch&& launch) {
   const int N = P.N;
   const int nh = (int)P.hosts.size();
   RecvBuffers rb;
@@ -184,10 +197,11 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 
   const bool serial = env_flag("RINGATTN_SERIAL_COPY");
   const bool poison = env_flag("RINGATTN_POISON");
-  bool forward = N > 1 && !serial && P.elt == 2 && nh == N && P.order.empty();
-  for (int s = 0; forward && s < nh; ++s) forward = P.hosts[s] == s;
+  const bool inplace = how == Exchange::kInPlace;
+  const bool forward = N > 1 && how == Exchange::kKernels;
+  const bool copies = N > 1 && how == Exchange::kCopies;
   hipStream_t side = stream;
-  if (!serial && !forward && N > 1) {
+  if (!serial && copies) {
     int rc = side_stream(&side);
     if (rc) return rc;
     R.side = side;
@@ -219,7 +233,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
     }
     return RA_OK;
   };
-  if (N > 1 && !serial && !forward) {
+  if (copies && !serial) {
     int rc = enqueue_copies(1);
     if (!rc && N > 2) rc = enqueue_copies(2);
     if (rc) return rc;
@@ -227,7 +241,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 
   const size_t rowe = (size_t)P.H * P.D;
   for (int t = 0; t < N; ++t) {
-    if (t >= 1 && !forward) {
+    if (t >= 1 && copies) {
       if (serial) {
         int rc = enqueue_copies(t);
         if (rc) return rc;
@@ -241,7 +255,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       const int i = P.hosts[s], j = P.blk(i, t);
       if (!P.active(i, j)) continue;
       StepHost h{};
-      if (t == 0) {
+      if (t == 0 || inplace) {
         h.k = (const char*)P.k + (size_t)j * P.c() * rowe * P.elt;
         h.v = (const char*)P.v + (size_t)j * P.c() * rowe * P.elt;
         h.kv_bstride = (long long)P.S * rowe;
@@ -253,6 +267,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       h.q_row0 = P.q_row0(i);
       h.q_pos0 = i * P.c();
       h.k_pos0 = j * P.c();
+      h.kv_rows = P.rows(j);
       h.flags = (t == first[s] ? kFirst : 0) | (t == last[s] ? kLast : 0);
       hs.push_back(h);
       host_ids.push_back(i);
@@ -274,10 +289,10 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       }
     }
     // contiguous: nothing has been enqueued on the stream since the previous step's launch
-    const bool contiguous = t > 0 && forward && !poison;
+    const bool contiguous = t > 0 && (inplace || (forward && !poison));
     int rc = launch(t, hs, host_ids, blk_ids, fw, contiguous);
     if (rc) return rc;
-    if (!serial && !forward && t >= 1 && t + 2 < N) {
+    if (!serial && copies && t >= 1 && t + 2 < N) {
       hipEvent_t done;
       rc = R.event(&done);
       if (rc) return rc;
@@ -300,12 +315,38 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 // ---------------------------------------------------------------------------------
 // Forward
 // ---------------------------------------------------------------------------------
+// Whole ring in ring order, bf16: all blocks are on this device, so nothing is exchanged and
+// one launch walks each query tile over its host's blocks (launch_fwd_ring_bf16): no receive
+// buffers, no state between steps, one grid instead of N, each with its own tail.  While
+// launches are being timed it runs as one launch a ring step, reading in place, so that
+// every step has its entry.  RINGATTN_SERIAL_COPY / RINGATTN_POISON ask for the exchange by
+// copies.  All give the same bits.
 static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream) {
   const int nh = (int)P.hosts.size();
-  const size_t recv = P.N > 1 ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
-  const size_t nrow = (size_t)P.B * P.H * P.Sq;
+  const bool inplace = P.elt == 2 && P.whole() && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
+  if (inplace && !timing_on()) {
+    FwdRing a{};
+    a.q = P.q;
+    a.k = P.k;
+    a.v = P.v;
+    a.o = o;
+    a.lse = lse;
+    a.bstride = (long long)P.S * P.H * P.D;
+    a.B = P.B;
+    a.H = P.H;
+    a.S = P.S;
+    a.c = P.c();
+    a.N = P.N;
+    a.causal = P.causal;
+    a.scale = 1.0f / sqrtf((float)P.D);
+    RA_HIP(launch_fwd_ring_bf16(a, P.D, stream));
+    return RA_OK;
+  }
+  const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
+  const int Sp = P.whole() ? P.N * P.c() : P.Sq;
+  const size_t nrow = (size_t)P.B * P.H * Sp;
   const bool need_state = P.N > 1;
-  const size_t state = need_state ? nrow * (P.D + 2) * sizeof(float) : 0;
+  const size_t state = need_state ? nrow * (P.D + 3) * sizeof(float) : 0;
   CallResources R(stream);
   int rc = R.alloc(recv + state);
   if (rc) return rc;
@@ -325,15 +366,16 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
   st.B = P.B;
   st.H = P.H;
   st.Sq = P.Sq;
+  st.Sp = Sp;
   st.c = P.c();
   st.causal = P.causal;
   st.scale = 1.0f / sqrtf((float)P.D);
   hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  return run_ring(P, stream, R, base, [&](int, const std::vector<StepHost>& hs, const std::vector<int>&,
-                                         const std::vector<int>&, const StepForward& fw, bool contiguous) -> int {
+  return run_ring(P, stream, R, base, inplace ? Exchange::kInPlace : Exchange::kCopies,
+                  [&](int, const std::vector<StepHost>& hs, const std::vector<int>&, const std::vector<int>&,
+                      const StepForward&, bool contiguous) -> int {
     st.n_slots = (int)hs.size();
     for (size_t s = 0; s < hs.size(); ++s) st.host[s] = hs[s];
-    st.fwd = fw;
     if (!contiguous) chain = nullptr;
     RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] {
       return P.elt == 2 ? launch_fwd_bf16(st, P.D, stream) : launch_fwd_f32(st, P.D, stream);
@@ -406,7 +448,8 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
     st.dv_out = dv;
   }
   hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  rc = run_ring(P, stream, R, base, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
+  const bool kernels = P.elt == 2 && P.whole() && !env_flag("RINGATTN_SERIAL_COPY");
+  rc = run_ring(P, stream, R, base, kernels ? Exchange::kKernels : Exchange::kCopies, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
                                        const std::vector<int>& blks, const StepForward& fw, bool contiguous) -> int {
     st.n_slots = (int)hs.size();
     st.fwd = fw;
@@ -578,7 +621,7 @@ static int validate(int B, int H, int S, int D, int N, int causal, int tile) {
 
 static RingProblem all_hosts(const void* q, const void* k, const void* v, int B, int H, int S, int D, int N,
                              int causal, int elt) {
-  RingProblem P{q, k, v, B, H, S, D, N, causal, elt, S, {}, {}};
+  RingProblem P{q, k, v, B, H, S, D, N, causal, elt, S / N, S, {}, {}};
   for (int i = 0; i < N; ++i) P.hosts.push_back(i);
   return P;
 }
@@ -719,7 +762,7 @@ int ring_attn_fwd_host(const void* q_blk, const void* k_all, const void* v_all, 
   if (rc) return rc;
   if (host_idx < 0 || host_idx >= n_hosts)
     return set_err(RA_EINVAL, "host_idx=%d outside [0, n_hosts=%d)", host_idx, n_hosts);
-  RingProblem P{q_blk, k_all, v_all, B, H, S, D, n_hosts, causal, 2, S / n_hosts, {host_idx}, {}};
+  RingProblem P{q_blk, k_all, v_all, B, H, S, D, n_hosts, causal, 2, S / n_hosts, S / n_hosts, {host_idx}, {}};
   return run_fwd(P, o_blk, lse_blk, stream);
 }
 
@@ -790,19 +833,9 @@ int ring_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o, f
   if (rc) return rc;
   rc = validate(B, H, (int)Sp, D, n_hosts, 1, 128);
   if (rc) return rc;
-  if (Sp == S) return run_fwd(all_hosts(q, k, v, B, H, S, D, n_hosts, 1, 2), o, lse, stream);
-  const long long row = (long long)H * D * 2, t = B * Sp * row;
-  CallResources R(stream);
-  if ((rc = R.alloc((size_t)(4 * t + (long long)B * H * Sp * 4)))) return rc;
-  char* w = (char*)R.ws;
-  char *qp = w, *kp = w + t, *vp = w + 2 * t, *op = w + 3 * t;
-  float* lp = (float*)(w + 4 * t);
-  if ((rc = pad_copy(qp, q, B, S, Sp, row, stream)) || (rc = pad_copy(kp, k, B, S, Sp, row, stream)) ||
-      (rc = pad_copy(vp, v, B, S, Sp, row, stream)))
-    return rc;
-  if ((rc = run_fwd(all_hosts(qp, kp, vp, B, H, (int)Sp, D, n_hosts, 1, 2), op, lp, stream))) return rc;
-  if ((rc = unpad_copy(o, op, B, S, Sp, row, stream))) return rc;
-  return unpad_copy(lse, lp, (long long)B * H, S, Sp, 4, stream);
+  RingProblem P = all_hosts(q, k, v, B, H, S, D, n_hosts, 1, 2);
+  P.blk_rows = (int)(Sp / n_hosts);  // the kernels read rows past S as zero and store none
+  return run_fwd(P, o, lse, stream);
 }
 
 int ring_attn_bwd_varlen(const void* q, const void* k, const void* v, const void* o, const float* lse,
