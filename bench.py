@@ -2,17 +2,16 @@
 """Benchmark of the ring-attention hot path on one MI355X.
 
 Workload (one "step"): causal ring-attention forward, B=1, S=32768, H=32, D=128, bf16
-inputs N(0,1), ring of 8 virtual hosts with 4096-token blocks -- partition and ring
-schedule, the attention-step kernel on every host (whose workgroups also pass the
-key/value block each host holds into the next host's receive buffer), and finalisation.  Inputs are resident in HBM before
-the timed region.  Prints ONE JSON line.
+inputs N(0,1), ring of 8 virtual hosts with 4096-token blocks -- partition, the attention
+kernel that folds every host's blocks in ring order (one launch), and finalisation.  Inputs
+are resident in HBM before the timed region.  Prints ONE JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu] [--no-extra] [--only NAMES]
 
 `value` is TFLOP/s of algorithmic work (4*B*H*D per visible (query, key) pair; causal
 masking halves the diagonal blocks and skips blocks above the diagonal).  The
-`roofline` object reports the step kernel's own throughput (HIP events around every
-launch, on the stream it runs on, in a second pass of as many calls after the timed ones) against the bf16 dense matrix-core peak, and beside it
+`roofline` object reports the kernel's own throughput (a call is one launch: the events
+around the timed calls) against the bf16 dense matrix-core peak, and beside it
 against the rates the chip sustains on back-to-back matrix products alone (the library's
 calibration kernel, measured in the same run): with fixed operands, and with random
 operands that change from product to product as real data does.  `ms_per_step` is the mean over the timed
@@ -204,7 +203,7 @@ def cpu_baselines_other():
 
 
 def recorded_traffic():
-    """HBM bytes per step-kernel launch from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE
+    """HBM bytes per launch of the whole-ring kernel from the committed rocprofv3 FETCH_SIZE/WRITE_SIZE
     summary, or None if the kernel sources changed since it was taken."""
     import hashlib
     prof = os.path.join(ROOT, "profiles", "attn_fwd_S32768_H32_D128_hosts8_traffic.md")
@@ -391,20 +390,10 @@ def main():
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    # the timed calls run without the library's per-launch timing events (each leaves the
-    # GPU idle for a few microseconds between two step kernels); the step kernel's own
-    # duration for the roofline is measured in a second pass of as many calls with them
     ms, ms_med, ms_min, wall = time_calls_each(step, args.steps)
-    ra.timing_read(ra.KERNEL_ATTN_FWD)
-    ra.timing_enable(True)
-    for _ in range(args.steps):
-        step()
-    torch.cuda.synchronize()
-    ra.timing_enable(False)
-    kms, launches = ra.timing_read(ra.KERNEL_ATTN_FWD)
-    k_avg_ms = kms / max(1, launches)
-    flops_per_launch = flops / N  # N launches per step
-    achieved = flops_per_launch / (k_avg_ms * 1e-3) / 1e12
+    # a call is one launch of the whole-ring kernel, back to back with the next one
+    launches, k_avg_ms = args.steps, ms
+    achieved = flops / (k_avg_ms * 1e-3) / 1e12
     value = flops / (ms * 1e-3) / 1e12
     mfma_loop = mfma_loop_peak(ra, torch)
     mfma_loop_rand = mfma_loop_peak(ra, torch, random_operands=True)
@@ -429,7 +418,7 @@ def main():
                    "global_batch": B, "seq_len": S, "parallelism": "virtual ring of 8 hosts on 1 GPU"},
         "pct_bf16_peak": round(100.0 * value / PEAK_BF16_TFLOPS, 2),
         "tokens_per_s": round(B * S / (ms * 1e-3), 1),
-        "roofline": {"bound": "mfma", "kernel": "fwd_bf16_kernel<128, 4> (attention step, four-wave workgroups)",
+        "roofline": {"bound": "mfma", "kernel": "fwd_bf16_kernel<128, 4, true> (whole ring in one launch, four-wave workgroups)",
                      "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": recorded_traffic(),
                      "avg_launch_ms": round(k_avg_ms, 4), "launches": launches,

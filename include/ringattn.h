@@ -11,15 +11,14 @@
  * dQ on the host and dK/dV with the rotating block.  A blockwise feed-forward network
  * (Section 2 equation; Algorithm 1) follows the attention of the same query block.
  *
- * On one GPU the ring is virtual: all hosts' blocks live in device memory.  The bf16
- * forward over the whole ring is one launch that folds every host's blocks, in ring order,
- * where they lie (one launch a ring step while ring_attn_timing_enable is on).  Every other
+ * On one GPU the ring is virtual: all hosts' blocks live in device memory.  bf16 calls over
+ * the whole ring are one launch (backward: one for dK/dV, one for dQ) that folds every
+ * host's blocks, in ring order, where they lie; while ring_attn_timing_enable is on, one
+ * launch a ring step.  Every other
  * call runs n_hosts ring steps, each one kernel launch covering every host that has work at
  * that step, and the block each host needs at the next step reaches its per-host receive
- * buffer (double buffer) during the current step: in the bf16 backward over the whole ring the
- * step kernels write it there themselves (each host sends the block it holds to the next
- * host); otherwise (one host's share, a custom order, float32) device-to-device copies on a
- * library-owned side stream bring it in, overlapping the compute of the current step.
+ * buffer (double buffer) during the current step by device-to-device copies on a
+ * library-owned side stream, overlapping the compute of the current step.
  *
  * Conventions shared by every entry point
  *   - Pointers are DEVICE pointers unless stated.  The caller allocates and owns every
@@ -92,7 +91,7 @@ int ring_attn_fwd(const void* q, const void* k, const void* v, void* o, float* l
  *   q, k, v, o, lse   the forward inputs and outputs (o, lse as written by ring_attn_fwd)
  *   dO        in   bf16 [B, S, H, D]   upstream gradient of o
  *   dq, dk, dv out bf16 [B, S, H, D]   gradients of sum(dO * o); accumulated in float32
- *                                      (dq on the host, dk/dv with their rotating block)
+ *                                      (dq with the host, dk/dv with their block)
  *                                      and rounded once at the end.
  */
 int ring_attn_bwd(const void* q, const void* k, const void* v, const void* o, const float* lse,
@@ -104,13 +103,9 @@ int ring_attn_bwd(const void* q, const void* k, const void* v, const void* o, co
  * one block per host; here the last blocks may be short or empty), bf16.  The block is
  * c = the smallest multiple of 128 with n_hosts * c >= S.  Rows past S count as zero.  Padded
  * keys lie after every real query, so the causal mask hides them; padded query rows add
- * exactly zero to dK and dV.  The forward works on the tensors as they are; the backward
- * stages them into zero-padded workspace copies of length n_hosts * c, runs the ring on
- * them and copies the first S rows out.  Arguments,
- * layouts and outputs as ring_attn_fwd / ring_attn_bwd with causal = 1; S need not be a
- * multiple of n_hosts or of 128 (when n_hosts * c == S no copies are made).  Workspace of
- * the backward: 8 bf16 tensors [B, n_hosts * c, H, D] plus one float32
- * [B, H, n_hosts * c], stream-ordered.  Errors: RA_EINVAL for null pointers or
+ * exactly zero to dK and dV.  Arguments, layouts and outputs as ring_attn_fwd /
+ * ring_attn_bwd with causal = 1; S need not be a multiple of n_hosts or of 128; nothing is
+ * copied.  Errors: RA_EINVAL for null pointers or
  * non-positive sizes, RA_EUNSUPPORTED when the padded shape is outside the supported set.
  */
 int ring_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o, float* lse,

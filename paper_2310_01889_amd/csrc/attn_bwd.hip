@@ -6,9 +6,18 @@
 // (gradient checkpointing: nothing of size [queries, keys] is stored) and
 //     P = exp(s - lse),  dV += P^T dO,  dP = dO V^T,  dS = P * (dP - Delta),
 //     dQ += dS K / sqrt(D),  dK += dS^T Q / sqrt(D),   Delta_r = sum_d dO_rd O_rd.
-// Each step runs two kernels: one owning key tiles (dK, dV in registers, looping over
-// the host's query tiles) and one owning query tiles (dQ in registers, looping over the
-// block's key tiles).  Both write their tile once per step, so no atomics are needed.
+// Two kernels: one owning key tiles (dK, dV in registers, looping over the query tiles that
+// see them) and one owning query tiles (dQ in registers, looping over key tiles).  Both write
+// their tile once, so no atomics are needed.
+//
+// In bf16 each covers the whole ring in one launch, or one ring step of the listed hosts.
+// Over the whole ring the gradients stay in registers; a launch per step read and wrote them
+// in float32 at every step (3.7 GB at 16384 tokens x 16 heads, all workgroups of a step at
+// once, a quarter of a dV/dK wave's life) and had a grid tail each.  Backward of 16384 x 16,
+// 8 hosts: 4190 us in 16 launches, 3220 in two; 4 x 2048 x 12 heads of 64, 4 hosts: 405, 215;
+// 2 x 3001 x 8, 8 hosts (ragged): 457 without the staging copies, 165.
+#include <type_traits>
+
 #include "ra_common.h"
 #include "ra_dma.h"
 #include "ra_kernels.h"
@@ -110,56 +119,160 @@ __global__ __launch_bounds__(256) void bwd_pre_f32_kernel(const float* o, const 
   }
 }
 
-// Adds a workgroup's dK (DK) or dV contribution (lanes over keys, accumulated transposed:
-// register 4 gg + e of product tile dt holds d = 32 dt + 8 gg + 4 hi + e) into the float32
-// gradient of the block (its home rows); dK carries the 1/sqrt(D).  The block's first
-// contribution is written, not added; its last goes out in bf16.  The sums are formed in
-// the accumulators, every carried value loaded before the first store.
-template <int NDT, bool DK>
-__device__ __forceinline__ void dkdv_epilogue(const BwdStep& p, int slot, int b, int h, int key_in_blk, int hi,
-                                                   f32x16 (&acc)[NDT]) {
+// Accumulators of a workgroup's dK (DK) or dV (lanes over keys, accumulated transposed:
+// register 4 gg + e of product tile dt holds d = 32 dt + 8 gg + 4 hi + e).
+// dkdv_start: their values before the first tile -- zero, or what the block's earlier ring
+// steps accumulated.  dkdv_finish: the whole ring done, dK and dV go out in bf16 (dK carries
+// the 1/sqrt(D)); steps to come, the accumulators are saved as they are, so that a call cut
+// into steps adds up in the order of a call made of one launch; one host's share: its
+// contribution is added to the float32 gradient that travels with the block.
+template <int NDT, bool DK, class P>
+__device__ __forceinline__ void dkdv_start(const P& p, int slot, int b, int h, int key_in_blk, int hi,
+                                           f32x16 (&acc)[NDT]) {
   constexpr int D = 32 * NDT;
+#pragma unroll
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+  if constexpr (std::is_same_v<P, BwdStep>) {
+    if (!p.whole || (p.dkv_flags[slot] & kFirst)) return;
+    const long long row = min(p.dkv_row0[slot] + key_in_blk, p.Skv - 1);
+    const float* g32 = (DK ? p.dk : p.dv) + (long long)b * p.dkv_bstride + row * (p.H * D) + h * D;
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) {
+        const f32x4 c4 = *(const f32x4*)(g32 + 32 * dt + 8 * gg + 4 * hi);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[dt][4 * gg + e] = c4[e];
+      }
+  }
+}
+
+template <int NDT, bool DK, class P>
+__device__ __forceinline__ void dkdv_finish(const P& p, int slot, int b, int h, int key_in_blk, int hi,
+                                            f32x16 (&acc)[NDT]) {
+  constexpr int D = 32 * NDT;
+  constexpr bool STEP = std::is_same_v<P, BwdStep>;
   const int rs = p.H * D;
-  const long long grow = (long long)b * p.dkv_bstride + (long long)(p.dkv_row0[slot] + key_in_blk) * rs + h * D;
-  const int kf = p.dkv_flags[slot];
-  float* g32 = DK ? p.dk : p.dv;
   const float sc = DK ? p.scale : 1.f;
-  if (kf & kFirst) {
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[dt][i] = DK ? 0.f + acc[dt][i] * sc : 0.f + acc[dt][i];
+  bool out16 = true;
+  long long grow;
+  bf16* o16;
+  if constexpr (STEP) {
+    const int row = p.dkv_row0[slot] + key_in_blk;
+    if (row >= p.Skv) return;
+    grow = (long long)b * p.dkv_bstride + (long long)row * rs + h * D;
+    out16 = p.whole && (p.dkv_flags[slot] & kLast);
+    o16 = (bf16*)(DK ? p.dk_out : p.dv_out);
   } else {
+    if (key_in_blk >= p.S) return;
+    grow = (long long)b * p.bstride + (long long)key_in_blk * rs + h * D;
+    o16 = (bf16*)(DK ? p.dk : p.dv);
+  }
+  if (out16) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
       for (int gg = 0; gg < 4; ++gg) {
-        const int d = 32 * dt + 8 * gg + 4 * hi;
-        const f32x4 c4 = *(const f32x4*)(g32 + grow + d);
+        const f32x16& a = acc[dt];
+        *(u32x2*)(o16 + grow + 32 * dt + 8 * gg + 4 * hi) =
+            u32x2{pack_bf16x2(a[4 * gg] * sc, a[4 * gg + 1] * sc), pack_bf16x2(a[4 * gg + 2] * sc, a[4 * gg + 3] * sc)};
+      }
+  } else if constexpr (STEP) {
+    float* g32 = (DK ? p.dk : p.dv) + grow;
+    if (!p.whole) {  // every carried value loaded before the first store
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[dt][4 * gg + e] = DK ? c4[e] + acc[dt][4 * gg + e] * sc : c4[e] + acc[dt][4 * gg + e];
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {
+          const f32x4 c4 = *(const f32x4*)(g32 + 32 * dt + 8 * gg + 4 * hi);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[dt][4 * gg + e] = DK ? c4[e] + acc[dt][4 * gg + e] * sc : c4[e] + acc[dt][4 * gg + e];
+        }
+    }
+#pragma unroll
+    for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+      for (int gg = 0; gg < 4; ++gg) {
+        const f32x16& a = acc[dt];
+        *(f32x4*)(g32 + 32 * dt + 8 * gg + 4 * hi) = f32x4{a[4 * gg], a[4 * gg + 1], a[4 * gg + 2], a[4 * gg + 3]};
       }
   }
-  if (kf & kLast) {
-    bf16* o16 = (bf16*)(DK ? p.dk_out : p.dv_out);
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int gg = 0; gg < 4; ++gg) {
-        const int d = 32 * dt + 8 * gg + 4 * hi;
-        const f32x16& a = acc[dt];
-        *(u32x2*)(o16 + grow + d) = u32x2{pack_bf16x2(a[4 * gg], a[4 * gg + 1]), pack_bf16x2(a[4 * gg + 2], a[4 * gg + 3])};
-      }
+}
+
+// What a dK/dV workgroup works on: 128 keys and the 32-query tiles that see them, in ring
+// order.  One ring step: the tiles of the host that holds the block (rows q_row0 of q space).
+// The whole ring: the hosts that fold block j do so in the order j, j + 1, ... (mod N), so
+// their queries are simply the rows from block j on (causal: to the end; else around the
+// ring, back to row wrap).
+struct KeyTile {
+  int slot, bh;
+  int key0;            // first key (row of k / v, from the block's base)
+  int kpos0;           // its global position
+  int kv_rows;         // rows of k / v that exist
+  int q_row0, q_pos0;  // q-space row and position of query tile 0
+  int q_rows;          // rows of q space that exist
+  int qt0, qt_free, n; // first tile, first one without mask (relative to tile 0), tiles visited
+  int wrap;            // tile index at which the walk continues at row 0 of q space
+  long long q_bs, kv_bs;
+  const bf16 *k, *v;
+};
+
+template <class P>
+__device__ __forceinline__ bool key_tile(const P& p, KeyTile& t) {
+  constexpr int kKB = 128, kQB = 32;
+  if constexpr (std::is_same_v<P, BwdRing>) {
+    const int n_kt = (p.S + kKB - 1) / kKB;
+    int tile;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_kt, t.bh, tile)) return false;
+    const int kt = n_kt - 1 - tile;  // under the causal mask the first keys have the most queries
+    const int n_q = (p.S + kQB - 1) / kQB;
+    t.slot = 0;
+    t.key0 = t.kpos0 = kt * kKB;
+    t.kv_rows = t.q_rows = p.S;
+    t.q_row0 = t.q_pos0 = 0;
+    t.q_bs = t.kv_bs = p.bstride;
+    t.wrap = n_q;
+    if (p.causal) {
+      t.qt0 = t.key0 / kQB;
+      t.qt_free = t.qt0 + kKB / kQB;
+      t.n = n_q - t.qt0;
+    } else {
+      t.qt0 = t.key0 / p.c * (p.c / kQB);
+      t.qt_free = t.qt0;
+      t.n = n_q;
+    }
+    t.k = (const bf16*)p.k;
+    t.v = (const bf16*)p.v;
   } else {
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int gg = 0; gg < 4; ++gg) {
-        const int d = 32 * dt + 8 * gg + 4 * hi;
-        const f32x16& a = acc[dt];
-        *(f32x4*)(g32 + grow + d) = f32x4{a[4 * gg], a[4 * gg + 1], a[4 * gg + 2], a[4 * gg + 3]};
-      }
+    const int n_kt = p.c / kKB, BH = p.B * p.H;
+    const int id = xcd_swizzle(blockIdx.x, p.n_slots * BH * n_kt);
+    const int grp = id / n_kt, kt = id % n_kt;
+    t.slot = grp / BH;
+    t.bh = grp % BH;
+    const StepHost& hs = p.host[t.slot];
+    t.key0 = kt * kKB;
+    t.kpos0 = hs.k_pos0 + t.key0;
+    t.kv_rows = hs.kv_rows;
+    t.q_row0 = hs.q_row0;
+    t.q_pos0 = hs.q_pos0;
+    t.q_rows = p.Sq;
+    t.q_bs = p.q_bstride;
+    t.kv_bs = hs.kv_bstride;
+    const int n_q = (min(p.c, p.Sq - hs.q_row0) + kQB - 1) / kQB;  // <= 0: the host has no rows
+    t.wrap = 0x7fffffff;
+    t.qt0 = t.qt_free = 0;
+    if (p.causal) {
+      const int rel = t.kpos0 - hs.q_pos0;
+      t.qt0 = rel <= 0 ? 0 : max(0, min(n_q, rel / kQB));
+      t.qt_free = max(t.qt0, rel + kKB <= 0 ? 0 : (rel + kKB - 1 + kQB - 1) / kQB);
+    }
+    t.n = max(0, n_q - t.qt0);
+    t.k = (const bf16*)hs.k;
+    t.v = (const bf16*)hs.v;
   }
+  return t.key0 < t.kv_rows;
 }
 
 // =====================================================================================
@@ -182,8 +295,8 @@ __device__ __forceinline__ void dkdv_epilogue(const BwdStep& p, int slot, int b,
 // =====================================================================================
 constexpr int kKB = 128, kQB = 32, kBT = 256;
 
-template <int D>
-__global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) {
+template <int D, class P>
+__global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const P p) {
   constexpr int NKK = D / 16, NDT = D / 32, CPR = D / 8;
   constexpr int ROWS_PER_LOAD = 64 / CPR, LOADS = kQB / 4 / ROWS_PER_LOAD;
   static_assert(LOADS >= 1, "each wave fills at least one 1 KB row group");
@@ -208,66 +321,32 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
     if constexpr (B == 0) return a; else if constexpr (B == 1) return b; else return c;
   };
 
-  const int n_kt = p.c / kKB;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_kt;
-  const int Lid = xcd_swizzle(blockIdx.x, total);
-  const int grp = Lid / n_kt, kt = Lid % n_kt;
-  const int slot = grp / BH, bh = grp % BH;
-  const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
+  KeyTile kt;
+  if (!key_tile(p, kt)) return;
+  const int b = kt.bh / p.H, h = kt.bh % p.H;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // uniform: LDS destinations in scalar registers
   const int rs = p.H * D;
   const float sl2 = p.scale * kLog2e;
 
-  const int key_in_blk = kt * kKB + wave * 32 + l32;  // this lane's key (B-operand column)
-  const int kpos = hs.k_pos0 + key_in_blk;
-  const bf16* krow = (const bf16*)hs.k + (long long)b * hs.kv_bstride + (long long)key_in_blk * rs + h * D;
-  const bf16* vrow = (const bf16*)hs.v + (long long)b * hs.kv_bstride + (long long)key_in_blk * rs + h * D;
-  // forwarding: the workgroup writes the rows of its 128 keys, as loaded, into the next
-  // host's receive slot for the next ring step (layout [B, c, H, D])
-  const int fto = p.fwd.to[slot] - 1;  // destination slot, or -1
-  bf16* fkrow = nullptr;
-  bf16* fvrow = nullptr;
-  if (fto >= 0 && p.fwd.k0 != nullptr && p.fwd.v0 != nullptr) {
-    const long long off = (long long)fto * p.fwd.blk_bytes + 2 * (((long long)b * p.c + key_in_blk) * rs + h * D);
-    fkrow = (bf16*)((char*)p.fwd.k0 + off);
-    fvrow = (bf16*)((char*)p.fwd.v0 + off);
-  }
+  const int key_in_blk = kt.key0 + wave * 32 + l32;  // this lane's key (B-operand column)
+  const int kpos = kt.kpos0 + wave * 32 + l32;
   bf16x8 kreg[NKK], vreg[NKK];
+  {
+    const long long off = (long long)b * kt.kv_bs + (long long)min(key_in_blk, kt.kv_rows - 1) * rs + h * D;
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) {
-    const bf16x8 kx = *(const bf16x8*)(krow + 16 * kk + 8 * hi);
-    vreg[kk] = *(const bf16x8*)(vrow + 16 * kk + 8 * hi);
-    if (fkrow) {
-      *(bf16x8*)(fkrow + 16 * kk + 8 * hi) = kx;
-      *(bf16x8*)(fvrow + 16 * kk + 8 * hi) = vreg[kk];
+    for (int kk = 0; kk < NKK; ++kk) {
+      kreg[kk] = *(const bf16x8*)(kt.k + off + 16 * kk + 8 * hi);
+      vreg[kk] = *(const bf16x8*)(kt.v + off + 16 * kk + 8 * hi);
     }
-    kreg[kk] = kx;
   }
   f32x16 dkacc[NDT], dvacc[NDT];
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) dkacc[dt][i] = dvacc[dt][i] = 0.f;
+  dkdv_start<NDT, true>(p, kt.slot, b, h, key_in_blk, hi, dkacc);
+  dkdv_start<NDT, false>(p, kt.slot, b, h, key_in_blk, hi, dvacc);
 
-  // query tiles with at least one query that sees a key of this workgroup; from
-  // qt_free on every query sees every key (no mask)
-  const int wg_first_k = hs.k_pos0 + kt * kKB;
-  const int n_qtiles = p.c / kQB;
-  int qt0 = 0, qt_free = 0;
-  if (p.causal) {
-    const int rel = wg_first_k - hs.q_pos0;
-    qt0 = rel <= 0 ? 0 : min(n_qtiles, rel / kQB);
-    const int rel_last = wg_first_k + kKB - 1 - hs.q_pos0;  // last key's offset in the q block
-    qt_free = rel_last < 0 ? 0 : min(n_qtiles, (rel_last + kQB - 1) / kQB);
-    qt_free = max(qt_free, qt0);
-  }
-
-  const bf16* qbase = (const bf16*)p.q + (long long)b * p.q_bstride + h * D;
-  const bf16* obase = (const bf16*)p.dO + (long long)b * p.q_bstride + h * D;
-  const long long lrow0 = (long long)bh * p.Sq + hs.q_row0;
+  const bf16* qbase = (const bf16*)p.q + (long long)b * kt.q_bs + h * D;
+  const bf16* obase = (const bf16*)p.dO + (long long)b * kt.q_bs + h * D;
+  const long long lrow0 = (long long)kt.bh * kt.q_rows;
   constexpr int RPW = kQB / 4;  // tile rows each wave fills
   int goff[LOADS];
 #pragma unroll
@@ -275,17 +354,19 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
     const int r = wave * RPW + j * ROWS_PER_LOAD + lane / CPR;
     goff[j] = 2 * (r * rs + 8 * ((lane % CPR) ^ swz<D>(r)));
   }
-  auto load_tile = [&](int qt, auto Bc) __attribute__((always_inline)) {
-    const long long t0 = (long long)(hs.q_row0 + qt * kQB) * rs;
+  auto load_tile = [&](int i, auto Bc) __attribute__((always_inline)) {
+    const int row = kt.q_row0 + (kt.qt0 + i - (kt.qt0 + i >= kt.wrap ? kt.wrap : 0)) * kQB;
+    const int rows = min(kQB, kt.q_rows - row);
+    const long long t0 = (long long)row * rs;
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
-      buffer_load_lds16(qbase + t0, kQB * rs * 2, pick(Bc, sQ0, sQ1, sQ2) + (wave_u * RPW + j * ROWS_PER_LOAD) * D,
+      buffer_load_lds16(qbase + t0, rows * rs * 2, pick(Bc, sQ0, sQ1, sQ2) + (wave_u * RPW + j * ROWS_PER_LOAD) * D,
                         goff[j]);
-      buffer_load_lds16(obase + t0, kQB * rs * 2, pick(Bc, sO0, sO1, sO2) + (wave_u * RPW + j * ROWS_PER_LOAD) * D,
+      buffer_load_lds16(obase + t0, rows * rs * 2, pick(Bc, sO0, sO1, sO2) + (wave_u * RPW + j * ROWS_PER_LOAD) * D,
                         goff[j]);
     }
-    if (wave_u == 0) buffer_load_lds4(p.lse + lrow0 + qt * kQB, kQB * 4, pick(Bc, sL0, sL1, sL2), 4 * lane);
-    if (wave_u == 1) buffer_load_lds4(p.delta + lrow0 + qt * kQB, kQB * 4, pick(Bc, sD0, sD1, sD2), 4 * lane);
+    if (wave_u == 0) buffer_load_lds4(p.lse + lrow0 + row, rows * 4, pick(Bc, sL0, sL1, sL2), 4 * lane);
+    if (wave_u == 1) buffer_load_lds4(p.delta + lrow0 + row, rows * 4, pick(Bc, sD0, sD1, sD2), 4 * lane);
   };
   const int qrow = swap_bits23(l32);
   int roff[NKK];
@@ -341,93 +422,42 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
   // One tile t (buffer Bc): loads of tile t+2 (buffer Bc+2), the S'/dP products of tile t+1
   // (buffer Bc+1; Nc: it exists) and, for tile t, P and dS in two groups of 16 queries, each
   // followed by its dV and dK products; then the wait for tile t+2 and the barrier that frees
-  // buffer Bc.  For D = 128 the region is laid out by hand in 20 fenced steps: step s issues
-  // S'/dP product s (s < 16; S' and dP alternate, so consecutive products are independent),
-  // the dV/dK product s - 4 (s >= 4; group (s - 4) / 8) and the vector work of one pair unit
-  // (group 0 at steps 0..3, group 1 at steps 4, 6, 8, 10), with LDS operand reads two steps
-  // ahead.  Other head dims run the same work in program order.
-  auto tile = [&](auto Bc, auto Mc, auto Nc, int qt, f32x16& s_cur, f32x16& dp_cur) __attribute__((always_inline)) {
+  // buffer Bc.
+  auto tile = [&](auto Bc, auto Mc, auto Nc, int i, f32x16& s_cur, f32x16& dp_cur) __attribute__((always_inline)) {
     constexpr int B = decltype(Bc)::value;
     constexpr bool NX = decltype(Nc)::value;
     using Bn = std::integral_constant<int, (B + 1) % 3>;
     using Bl = std::integral_constant<int, (B + 2) % 3>;
-    if (qt + 2 < n_qtiles) load_tile(qt + 2, Bl{});
+    if (i + 2 < kt.n) load_tile(i + 2, Bl{});
     const bf16* qn = pick(Bn{}, sQ0, sQ1, sQ2);  // next tile: row reads
     const bf16* on = pick(Bn{}, sO0, sO1, sO2);
     const bf16* qc = pick(Bc, sQ0, sQ1, sQ2);    // this tile: transpose reads
     const bf16* oc = pick(Bc, sO0, sO1, sO2);
-    const int qpos0 = hs.q_pos0 + qt * kQB;
+    const int qpos0 = kt.q_pos0 + (kt.qt0 + i) * kQB;
     f32x16 s_nx, dp_nx;
     if constexpr (NX) inits(Bn{}, s_nx, dp_nx);
-    if constexpr (D == 128) {
-      bf16x8 aop[16], top[16];
-      uint32_t wp[2][4], ws[2][4];
-      bf16x8 pb[2], dsb[2];
-      constexpr int kPF = 2;
-      auto read_a = [&](auto Sc) __attribute__((always_inline)) {  // product s: kk = s / 2, dP if odd
-        constexpr int S = decltype(Sc)::value;
-        aop[S] = *(const bf16x8*)(((S & 1) ? on : qn) + roff[S / 2]);
-      };
-      auto read_t = [&](auto Qc) __attribute__((always_inline)) {  // product q: group q / 8, dt (q % 8) / 2
-        constexpr int Q = decltype(Qc)::value, g = Q / 8, dt = (Q % 8) / 2;
-        const bf16* src = (Q & 1) ? qc : oc;
-        const bf16x4 lo = lds_read_tr16(src + 16 * g * D + toff[0][dt]);
-        const bf16x4 up = lds_read_tr16(src + 16 * g * D + toff[1][dt]);
-        top[Q] = bf16x8{lo[0], lo[1], lo[2], lo[3], up[0], up[1], up[2], up[3]};
-      };
-      if constexpr (NX) static_for<0, kPF>([&](auto Sc) __attribute__((always_inline)) { read_a(Sc); });
-      static_for<0, 20>([&](auto Sc) __attribute__((always_inline)) {
-        constexpr int S = decltype(Sc)::value;
-        if constexpr (NX && S + kPF < 16) read_a(std::integral_constant<int, S + kPF>{});
-        if constexpr (S + kPF >= 4 && S + kPF < 20) read_t(std::integral_constant<int, S + kPF - 4>{});
-        if constexpr (NX && S < 16) {
-          if constexpr (S & 1)
-            dp_nx = mfma32(aop[S], vreg[S / 2], dp_nx);
-          else
-            s_nx = mfma32(aop[S], kreg[S / 2], s_nx);
-        }
-        if constexpr (S >= 4) {
-          constexpr int q = S - 4, g = q / 8, dt = (q % 8) / 2;
-          if constexpr (q % 8 == 0) {
-            pb[g] = __builtin_bit_cast(bf16x8, u32x4{wp[g][0], wp[g][1], wp[g][2], wp[g][3]});
-            dsb[g] = __builtin_bit_cast(bf16x8, u32x4{ws[g][0], ws[g][1], ws[g][2], ws[g][3]});
-          }
-          if constexpr (q & 1)
-            dkacc[dt] = mfma32(top[q], dsb[g], dkacc[dt]);
-          else
-            dvacc[dt] = mfma32(top[q], pb[g], dvacc[dt]);
-        }
-        if constexpr (S < 4) {
-          unit(Mc, s_cur, dp_cur, qpos0, 0, S, wp[0][S], ws[0][S]);
-        } else if constexpr (S < 12 && S % 2 == 0) {
-          unit(Mc, s_cur, dp_cur, qpos0, 1, (S - 4) / 2, wp[1][(S - 4) / 2], ws[1][(S - 4) / 2]);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    } else {
-      if constexpr (NX) {
+    if constexpr (NX) {
 #pragma unroll
-        for (int kk = 0; kk < NKK; ++kk) {
-          s_nx = mfma32(*(const bf16x8*)(qn + roff[kk]), kreg[kk], s_nx);
-          dp_nx = mfma32(*(const bf16x8*)(on + roff[kk]), vreg[kk], dp_nx);
-        }
+      for (int kk = 0; kk < NKK; ++kk) {
+        s_nx = mfma32(*(const bf16x8*)(qn + roff[kk]), kreg[kk], s_nx);
+        dp_nx = mfma32(*(const bf16x8*)(on + roff[kk]), vreg[kk], dp_nx);
       }
+    }
 #pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        uint32_t wp[4], ws[4];
+    for (int g = 0; g < 2; ++g) {
+      uint32_t wp[4], ws[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) unit(Mc, s_cur, dp_cur, qpos0, g, u, wp[u], ws[u]);
-        const bf16x8 pbg = __builtin_bit_cast(bf16x8, u32x4{wp[0], wp[1], wp[2], wp[3]});
-        const bf16x8 dsg = __builtin_bit_cast(bf16x8, u32x4{ws[0], ws[1], ws[2], ws[3]});
+      for (int u = 0; u < 4; ++u) unit(Mc, s_cur, dp_cur, qpos0, g, u, wp[u], ws[u]);
+      const bf16x8 pbg = __builtin_bit_cast(bf16x8, u32x4{wp[0], wp[1], wp[2], wp[3]});
+      const bf16x8 dsg = __builtin_bit_cast(bf16x8, u32x4{ws[0], ws[1], ws[2], ws[3]});
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
-          const bf16x4 olo = lds_read_tr16(oc + 16 * g * D + toff[0][dt]);
-          const bf16x4 oup = lds_read_tr16(oc + 16 * g * D + toff[1][dt]);
-          dvacc[dt] = mfma32(bf16x8{olo[0], olo[1], olo[2], olo[3], oup[0], oup[1], oup[2], oup[3]}, pbg, dvacc[dt]);
-          const bf16x4 qlo = lds_read_tr16(qc + 16 * g * D + toff[0][dt]);
-          const bf16x4 qup = lds_read_tr16(qc + 16 * g * D + toff[1][dt]);
-          dkacc[dt] = mfma32(bf16x8{qlo[0], qlo[1], qlo[2], qlo[3], qup[0], qup[1], qup[2], qup[3]}, dsg, dkacc[dt]);
-        }
+      for (int dt = 0; dt < NDT; ++dt) {
+        const bf16x4 olo = lds_read_tr16(oc + 16 * g * D + toff[0][dt]);
+        const bf16x4 oup = lds_read_tr16(oc + 16 * g * D + toff[1][dt]);
+        dvacc[dt] = mfma32(bf16x8{olo[0], olo[1], olo[2], olo[3], oup[0], oup[1], oup[2], oup[3]}, pbg, dvacc[dt]);
+        const bf16x4 qlo = lds_read_tr16(qc + 16 * g * D + toff[0][dt]);
+        const bf16x4 qup = lds_read_tr16(qc + 16 * g * D + toff[1][dt]);
+        dkacc[dt] = mfma32(bf16x8{qlo[0], qlo[1], qlo[2], qlo[3], qup[0], qup[1], qup[2], qup[3]}, dsg, dkacc[dt]);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // tile t+2 landed
@@ -438,9 +468,9 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
     }
   };
 
-  if (qt0 < n_qtiles) {
-    load_tile(qt0, std::integral_constant<int, 0>{});
-    if (qt0 + 1 < n_qtiles) load_tile(qt0 + 1, std::integral_constant<int, 1>{});
+  if (kt.n > 0) {
+    load_tile(0, std::integral_constant<int, 0>{});
+    if (kt.n > 1) load_tile(1, std::integral_constant<int, 1>{});
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     f32x16 s_cur, dp_cur;  // S' and dP of the tile being processed
@@ -450,15 +480,15 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
       s_cur = mfma32(*(const bf16x8*)(sQ0 + roff[kk]), kreg[kk], s_cur);
       dp_cur = mfma32(*(const bf16x8*)(sO0 + roff[kk]), vreg[kk], dp_cur);
     }
-    // buffer of tile qt is (qt - qt0) % 3, known at compile time in a loop unrolled by 3;
-    // tiles [a, e) all have a successor
+    // buffer of tile i is i % 3, known at compile time in a loop unrolled by 3; tiles [a, e)
+    // all have a successor
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
     auto run = [&](auto Mc, int a, int e) __attribute__((always_inline)) {
       int it = a;
-      if (it < e && (it - qt0) % 3 == 1) tile(I1{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
-      if (it < e && (it - qt0) % 3 == 2) tile(I2{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
+      if (it < e && it % 3 == 1) tile(I1{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
+      if (it < e && it % 3 == 2) tile(I2{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
       for (; it + 2 < e; it += 3) {
         tile(I0{}, Mc, std::true_type{}, it, s_cur, dp_cur);
         tile(I1{}, Mc, std::true_type{}, it + 1, s_cur, dp_cur);
@@ -467,22 +497,22 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
       if (it < e) tile(I0{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
       if (it < e) tile(I1{}, Mc, std::true_type{}, it++, s_cur, dp_cur);
     };
-    const int ql = n_qtiles - 1;
-    const int split = max(qt0, min(qt_free, ql));  // masked tiles first
-    run(std::true_type{}, qt0, split);
-    run(std::false_type{}, split, ql);
+    const int il = kt.n - 1;
+    const int split = max(0, min(kt.qt_free - kt.qt0, il));  // masked tiles first
+    run(std::true_type{}, 0, split);
+    run(std::false_type{}, split, il);
     // last tile: no successor
-    const int ph = (ql - qt0) % 3;
+    const int ph = il % 3;
     auto last = [&](auto Mc) __attribute__((always_inline)) {
-      if (ph == 0) tile(I0{}, Mc, std::false_type{}, ql, s_cur, dp_cur);
-      else if (ph == 1) tile(I1{}, Mc, std::false_type{}, ql, s_cur, dp_cur);
-      else tile(I2{}, Mc, std::false_type{}, ql, s_cur, dp_cur);
+      if (ph == 0) tile(I0{}, Mc, std::false_type{}, il, s_cur, dp_cur);
+      else if (ph == 1) tile(I1{}, Mc, std::false_type{}, il, s_cur, dp_cur);
+      else tile(I2{}, Mc, std::false_type{}, il, s_cur, dp_cur);
     };
-    if (ql < qt_free) last(std::true_type{}); else last(std::false_type{});
+    if (kt.qt0 + il < kt.qt_free) last(std::true_type{}); else last(std::false_type{});
   }
 
-  dkdv_epilogue<NDT, true>(p, slot, b, h, key_in_blk, hi, dkacc);
-  dkdv_epilogue<NDT, false>(p, slot, b, h, key_in_blk, hi, dvacc);
+  dkdv_finish<NDT, true>(p, kt.slot, b, h, key_in_blk, hi, dkacc);
+  dkdv_finish<NDT, false>(p, kt.slot, b, h, key_in_blk, hi, dvacc);
 }
 
 // =====================================================================================
@@ -508,7 +538,8 @@ __global__ __launch_bounds__(kBT, 1) void bwd_dkdv_bf16_kernel(const BwdStep p) 
 // =====================================================================================
 constexpr int kPT = 768;
 
-__global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
+template <class P>
+__global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const P p) {
   constexpr int D = 128, NKK = D / 16, NDT = D / 32, CPR = D / 8, ROWS_PER_LOAD = 64 / CPR;
   static_assert(kQB == 8 * ROWS_PER_LOAD, "waves 0-7 fill 4 rows of a tile each");
   // Q tiles 0-3, then dO tiles 0-3, in one LDS object, so that every read of a ring buffer
@@ -530,51 +561,34 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
   using I2 = std::integral_constant<int, 2>;
   using I3 = std::integral_constant<int, 3>;
 
-  const int n_kt = p.c / kKB;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_kt;
-  const int Lid = xcd_swizzle(blockIdx.x, total);
-  const int grp = Lid / n_kt, kt = Lid % n_kt;
-  const int slot = grp / BH, bh = grp % BH;
-  const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
+  KeyTile kt;
+  if (!key_tile(p, kt)) return;
+  const int b = kt.bh / p.H, h = kt.bh % p.H;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS destinations in scalar registers
   const int col = wave_u & 3;                                   // the wave's 32-key column
   const int rs = p.H * D;
-  const int key_in_blk = kt * kKB + col * 32 + l32;  // this lane's key (B-operand column)
+  const int key_in_blk = kt.key0 + col * 32 + l32;  // this lane's key (B-operand column)
+  const int n = kt.n;  // tiles visited
 
-  // query tiles with at least one query that sees a key of this workgroup; from
-  // qt_free on every query sees every key (no mask)
-  const int wg_first_k = hs.k_pos0 + kt * kKB;
-  const int n_qtiles = p.c / kQB;
-  int qt0 = 0, qt_free = 0;
-  if (p.causal) {
-    const int rel = wg_first_k - hs.q_pos0;
-    qt0 = rel <= 0 ? 0 : min(n_qtiles, rel / kQB);
-    const int rel_last = wg_first_k + kKB - 1 - hs.q_pos0;  // last key's offset in the q block
-    qt_free = rel_last < 0 ? 0 : min(n_qtiles, (rel_last + kQB - 1) / kQB);
-    qt_free = max(qt_free, qt0);
-  }
-  const int n = n_qtiles - qt0;  // tiles visited; tile i of the workgroup is query tile qt0 + i
-
-  const bf16* qbase = (const bf16*)p.q + (long long)b * p.q_bstride + h * D;
-  const bf16* obase = (const bf16*)p.dO + (long long)b * p.q_bstride + h * D;
-  const long long lrow0 = (long long)bh * p.Sq + hs.q_row0;
+  const bf16* qbase = (const bf16*)p.q + (long long)b * kt.q_bs + h * D;
+  const bf16* obase = (const bf16*)p.dO + (long long)b * kt.q_bs + h * D;
+  const long long lrow0 = (long long)kt.bh * kt.q_rows;
   const int lrow = (wave_u & 7) * ROWS_PER_LOAD + lane / CPR;  // the tile row this lane fills (waves 0-7)
   const int goff = 2 * (lrow * rs + 8 * ((lane % CPR) ^ swz<D>(lrow)));
   // tile i into ring buffer buf: the Q and dO rows by waves 0-7, -lse sqrt(D) by wave 0,
   // -Delta by wave 1
   auto load_tile = [&](int i, int buf) __attribute__((always_inline)) {
-    const int qt = qt0 + i;
-    const long long t0 = (long long)(hs.q_row0 + qt * kQB) * rs;
+    const int row = kt.q_row0 + (kt.qt0 + i - (kt.qt0 + i >= kt.wrap ? kt.wrap : 0)) * kQB;
+    const int rows = min(kQB, kt.q_rows - row);  // rows past the end read as zero
+    const long long t0 = (long long)row * rs;
     if (wave_u < 8) {
-      dma_lds16(make_rsrc(qbase + t0, kQB * rs * 2), lds_addr(sQO + (buf * kQB + wave_u * ROWS_PER_LOAD) * D), goff);
-      dma_lds16(make_rsrc(obase + t0, kQB * rs * 2), lds_addr(sQO + ((4 + buf) * kQB + wave_u * ROWS_PER_LOAD) * D),
+      dma_lds16(make_rsrc(qbase + t0, rows * rs * 2), lds_addr(sQO + (buf * kQB + wave_u * ROWS_PER_LOAD) * D), goff);
+      dma_lds16(make_rsrc(obase + t0, rows * rs * 2), lds_addr(sQO + ((4 + buf) * kQB + wave_u * ROWS_PER_LOAD) * D),
                 goff);
     }
-    if (wave_u == 0) dma_lds4(make_rsrc(p.lse + lrow0 + qt * kQB, kQB * 4), lds_addr(sLD + buf * 64), 4 * lane);
-    if (wave_u == 1) dma_lds4(make_rsrc(p.delta + lrow0 + qt * kQB, kQB * 4), lds_addr(sLD + (4 + buf) * 64), 4 * lane);
+    if (wave_u == 0) dma_lds4(make_rsrc(p.lse + lrow0 + row, rows * 4), lds_addr(sLD + buf * 64), 4 * lane);
+    if (wave_u == 1) dma_lds4(make_rsrc(p.delta + lrow0 + row, rows * 4), lds_addr(sLD + (4 + buf) * 64), 4 * lane);
   };
   // regions [a, e) with the buffer of region i (i % 4) known at compile time
   auto run4 = [&](int a, int e, auto&& f) __attribute__((always_inline)) {
@@ -612,30 +626,16 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
 
   if (wave_u < 4) {
     // ---------------------------------------------------------------- row wave
-    const int kpos = hs.k_pos0 + key_in_blk;
+    const int kpos = kt.kpos0 + col * 32 + l32;
     const float sl2 = p.scale * kLog2e;
-    const bf16* krow = (const bf16*)hs.k + (long long)b * hs.kv_bstride + (long long)key_in_blk * rs + h * D;
-    const bf16* vrow = (const bf16*)hs.v + (long long)b * hs.kv_bstride + (long long)key_in_blk * rs + h * D;
-    // forwarding: the row waves write the rows of the workgroup's 128 keys, as loaded,
-    // into the next host's receive slot for the next ring step (layout [B, c, H, D])
-    const int fto = p.fwd.to[slot] - 1;  // destination slot, or -1
-    bf16* fkrow = nullptr;
-    bf16* fvrow = nullptr;
-    if (fto >= 0 && p.fwd.k0 != nullptr && p.fwd.v0 != nullptr) {
-      const long long off = (long long)fto * p.fwd.blk_bytes + 2 * (((long long)b * p.c + key_in_blk) * rs + h * D);
-      fkrow = (bf16*)((char*)p.fwd.k0 + off);
-      fvrow = (bf16*)((char*)p.fwd.v0 + off);
-    }
     bf16x8 kreg[NKK], vreg[NKK];
+    {
+      const long long off = (long long)b * kt.kv_bs + (long long)min(key_in_blk, kt.kv_rows - 1) * rs + h * D;
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      const bf16x8 kx = *(const bf16x8*)(krow + 16 * kk + 8 * hi);
-      vreg[kk] = *(const bf16x8*)(vrow + 16 * kk + 8 * hi);
-      if (fkrow) {
-        *(bf16x8*)(fkrow + 16 * kk + 8 * hi) = kx;
-        *(bf16x8*)(fvrow + 16 * kk + 8 * hi) = vreg[kk];
+      for (int kk = 0; kk < NKK; ++kk) {
+        kreg[kk] = *(const bf16x8*)(kt.k + off + 16 * kk + 8 * hi);
+        vreg[kk] = *(const bf16x8*)(kt.v + off + 16 * kk + 8 * hi);
       }
-      kreg[kk] = kx;
     }
     if (n == 0) return;
     const int qrow = swap_bits23(l32);
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
       const bf16* qn = qt_lds(Bn{});
       const bf16* on = ot_lds(Bn{});
       u32x4* xw = ((B & 1) ? sX1 : sX0) + col * 4 * 64 + lane;
-      const int qpos0 = hs.q_pos0 + (qt0 + i) * kQB;
+      const int qpos0 = kt.q_pos0 + (kt.qt0 + i) * kQB;
       f32x16 s_nx, dp_nx;
       if constexpr (NX) inits(Bn{}, s_nx, dp_nx);
       bf16x8 aop[16];
@@ -736,14 +736,14 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
       }
     };
     // masked tiles first; every tile but the last has a successor
-    const int ms = max(0, min(qt_free - qt0, n - 1));
+    const int ms = max(0, min(kt.qt_free - kt.qt0, n - 1));
     run4(0, ms, [&](auto Bc, int i) __attribute__((always_inline)) {
       region(Bc, std::true_type{}, std::true_type{}, i);
     });
     run4(ms, n - 1, [&](auto Bc, int i) __attribute__((always_inline)) {
       region(Bc, std::false_type{}, std::true_type{}, i);
     });
-    if (qt0 + n - 1 < qt_free)
+    if (kt.qt0 + n - 1 < kt.qt_free)
       at(n - 1, [&](auto Bc, int i) __attribute__((always_inline)) { region(Bc, std::true_type{}, std::false_type{}, i); });
     else
       at(n - 1, [&](auto Bc, int i) __attribute__((always_inline)) { region(Bc, std::false_type{}, std::false_type{}, i); });
@@ -755,10 +755,7 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
   auto column = [&](auto Kc) __attribute__((always_inline)) {
     constexpr bool DK = decltype(Kc)::value;
     f32x16 acc[NDT];
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    dkdv_start<NDT, DK>(p, kt.slot, b, h, key_in_blk, hi, acc);
     if (n > 0) {
       const int g16 = lane >> 4, li = lane & 15;
       int toff[2][NDT];
@@ -796,7 +793,7 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
         if (i < n) sync();
       }
     }
-    dkdv_epilogue<NDT, DK>(p, slot, b, h, key_in_blk, hi, acc);
+    dkdv_finish<NDT, DK>(p, kt.slot, b, h, key_in_blk, hi, acc);
   };
   if (wave_u >= 8) column(std::true_type{});
   else column(std::false_type{});
@@ -815,8 +812,9 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const BwdStep p) {
 // =====================================================================================
 constexpr int kQQ = 128, kKK = 64;
 
-template <int D>
-__global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
+template <int D, class P>
+__global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const P p) {
+  constexpr bool RING = std::is_same_v<P, BwdRing>;
   constexpr int NKK = D / 16, NDT = D / 32, CPR = D / 8;
   constexpr int ROWS_PER_LOAD = 64 / CPR, LOADS = kKK / 4 / ROWS_PER_LOAD;
   // one LDS object per buffer (see the dK/dV kernel)
@@ -832,29 +830,58 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
     if constexpr (decltype(Bc)::value == 0) return a; else return b;
   };
 
-  const int n_qt = p.c / kQQ;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_qt;
-  const int Lid = xcd_swizzle(blockIdx.x, total);
-  const int grp = Lid / n_qt;
-  const int qt = n_qt - 1 - (Lid % n_qt);
-  const int slot = grp / BH, bh = grp % BH;
+  // the workgroup's query rows and the blocks it folds (as in the forward kernel)
+  int bh, q_tile_row, tile_first_q, k_pos0, kv_rows, q_rows, host = 0, flags = kFirst | kLast;
+  long long q_bs;
+  const bf16 *kbase, *vbase;
+  const int blk_tiles = p.c / kKK;
+  if constexpr (RING) {
+    const int n_qt = (p.S + kQQ - 1) / kQQ;
+    int qt;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, bh, qt)) return;
+    q_tile_row = tile_first_q = qt * kQQ;
+    host = q_tile_row / p.c;
+    k_pos0 = host * p.c;
+    kv_rows = q_rows = p.S;
+    q_bs = p.bstride;
+    const long long off = (long long)(bh / p.H) * p.bstride + (bh % p.H) * D;
+    kbase = (const bf16*)p.k + off;
+    vbase = (const bf16*)p.v + off;
+  } else {
+    const int n_qt = p.c / kQQ;
+    const int BH = p.B * p.H;
+    const int L = xcd_swizzle(blockIdx.x, p.n_slots * BH * n_qt);
+    const int grp = L / n_qt, qt = n_qt - 1 - (L % n_qt);
+    const StepHost& hs = p.host[grp / BH];
+    bh = grp % BH;
+    q_tile_row = hs.q_row0 + qt * kQQ;
+    tile_first_q = hs.q_pos0 + qt * kQQ;
+    k_pos0 = hs.k_pos0;
+    kv_rows = hs.kv_rows;
+    q_rows = p.Sq;
+    q_bs = p.q_bstride;
+    flags = hs.flags;
+    const long long off = (long long)(bh / p.H) * hs.kv_bstride + (bh % p.H) * D;
+    kbase = (const bf16*)hs.k + off;
+    vbase = (const bf16*)hs.v + off;
+    if (q_tile_row >= p.Sq) return;
+  }
   const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // uniform: LDS destinations in scalar registers
   const int rs = p.H * D;
 
-  const int qr = hs.q_row0 + qt * kQQ + wave * 32 + l32;
-  const int qpos = hs.q_pos0 + qt * kQQ + wave * 32 + l32;
-  const int tile_first_q = hs.q_pos0 + qt * kQQ;
-  const long long lrow = (long long)bh * p.Sq + qr;
+  const int qr = q_tile_row + wave * 32 + l32;
+  const int qpos = tile_first_q + wave * 32 + l32;
+  const int qr_ld = min(qr, q_rows - 1);  // rows past the end: any row (nothing of them is stored)
+  const long long lrow = (long long)bh * q_rows + qr_ld;
+  const long long qoff = (long long)b * q_bs + (long long)qr_ld * rs + h * D;
   const float nlse_s = p.lse[lrow];  // -lse sqrt(D) (written by the preprocess kernel)
   const float ndlt = p.delta[lrow];  // -Delta
 
   bf16x8 qreg[NKK], oreg[NKK];
   {
-    const long long off = (long long)b * p.q_bstride + (long long)qr * rs + h * D + 8 * hi;
+    const long long off = qoff + 8 * hi;
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) {
       qreg[kk] = *(const bf16x8*)((const bf16*)p.q + off + 16 * kk);
@@ -866,20 +893,36 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) asm volatile("" ::"v"(qreg[kk]), "v"(oreg[kk]));
   }
+  // dQ^T: zero, or what the host's earlier ring steps accumulated
   f32x16 dqacc[NDT];
 #pragma unroll
   for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
     for (int i = 0; i < 16; ++i) dqacc[dt][i] = 0.f;
-
-  int nt = p.c / kKK, n_full = nt;
-  if (p.causal) {
-    const int vis = tile_first_q + kQQ - hs.k_pos0;
-    nt = min(nt, max(0, (vis + kKK - 1) / kKK));
-    n_full = min(nt, max(0, (tile_first_q - hs.k_pos0 + 1) / kKK));
+  if constexpr (!RING) {
+    if (!(flags & kFirst)) {
+#pragma unroll
+      for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+        for (int gg = 0; gg < 4; ++gg) {
+          const f32x4 c4 = *(const f32x4*)(p.dq + qoff + 32 * dt + 8 * gg + 4 * hi);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dqacc[dt][4 * gg + e] = c4[e];
+        }
+    }
   }
-  const bf16* kbase = (const bf16*)hs.k + (long long)b * hs.kv_bstride + h * D;
-  const bf16* vbase = (const bf16*)hs.v + (long long)b * hs.kv_bstride + h * D;
+
+  // tiles of the first block (the last ones under the mask), then the other blocks in ring
+  // order: the walk of the forward kernel
+  int n_own = blk_tiles, n_full = blk_tiles;
+  if (p.causal) {
+    n_own = min(n_own, max(0, (tile_first_q + kQQ - k_pos0 + kKK - 1) / kKK));
+    n_own = min(n_own, (max(0, RING ? kv_rows - k_pos0 : kv_rows) + kKK - 1) / kKK);
+    n_full = min(n_own, max(0, (tile_first_q - k_pos0 + 1) / kKK));
+  }
+  int nt = n_own;
+  if constexpr (RING) nt += (p.causal ? host : p.N - 1) * blk_tiles;
+  int w_row = RING ? k_pos0 : 0, w_left = n_own, w_blk = host;  // next tile to load
 
   // direct-to-LDS staging: load j of wave w fills rows j * 4 ROWS_PER_LOAD + w ROWS_PER_LOAD +
   // lane / CPR.  The swizzle of those rows does not depend on j, so all loads of a lane read
@@ -887,9 +930,18 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
   static_assert(16 == LOADS * ROWS_PER_LOAD, "each wave fills LOADS row groups");
   const int goff = 2 * ((wave * ROWS_PER_LOAD + lane / CPR) * rs +
                         8 * ((lane % CPR) ^ swz<D>(wave * ROWS_PER_LOAD + lane / CPR)));
-  auto load_tile = [&](int it, auto Bc) __attribute__((always_inline)) {
-    const long long t0 = (long long)it * kKK * rs;
-    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase + t0, kKK * rs * 2), rv = make_rsrc(vbase + t0, kKK * rs * 2);
+  auto load_tile = [&](auto Bc) __attribute__((always_inline)) {  // the next tile of the walk
+    const long long t0 = (long long)w_row * rs;
+    const int bytes = min(kKK, kv_rows - w_row) * rs * 2;  // rows past the end read as zero
+    w_row += kKK;
+    if constexpr (RING) {
+      if (--w_left == 0) {
+        w_blk = w_blk == 0 ? p.N - 1 : w_blk - 1;
+        w_row = w_blk * p.c;
+        w_left = blk_tiles;
+      }
+    }
+    const __amdgpu_buffer_rsrc_t rk = make_rsrc(kbase + t0, bytes), rv = make_rsrc(vbase + t0, bytes);
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const int row = (j * 4 + wave_u) * ROWS_PER_LOAD, so = j * 8 * ROWS_PER_LOAD * rs;
@@ -922,7 +974,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
   auto body_sched = [&](auto Bc, auto Mc, int it) __attribute__((always_inline)) {
     constexpr int B = decltype(Bc)::value;
     constexpr bool MASK = decltype(Mc)::value;
-    if (it + 1 < nt) load_tile(it + 1, std::integral_constant<int, B ^ 1>{});
+    if (it + 1 < nt) load_tile(std::integral_constant<int, B ^ 1>{});
     const bf16* kt = pick(Bc, sK0, sK1);
     const bf16* vt = pick(Bc, sV0, sV1);
     constexpr int NA = 2 * NKK;       // S^T and dP^T products of one 32-key half
@@ -932,7 +984,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
     f32x16 sacc[2], dpacc[2];
     bf16x8 aop[2 * NA], top[NQ];
     u32x4 w[4];  // dS^T of the four 16-key groups, packed bf16: the B operands as they are
-    const int kpos0 = hs.k_pos0 + it * kKK;
+    const int kpos0 = k_pos0 + it * kKK;
     // step S < 2 NA: half h = S / NA, product j = S % NA of it (S^T if j even, dP^T if odd,
     // reduction slice kk = j / 2); step S >= 2 NA: dQ^T product q = S - 2 NA (keys of group
     // kb = q / NDT, dims 32 (q % NDT)..)
@@ -997,7 +1049,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
   auto body_plain = [&](auto Bc, auto Mc, int it) __attribute__((always_inline)) {
     constexpr int B = decltype(Bc)::value;
     constexpr bool MASK = decltype(Mc)::value;
-    if (it + 1 < nt) load_tile(it + 1, std::integral_constant<int, B ^ 1>{});
+    if (it + 1 < nt) load_tile(std::integral_constant<int, B ^ 1>{});
     const bf16* kt = pick(Bc, sK0, sK1);
     const bf16* vt = pick(Bc, sV0, sV1);
     f32x16 sacc[2], dpacc[2];
@@ -1014,7 +1066,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
         dpacc[mt] = mfma32(*(const bf16x8*)(vt + 32 * mt * D + roff[kk]), oreg[kk], dpacc[mt]);
       }
     }
-    const int kpos0 = hs.k_pos0 + it * kKK;
+    const int kpos0 = k_pos0 + it * kKK;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       u32x4 w;
@@ -1062,44 +1114,35 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const BwdStep p) {
     }
     if (it < e) body(std::integral_constant<int, 0>{}, Mc, it);
   };
-  if (nt > 0) load_tile(0, std::integral_constant<int, 0>{});
+  if (nt > 0) load_tile(std::integral_constant<int, 0>{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   run(std::false_type{}, 0, n_full);
-  run(std::true_type{}, n_full, nt);
+  run(std::true_type{}, n_full, n_own);
+  if constexpr (RING) run(std::false_type{}, n_own, nt);
 
-  // dq (float32, [B, Sq, H, D]) += scale * dQ; with dq_out set, the host's first active
-  // step writes instead of adding and its last writes the bf16 result
-  const long long qoff = (long long)b * p.q_bstride + (long long)qr * rs + h * D;
-  float* dqrow = p.dq + qoff;
-  const bool first = p.dq_out != nullptr && (hs.flags & kFirst);
-  const bool fin = p.dq_out != nullptr && (hs.flags & kLast);
-  // all carried values loaded before the first store (one memory round trip, not 16)
-  f32x4 qin[NDT][4];
-  if (first) {
+  // the host's last step writes dq = scale * dQ in bf16; earlier ones save the accumulators
+  if (qr >= q_rows) return;
+  if (flags & kLast) {
+    bf16* out = [&] { if constexpr (RING) return (bf16*)p.dq; else return (bf16*)p.dq_out; }() + qoff;
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int gg = 0; gg < 4; ++gg) qin[dt][gg] = f32x4{0.f, 0.f, 0.f, 0.f};
-  } else {
+      for (int gg = 0; gg < 4; ++gg) {
+        const f32x16& a = dqacc[dt];
+        *(u32x2*)(out + 32 * dt + 8 * gg + 4 * hi) =
+            u32x2{pack_bf16x2(a[4 * gg] * p.scale, a[4 * gg + 1] * p.scale),
+                  pack_bf16x2(a[4 * gg + 2] * p.scale, a[4 * gg + 3] * p.scale)};
+      }
+  } else if constexpr (!RING) {
 #pragma unroll
     for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-      for (int gg = 0; gg < 4; ++gg) qin[dt][gg] = *(const f32x4*)(dqrow + 32 * dt + 8 * gg + 4 * hi);
+      for (int gg = 0; gg < 4; ++gg) {
+        const f32x16& a = dqacc[dt];
+        *(f32x4*)(p.dq + qoff + 32 * dt + 8 * gg + 4 * hi) = f32x4{a[4 * gg], a[4 * gg + 1], a[4 * gg + 2], a[4 * gg + 3]};
+      }
   }
-#pragma unroll
-  for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-    for (int gg = 0; gg < 4; ++gg) {
-      const int d = 32 * dt + 8 * gg + 4 * hi;
-      f32x4 t = qin[dt][gg];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[e] += dqacc[dt][4 * gg + e] * p.scale;
-      if (fin)
-        *(u32x2*)((bf16*)p.dq_out + qoff + d) = u32x2{pack_bf16x2(t[0], t[1]), pack_bf16x2(t[2], t[3])};
-      else
-        *(f32x4*)(dqrow + d) = t;
-    }
 }
 
 // =====================================================================================
@@ -1275,21 +1318,29 @@ hipError_t launch_bwd_pre_f32(const float* o, const float* dO, float* delta, int
 
 hipError_t launch_bwd_bf16(const BwdStep& s, int D, hipStream_t st) {
   if (s.n_slots == 0) return hipSuccess;
-  // a forwarding destination needs both receive bases and a slot size
-  for (int n = 0; n < s.n_slots; ++n)
-    if (s.fwd.to[n] != 0 && (s.fwd.to[n] < 0 || s.fwd.k0 == nullptr || s.fwd.v0 == nullptr || s.fwd.blk_bytes <= 0))
-      return hipErrorInvalidValue;
   // a last touch needs the bf16 outputs
-  for (int n = 0; n < s.n_slots; ++n)
-    if ((s.dkv_flags[n] & kLast) && (s.dk_out == nullptr || s.dv_out == nullptr)) return hipErrorInvalidValue;
+  if (s.whole && (s.dk_out == nullptr || s.dv_out == nullptr)) return hipErrorInvalidValue;
   const int g1 = s.n_slots * s.B * s.H * (s.c / kKB);
   const int g2 = s.n_slots * s.B * s.H * (s.c / kQQ);
   if (D == 128) {
-    hipLaunchKernelGGL(bwd_dkdv_split_kernel, dim3(g1), dim3(kPT), 0, st, s);
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<128>, dim3(g2), dim3(kBT), 0, st, s);
+    hipLaunchKernelGGL(bwd_dkdv_split_kernel<BwdStep>, dim3(g1), dim3(kPT), 0, st, s);
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<128, BwdStep>), dim3(g2), dim3(kBT), 0, st, s);
   } else {
-    hipLaunchKernelGGL(bwd_dkdv_bf16_kernel<64>, dim3(g1), dim3(kBT), 0, st, s);
-    hipLaunchKernelGGL(bwd_dq_bf16_kernel<64>, dim3(g2), dim3(kBT), 0, st, s);
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<64, BwdStep>), dim3(g1), dim3(kBT), 0, st, s);
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<64, BwdStep>), dim3(g2), dim3(kBT), 0, st, s);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_bwd_ring_bf16(const BwdRing& s, int D, hipStream_t st) {
+  const int g1 = ring_grid(s.B * s.H, (s.S + kKB - 1) / kKB);
+  const int g2 = ring_grid(s.B * s.H, (s.S + kQQ - 1) / kQQ);
+  if (D == 128) {
+    hipLaunchKernelGGL(bwd_dkdv_split_kernel<BwdRing>, dim3(g1), dim3(kPT), 0, st, s);
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<128, BwdRing>), dim3(g2), dim3(kBT), 0, st, s);
+  } else {
+    hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<64, BwdRing>), dim3(g1), dim3(kBT), 0, st, s);
+    hipLaunchKernelGGL((bwd_dq_bf16_kernel<64, BwdRing>), dim3(g2), dim3(kBT), 0, st, s);
   }
   return hipGetLastError();
 }

@@ -61,7 +61,8 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, int num_byte
 }
 
 // As buffer_load_lds16, the read address being base + voff_bytes + soff_bytes with soff_bytes
-// wave-uniform (a scalar register: no vector register per load).
+// wave-uniform (a scalar register: no vector register per load).  The sum of both offsets is
+// held against num_bytes (checked on the device, sums past num_bytes by either part).
 __device__ __forceinline__ void buffer_load_lds16_so(const void* base, int num_bytes, void* lds_dst, int voff_bytes,
                                                      int soff_bytes) {
 #if __HIP_DEVICE_COMPILE__

@@ -11,20 +11,6 @@ constexpr int kMaxSlots = 64;        // hosts per launch (= maximum ring size)
 constexpr int kFirst = 1;            // host's first active step: start from m=-inf, l=0, acc=0
 constexpr int kLast = 2;             // host's last active step: finalize o = acc / l, lse
 
-// Forwarding of the key/value block a host holds to the host that needs it at the next
-// ring step (host i at step t holds block j = (i - t) mod N, which host i+1 holds at step
-// t+1).  The bf16 dK/dV kernel copies the block's rows, as it loads them, into that host's
-// receive slot for the next step: slot s of the next step's half of
-// the receive buffers starts at k0 + s * blk_bytes (v0 for values), in the layout
-// [B, c, H, D].  to[n] is 1 + the destination slot of launch slot n, or 0 for none, so
-// that a zero-initialised descriptor forwards nothing.
-struct StepForward {
-  const void* k0;
-  const void* v0;
-  long long blk_bytes;
-  signed char to[kMaxSlots];
-};
-
 // One host's work in one ring step.
 struct StepHost {
   const void* k;          // key block, row 0 (batch 0, head 0)
@@ -70,25 +56,34 @@ struct BwdStep {
   const void* dO;         // [B, Sq, H, D]
   const float* lse;       // [B, H, Sq]  lse, natural log (float32 kernels); -lse sqrt(D) (bf16)
   const float* delta;     // [B, H, Sq]  rowsum(dO * o) (float32 kernels); its negative (bf16)
-  float* dq;              // float32 [B, Sq, H, D]
+  float* dq;              // float32 [B, Sq, H, D] (bf16: accumulators between the host's steps)
   float* dk;              // float32 [B, Skv, H, D]: gradient of the block each host holds
   float* dv;              //   (home position of that block: see dkv_row0)
   int dkv_row0[kMaxSlots];// first row of the host's current block in dk / dv
   long long q_bstride;    // Sq * H * D
-  long long dkv_bstride;  // Skv * H * D
+  long long dkv_bstride;  // elements between consecutive batches of dk / dv
   int n_slots, B, H, Sq, c, causal;
+  int Skv;                // rows of dk / dv that exist
   float scale;
-  StepForward fwd;        // bf16 dK/dV kernel only: forward each slot's block (the keys a
-                          // workgroup holds) to the next host
-  // bf16 kernels, when the call holds every contribution to the gradients: the block a slot
-  // holds is touched for the first time (kFirst: write dk / dv instead of adding into them)
-  // or the last time (kLast: write the final sum, rounded, to dk_out / dv_out instead).
-  // 0 = add into dk / dv.
+  // bf16 kernels.  whole: the call holds every contribution to dk / dv, so these hold the
+  // accumulators between steps; the block a slot holds is touched for the first (kFirst: start
+  // from zero) or the last time (kLast: the sum goes out, rounded, to dk_out / dv_out).
+  // Otherwise contributions are added into dk / dv.
+  int whole;
   unsigned char dkv_flags[kMaxSlots];
   void* dk_out;           // bf16 [B, Skv, H, D] results (rows at the block's home position)
   void* dv_out;
-  void* dq_out;           // bf16 [B, Sq, H, D]; when set, dq follows the host's kFirst / kLast
-                          // flags the same way (null: always add into dq)
+  void* dq_out;           // bf16 [B, Sq, H, D], written on a host's kLast step
+};
+
+// Backward over the whole ring, bf16: one launch for dK and dV, one for dQ.
+struct BwdRing {
+  const void *q, *k, *v, *dO;  // [B, S, H, D]
+  const float *lse, *delta;    // -lse sqrt(D) and -Delta, [B, H, S]
+  void *dq, *dk, *dv;          // [B, S, H, D]
+  long long bstride;           // S * H * D
+  int B, H, S, c, N, causal;   // causal: S need not fill the N blocks of c rows
+  float scale;
 };
 
 hipError_t launch_fwd_bf16(const FwdStep& s, int D, hipStream_t st);
@@ -100,6 +95,7 @@ hipError_t launch_bwd_pre_bf16(const void* o, const void* dO, const float* lse, 
 hipError_t launch_bwd_pre_f32(const float* o, const float* dO, float* delta, int B, int S, int H,
                               int D, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdStep& s, int D, hipStream_t st);
+hipError_t launch_bwd_ring_bf16(const BwdRing& s, int D, hipStream_t st);
 hipError_t launch_bwd_f32(const BwdStep& s, int D, hipStream_t st);
 hipError_t launch_cast_f32_bf16(const float* src, void* dst, long long n, hipStream_t st);
 hipError_t launch_zero_f32(float* p, long long n, hipStream_t st);

@@ -4,15 +4,15 @@
 // key/value block live in device memory; host i folds key/value block order(i, t) --
 // (i - t) mod n_hosts for the ring -- at step t.
 //
-// The bf16 forward over the whole ring in ring order runs as one launch that walks every query
-// tile over its host's blocks, read where they lie.  Every other call runs n_hosts steps,
+// bf16 calls over the whole ring in ring order run as one launch (backward: one for dK/dV,
+// one for dQ) that walks every query (key) tile over the blocks it meets, read where they
+// lie.  Every other call runs n_hosts steps,
 // every host with work at a step being one slot of a single kernel launch.  Step 0 reads each
 // host's block where it lies (a host's own block needs no transfer).  For t >= 1 the
 // block comes from that host's receive buffer: two slots used alternately (the
 // double buffer of the paper's memory accounting: current and receiving key/value
 // blocks).  The slot for step t+1 is filled while step t computes (the ppermute of the
-// paper's code, overlapped with the blockwise computation): by the step-t kernels
-// themselves when a bf16 backward call covers the whole ring in ring order, otherwise by copies
+// paper's code, overlapped with the blockwise computation) by copies
 // on a library-owned side stream, with events ordering every copy after the last reader of
 // its slot and every step after its copy (see run_ring).
 #include <stdarg.h>
@@ -159,25 +159,15 @@ static int copy_block(const RingProblem& P, const void* src_all, char* dst, int 
   return RA_OK;
 }
 
-// Enqueue the whole ring: `launch(t, hosts_of_step, ..., forward, contiguous)` is called once
+// Enqueue the whole ring: `launch(t, hosts_of_step, ..., contiguous)` is called once
 // per step with, for every active host, (host, block, kv pointers, batch stride, first/last
 // flags); `contiguous` says that nothing was enqueued on the stream since the previous step.
 //
-// The block a host needs at step t+1 is the one its predecessor holds at step t.  In the bf16
-// backward, when the call covers every host of the ring in ring order, the step-t dK/dV kernels
-// write that block into the successor's receive slot themselves, from the rows they load
-// anyway -- the send half of the ring's exchange, with no separate copy and no wait between
-// the steps.  Otherwise
-// (one host's share; a custom order; float32; or RINGATTN_SERIAL_COPY set) each step's
-// blocks are copied from their home rows into the receive slots by device-to-device
-// copies, on a side stream two steps ahead (or serially on the caller stream).
-enum class Exchange {
-  kInPlace,  // none: every step reads the blocks where they lie
-  kKernels,  // the step kernels write each block into the next host's receive slot
-  kCopies    // device-to-device copies into the receive slots
-};
+// inplace: every step reads the blocks where they lie.  Otherwise each step's blocks are
+// copied from their home rows into the receive slots by device-to-device copies, on a side
+// stream two steps ahead (or, with RINGATTN_SERIAL_COPY set, serially on the caller stream).
 template <class Launch>
-static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, Exchange how,
+static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, bool inplace,
                     Launch&& launch) {
   const int N = P.N;
   const int nh = (int)P.hosts.size();
@@ -197,9 +187,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 
   const bool serial = env_flag("RINGATTN_SERIAL_COPY");
   const bool poison = env_flag("RINGATTN_POISON");
-  const bool inplace = how == Exchange::kInPlace;
-  const bool forward = N > 1 && how == Exchange::kKernels;
-  const bool copies = N > 1 && how == Exchange::kCopies;
+  const bool copies = N > 1 && !inplace;
   hipStream_t side = stream;
   if (!serial && copies) {
     int rc = side_stream(&side);
@@ -273,24 +261,8 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       host_ids.push_back(i);
       blk_ids.push_back(j);
     }
-    StepForward fw{};  // zero: no forwarding
-    if (forward && t + 1 < N) {
-      const int nxt = (t + 1) & 1;
-      fw.k0 = rb.k(nxt, 0);
-      fw.v0 = rb.v(nxt, 0);
-      fw.blk_bytes = (long long)rb.blk_bytes;
-      for (size_t n = 0; n < hs.size(); ++n) {
-        const int succ = (host_ids[n] + 1) % N;  // holds block blk_ids[n] at step t+1
-        if (P.active(succ, blk_ids[n])) fw.to[n] = (signed char)(succ + 1);
-      }
-      if (poison) {  // a receive slot the step-t kernels leave unwritten would read NaN
-        RA_HIP(hipMemsetAsync(rb.k(nxt, 0), 0xFF, rb.blk_bytes * nh, stream));
-        RA_HIP(hipMemsetAsync(rb.v(nxt, 0), 0xFF, rb.blk_bytes * nh, stream));
-      }
-    }
     // contiguous: nothing has been enqueued on the stream since the previous step's launch
-    const bool contiguous = t > 0 && (inplace || (forward && !poison));
-    int rc = launch(t, hs, host_ids, blk_ids, fw, contiguous);
+    int rc = launch(t, hs, host_ids, blk_ids, t > 0 && inplace);
     if (rc) return rc;
     if (!serial && copies && t >= 1 && t + 2 < N) {
       hipEvent_t done;
@@ -371,9 +343,8 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
   st.causal = P.causal;
   st.scale = 1.0f / sqrtf((float)P.D);
   hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  return run_ring(P, stream, R, base, inplace ? Exchange::kInPlace : Exchange::kCopies,
-                  [&](int, const std::vector<StepHost>& hs, const std::vector<int>&, const std::vector<int>&,
-                      const StepForward&, bool contiguous) -> int {
+  return run_ring(P, stream, R, base, inplace, [&](int, const std::vector<StepHost>& hs, const std::vector<int>&,
+                                                  const std::vector<int>&, bool contiguous) -> int {
     st.n_slots = (int)hs.size();
     for (size_t s = 0; s < hs.size(); ++s) st.host[s] = hs[s];
     if (!contiguous) chain = nullptr;
@@ -387,26 +358,55 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
 // ---------------------------------------------------------------------------------
 // Backward
 // ---------------------------------------------------------------------------------
+// bf16: as in the forward, the whole ring runs as one launch for dK/dV and one for dQ, each
+// workgroup's accumulators staying in registers for the whole ring (no float32 gradients in
+// memory, no receive buffers); step by step while launches are being timed or when the
+// exchange by copies is asked for, the accumulators saved between steps.
 static int run_bwd(const RingProblem& P, const void* o, const float* lse, const void* dO, void* dq,
                    void* dk, void* dv, hipStream_t stream) {
   const int nh = (int)P.hosts.size();
-  const size_t recv = P.N > 1 ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
   const size_t nrow = (size_t)P.B * P.H * P.Sq;
   const size_t telems = (size_t)P.B * P.S * P.H * P.D;
   const bool f32 = P.elt == 4;  // float32 gradients accumulate straight into the outputs
-  const size_t grads = f32 ? 0 : 3 * telems * sizeof(float);
+  const bool inplace = !f32 && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
+  const bool one = inplace && !timing_on();
+  const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
+  const size_t grads = f32 || one ? 0 : 3 * telems * sizeof(float);
   CallResources R(stream);
   int rc = R.alloc(recv + 2 * nrow * sizeof(float) + grads);
   if (rc) return rc;
   char* base = (char*)R.ws;
   float* delta = (float*)(base + recv);
   float* lse2 = delta + nrow;  // bf16 path: -lse sqrt(D), in units of q.k
+  if (f32)
+    RA_HIP(launch_bwd_pre_f32((const float*)o, (const float*)dO, delta, P.B, P.Sq, P.H, P.D, stream));
+  else
+    RA_HIP(launch_bwd_pre_bf16(o, dO, lse, delta, lse2, P.B, P.Sq, P.H, P.D, stream));
+  if (one) {
+    BwdRing a{};
+    a.q = P.q;
+    a.k = P.k;
+    a.v = P.v;
+    a.dO = dO;
+    a.lse = lse2;
+    a.delta = delta;
+    a.dq = dq;
+    a.dk = dk;
+    a.dv = dv;
+    a.bstride = (long long)P.S * P.H * P.D;
+    a.B = P.B;
+    a.H = P.H;
+    a.S = P.S;
+    a.c = P.c();
+    a.N = P.N;
+    a.causal = P.causal;
+    a.scale = 1.0f / sqrtf((float)P.D);
+    RA_HIP(launch_bwd_ring_bf16(a, P.D, stream));
+    return RA_OK;
+  }
   float* gq = f32 ? (float*)dq : lse2 + nrow;
   float* gk = f32 ? (float*)dk : gq + telems;
   float* gv = f32 ? (float*)dv : gk + telems;
-  // bf16: the call covers every host, so it holds every contribution to each gradient
-  // row: the first one is written and the last one goes out in bf16 (no zero fill, no
-  // cast).  float32: the outputs are zeroed and accumulated into.
   std::vector<int> blk_first(P.N, -1), blk_last(P.N, -1);  // steps that touch block j
   if (f32) {
     RA_HIP(launch_zero_f32(gq, (long long)telems, stream));
@@ -421,10 +421,6 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
         blk_last[j] = t;
       }
   }
-  if (f32)
-    RA_HIP(launch_bwd_pre_f32((const float*)o, (const float*)dO, delta, P.B, P.Sq, P.H, P.D, stream));
-  else
-    RA_HIP(launch_bwd_pre_bf16(o, dO, lse, delta, lse2, P.B, P.Sq, P.H, P.D, stream));
 
   BwdStep st{};
   st.q = P.q;
@@ -439,20 +435,20 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
   st.B = P.B;
   st.H = P.H;
   st.Sq = P.Sq;
+  st.Skv = P.S;
   st.c = P.c();
   st.causal = P.causal;
   st.scale = 1.0f / sqrtf((float)P.D);
   if (!f32) {
+    st.whole = 1;
     st.dq_out = dq;
     st.dk_out = dk;
     st.dv_out = dv;
   }
   hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  const bool kernels = P.elt == 2 && P.whole() && !env_flag("RINGATTN_SERIAL_COPY");
-  rc = run_ring(P, stream, R, base, kernels ? Exchange::kKernels : Exchange::kCopies, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
-                                       const std::vector<int>& blks, const StepForward& fw, bool contiguous) -> int {
+  return run_ring(P, stream, R, base, inplace, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
+                                                  const std::vector<int>& blks, bool contiguous) -> int {
     st.n_slots = (int)hs.size();
-    st.fwd = fw;
     for (size_t s = 0; s < hs.size(); ++s) {
       st.host[s] = hs[s];
       st.dkv_row0[s] = blks[s] * P.c();
@@ -466,7 +462,6 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
     }, &chain));
     return RA_OK;
   });
-  return rc;
 }
 
 // ---------------------------------------------------------------------------------
@@ -556,6 +551,7 @@ static int run_bwd_host(const void* q_blk, const void* k_all, const void* v_all,
   st.B = B;
   st.H = H;
   st.Sq = c;
+  st.Skv = c;
   st.c = c;
   st.causal = causal;
   st.scale = 1.0f / sqrtf((float)D);
@@ -584,6 +580,7 @@ static int run_bwd_host(const void* q_blk, const void* k_all, const void* v_all,
     h.q_row0 = 0;
     h.q_pos0 = host * c;
     h.k_pos0 = j * c;
+    h.kv_rows = c;
     h.flags = (t == 0 ? kFirst : 0) | (t == t_last ? kLast : 0);
     st.dkv_row0[0] = 0;
     RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] { return launch_bwd_bf16(st, D, stream); }));
@@ -633,44 +630,12 @@ using namespace ra;
 // ---------------------------------------------------------------------------------
 // Ragged causal lengths.  The sequence is cut into n_hosts blocks of c tokens, c the
 // smallest multiple of 128 with n_hosts * c >= S, so the trailing blocks are short or
-// empty; the tensors are staged into zero-padded workspace copies of length n_hosts * c.
-// Under the causal mask no real query sees a padded key (its position is >= S), and a
-// padded query row adds exactly zero to dK and dV (its o and dO are zero, so Delta = 0,
-// dP = 0 and dS = 0), so the real rows come out as for the unpadded sequence.
+// empty.  The kernels read rows past S as zero (the bounds of their buffer descriptors) and
+// store none.  Under the causal mask no real query sees a padded key (its position is >= S),
+// and a padded query row adds exactly zero to dK and dV (its dO and Delta are zero, so dP = 0
+// and dS = 0).
 // ---------------------------------------------------------------------------------
 namespace {
-
-__global__ void pad_zero_kernel(uint32_t* base, long long pitch_w, long long off_w, long long len_w,
-                                long long rows) {
-  const long long n = rows * len_w;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    base[(i / len_w) * pitch_w + off_w + i % len_w] = 0u;
-}
-
-// dst [outer][n_dst units] <- src [outer][n_src units], n_src <= n_dst, the tail of each
-// row zeroed; unit bytes a multiple of 4
-int pad_copy(void* dst, const void* src, long long outer, long long n_src, long long n_dst, long long unit,
-             hipStream_t st) {
-  RA_HIP(hipMemcpy2DAsync(dst, (size_t)(n_dst * unit), src, (size_t)(n_src * unit), (size_t)(n_src * unit),
-                          (size_t)outer, hipMemcpyDeviceToDevice, st));
-  const long long pad_w = (n_dst - n_src) * unit / 4;
-  if (pad_w > 0) {
-    const long long n = outer * pad_w;
-    const int blocks = (int)std::min<long long>((n + 255) / 256, 4096);
-    pad_zero_kernel<<<blocks, 256, 0, st>>>((uint32_t*)dst, n_dst * unit / 4, n_src * unit / 4, pad_w, outer);
-    RA_HIP(hipGetLastError());
-  }
-  return RA_OK;
-}
-
-// dst [outer][n_dst units] <- the first n_dst units of each row of src [outer][n_src units]
-int unpad_copy(void* dst, const void* src, long long outer, long long n_dst, long long n_src, long long unit,
-               hipStream_t st) {
-  RA_HIP(hipMemcpy2DAsync(dst, (size_t)(n_dst * unit), src, (size_t)(n_src * unit), (size_t)(n_dst * unit),
-                          (size_t)outer, hipMemcpyDeviceToDevice, st));
-  return RA_OK;
-}
 
 // *Sp = n_hosts * c
 int padded_len(int S, int N, long long* Sp) {
@@ -834,7 +799,7 @@ int ring_attn_fwd_varlen(const void* q, const void* k, const void* v, void* o, f
   rc = validate(B, H, (int)Sp, D, n_hosts, 1, 128);
   if (rc) return rc;
   RingProblem P = all_hosts(q, k, v, B, H, S, D, n_hosts, 1, 2);
-  P.blk_rows = (int)(Sp / n_hosts);  // the kernels read rows past S as zero and store none
+  P.blk_rows = (int)(Sp / n_hosts);
   return run_fwd(P, o, lse, stream);
 }
 
@@ -849,24 +814,9 @@ int ring_attn_bwd_varlen(const void* q, const void* k, const void* v, const void
   if (rc) return rc;
   rc = validate(B, H, (int)Sp, D, n_hosts, 1, 128);
   if (rc) return rc;
-  if (Sp == S) return run_bwd(all_hosts(q, k, v, B, H, S, D, n_hosts, 1, 2), o, lse, dO, dq, dk, dv, stream);
-  const long long row = (long long)H * D * 2, t = B * Sp * row;
-  CallResources R(stream);
-  if ((rc = R.alloc((size_t)(8 * t + (long long)B * H * Sp * 4)))) return rc;
-  char* w = (char*)R.ws;
-  char* p[8];
-  for (int i = 0; i < 8; ++i) p[i] = w + i * t;  // q k v o dO dq dk dv
-  float* lp = (float*)(w + 8 * t);
-  const void* src[5] = {q, k, v, o, dO};
-  for (int i = 0; i < 5; ++i)
-    if ((rc = pad_copy(p[i], src[i], B, S, Sp, row, stream))) return rc;
-  if ((rc = pad_copy(lp, lse, (long long)B * H, S, Sp, 4, stream))) return rc;
-  if ((rc = run_bwd(all_hosts(p[0], p[1], p[2], B, H, (int)Sp, D, n_hosts, 1, 2), p[3], lp, p[4], p[5], p[6], p[7],
-                    stream)))
-    return rc;
-  if ((rc = unpad_copy(dq, p[5], B, S, Sp, row, stream)) || (rc = unpad_copy(dk, p[6], B, S, Sp, row, stream)))
-    return rc;
-  return unpad_copy(dv, p[7], B, S, Sp, row, stream);
+  RingProblem P = all_hosts(q, k, v, B, H, S, D, n_hosts, 1, 2);
+  P.blk_rows = (int)(Sp / n_hosts);
+  return run_bwd(P, o, lse, dO, dq, dk, dv, stream);
 }
 
 }  // extern "C"

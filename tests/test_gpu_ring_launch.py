@@ -1,7 +1,7 @@
 """The whole ring in one launch against the same call made of one launch a ring step.
 
-Under ring_attn_timing_enable a whole-ring bf16 call runs step by step; both forms fold the
-same tiles in the same order, so their results are equal bit for bit.  The shapes sit where
+Under ring_attn_timing_enable a whole-ring bf16 call, forward or backward, runs step by step;
+both forms fold the same tiles in the same order, so their results are equal bit for bit.  The shapes sit where
 the one-launch form can go wrong: (batch, head) groups that do not divide over the 8 XCDs,
 one tile per workgroup, blocks of one tile row, more hosts than full blocks, ragged ends one
 row past and one row short of a tile, the eight-wave kernel.
@@ -17,6 +17,7 @@ from tests.gpu_util import dev, log, max_err, np64
 pytestmark = pytest.mark.gpu
 
 TOL_O = 2e-2  # bf16 outputs against float64, as in test_gpu_attention
+TOL_G = 5e-2
 
 # B, S, H, D, N, causal
 SHAPES = [
@@ -40,18 +41,25 @@ SHAPES = [
 @pytest.mark.parametrize("B,S,H,D,N,causal", SHAPES)
 def test_one_launch_equals_steps(B, S, H, D, N, causal):
     log("one launch B=%d S=%d H=%d D=%d N=%d causal=%d" % (B, S, H, D, N, causal))
-    q, k, v = synth.attention_inputs(S + H, B, S, H, D)
-    qd, kd, vd = dev(q, k, v)
+    q, k, v, do = synth.attention_inputs(S + H, B, S, H, D, with_grad=True)
+    qd, kd, vd, dod = dev(q, k, v, do)
     o, lse = ra.attention_fwd(qd, kd, vd, N, causal)
+    grads = ra.attention_bwd(qd, kd, vd, o, lse, dod, N, causal)
     torch.cuda.synchronize()
     ra.timing_enable(True)
     try:
         o1, lse1 = ra.attention_fwd(qd, kd, vd, N, causal)
+        grads1 = ra.attention_bwd(qd, kd, vd, o, lse, dod, N, causal)
         torch.cuda.synchronize()
     finally:
         ra.timing_enable(False)
         ra.timing_read(ra.KERNEL_ATTN_FWD)
+        ra.timing_read(ra.KERNEL_ATTN_BWD)
     assert torch.equal(o, o1) and torch.equal(lse, lse1)
+    for g, g1 in zip(grads, grads1):
+        assert torch.equal(g, g1)
     if S <= 8192:
         o_ref, lse_ref = OA.attention_fwd(np64(q), np64(k), np64(v), bool(causal))
         assert max_err(o, o_ref) <= TOL_O and max_err(lse, lse_ref) <= TOL_O
+        ref = OA.attention_bwd(np64(q), np64(k), np64(v), np64(do), bool(causal))
+        assert max(max_err(g, r) for g, r in zip(grads, ref)) <= TOL_G
