@@ -210,8 +210,9 @@ int ring_attn_decode_noalloc(const void* q, const void* k_cache, const void* v_c
 /*
  * Blockwise feed-forward network (Section 2 equation and "Blockwise Parallel
  * Transformers"; Algorithm 1's feed-forward step), bf16:
- *   y = act(x W1 + b1) W2 + b2, computed `block` rows at a time, so the [rows, d_ff]
- *   intermediate exists for one block only.
+ *   y = act(x W1 + b1) W2 + b2, computed in groups of whole `block`s, as many as 4 GiB of
+ *   [rows, d_ff] intermediates hold (one block at least): 2 bytes a hidden unit and row here,
+ *   8 in the backward; 2 and 14 in swiglu_ffn and its backward.
  *   x  in bf16 [T, d_model];  w1 in bf16 [d_model, d_ff];  b1 in bf16 [d_ff] or NULL
  *   w2 in bf16 [d_ff, d_model];  b2 in bf16 [d_model] or NULL;  y out bf16 [T, d_model]
  *   act: an ra_act value.   T % block == 0, block % 256 == 0, d_model % 256 == 0,
@@ -222,7 +223,7 @@ int blockwise_ffn(const void* x, const void* w1, const void* b1, const void* w2,
 
 /*
  * Backward of blockwise_ffn for upstream dy (bf16 [T, d_model]).  The pre-activation
- * x W1 + b1 is recomputed block by block (gradient checkpointing, Section 4 setting).
+ * x W1 + b1 is recomputed group by group (gradient checkpointing, Section 4 setting).
  *   dx  out bf16 [T, d_model]
  *   dw1 out f32 [d_model, d_ff], db1 out f32 [d_ff] (may be NULL),
  *   dw2 out f32 [d_ff, d_model], db2 out f32 [d_model] (may be NULL).
@@ -308,7 +309,7 @@ int swiglu_ffn(const void* x, const void* w1, const void* w3, const void* w2, co
                void* y, int T, int d_model, int d_ff, int block, hipStream_t stream);
 
 /* Backward of swiglu_ffn (no residual) for upstream dy bf16 [T, d_model], recomputing
- * x W1 and x W3 block by block: dx out bf16 [T, d_model]; dw1, dw3 out f32 [d_model, d_ff],
+ * x W1 and x W3 group by group: dx out bf16 [T, d_model]; dw1, dw3 out f32 [d_model, d_ff],
  * dw2 out f32 [d_ff, d_model] (overwritten). */
 int swiglu_ffn_bwd(const void* x, const void* w1, const void* w3, const void* w2, const void* dy,
                    void* dx, float* dw1, float* dw3, float* dw2, int T, int d_model, int d_ff,

@@ -1274,17 +1274,6 @@ __global__ __launch_bounds__(64) void bwd_dq_f32_kernel(const BwdStep p) {
   for (int d = 0; d < D; ++d) dqrow[d] += dq[d] * p.scale;
 }
 
-__global__ void cast_f32_bf16_kernel(const float* src, bf16* dst, long long n) {
-  const long long i = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i + 3 < n) {
-    const f32x4 v = *(const f32x4*)(src + i);
-    u32x2 w = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-    *(u32x2*)(dst + i) = w;
-  } else {
-    for (long long j = i; j < n; ++j) dst[j] = (bf16)src[j];
-  }
-}
-
 __global__ void zero_f32_kernel(float* p, long long n) {
   const long long i = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (i + 3 < n) {
@@ -1355,12 +1344,6 @@ hipError_t launch_bwd_f32(const BwdStep& s, int D, hipStream_t st) {
     hipLaunchKernelGGL(bwd_dkdv_f32_kernel<64>, dim3(g), dim3(64), 0, st, s);
     hipLaunchKernelGGL(bwd_dq_f32_kernel<64>, dim3(g), dim3(64), 0, st, s);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_cast_f32_bf16(const float* src, void* dst, long long n, hipStream_t st) {
-  const long long blocks = (n / 4 + 255) / 256 + 1;
-  hipLaunchKernelGGL(cast_f32_bf16_kernel, dim3(blocks), dim3(256), 0, st, src, (bf16*)dst, n);
   return hipGetLastError();
 }
 

@@ -2,9 +2,9 @@
 //
 // The feed-forward network of Section 2 is applied to `block` rows at a time
 // (Blockwise Parallel Transformers, Section 2; the feed-forward step of Algorithm 1),
-// so the [rows, d_ff] intermediate exists for one block only.  Every product runs in
-// the bf16 matrix-core GEMM; bias, activation, residual and activation-derivative are
-// fused into its epilogue.  The backward pass recomputes each block's pre-activation
+// so the [rows, d_ff] intermediate exists for a bounded number of blocks only.  Every product
+// runs in the bf16 matrix-core GEMM; bias, activation, residual and activation-derivative are
+// fused into its epilogue.  The backward pass recomputes each group's pre-activation
 // (gradient checkpointing) and accumulates weight gradients in float32.
 #include "ra_gemm.h"
 #include "ra_ops.h"
@@ -30,104 +30,99 @@ int gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st) {
   return RA_OK;
 }
 
-// y (bf16) = x w (+ residual), row blocks of `block`
-int proj(const void* x, const void* w, const void* residual, void* y, int T, int din, int dout, int block,
-                hipStream_t st) {
-  for (int r0 = 0; r0 < T; r0 += block) {
-    GemmArgs g{};
-    g.A = (const char*)x + (size_t)r0 * din * 2;
-    g.B = w;
-    g.C = (char*)y + (size_t)r0 * dout * 2;
-    g.residual = residual ? (const char*)residual + (size_t)r0 * dout * 2 : nullptr;
-    g.lda = din;
-    g.ldb = dout;
-    g.ldc = dout;
-    g.M = block;
-    g.N = dout;
-    g.K = din;
-    int rc = gemm(g, false, false, EPI_BF16, st);
-    if (rc) return rc;
-  }
-  return RA_OK;
+GemmArgs gemm_args(const void* A, long long lda, const void* B, long long ldb, void* C, long long ldc, int M, int N,
+                   int K) {
+  GemmArgs g{};
+  g.A[0] = A;
+  g.B[0] = B;
+  g.C[0] = C;
+  g.lda = lda;
+  g.ldb = ldb;
+  g.ldc = ldc;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  return g;
 }
 
-// dW (f32, overwritten) = x^T dy, accumulated over row blocks
-int wgrad(const void* x, const void* dy, float* dw, int T, int din, int dout, int block, hipStream_t st) {
-  for (int bi = 0, r0 = 0; r0 < T; ++bi, r0 += block) {
-    GemmArgs g{};
-    g.A = (const char*)x + (size_t)r0 * din * 2;
-    g.B = (const char*)dy + (size_t)r0 * dout * 2;
-    g.C = dw;
-    g.lda = din;
-    g.ldb = dout;
-    g.ldc = dout;
-    g.M = din;
-    g.N = dout;
-    g.K = block;
-    g.accumulate = bi > 0;
-    int rc = gemm(g, true, false, EPI_F32, st);
-    if (rc) return rc;
-  }
-  return RA_OK;
+int proj(const void* x, const void* w, const void* residual, void* y, int T, int din, int dout, hipStream_t st) {
+  GemmArgs g = gemm_args(x, din, w, dout, y, dout, T, dout, din);
+  g.residual = residual;
+  return gemm(g, false, false, EPI_BF16, st);
 }
 
-// dx32 (f32) (+)= dy w^T, row blocks
-int dgrad32(const void* dy, const void* w, float* dx32, int accumulate, int T, int din, int dout, int block,
-                   hipStream_t st) {
-  for (int r0 = 0; r0 < T; r0 += block) {
-    GemmArgs g{};
-    g.A = (const char*)dy + (size_t)r0 * dout * 2;
-    g.B = w;
-    g.C = dx32 + (size_t)r0 * din;
-    g.lda = dout;
-    g.ldb = dout;
-    g.ldc = din;
-    g.M = block;
-    g.N = din;
-    g.K = dout;
-    g.accumulate = accumulate;
-    int rc = gemm(g, false, true, EPI_F32, st);
-    if (rc) return rc;
+int proj3(const void* x, const void* const* w, void* const* y, int T, int din, int dout, hipStream_t st) {
+  GemmArgs g = gemm_args(x, din, w[0], dout, y[0], dout, T, dout, din);
+  g.nb = 3;
+  for (int i = 0; i < 3; ++i) {
+    g.A[i] = x;
+    g.B[i] = w[i];
+    g.C[i] = y[i];
   }
-  return RA_OK;
+  return gemm(g, false, false, EPI_BF16, st);
+}
+
+int dgrad(const void* dy, const void* w, void* dx, int T, int din, int dout, hipStream_t st) {
+  return gemm(gemm_args(dy, dout, w, dout, dx, din, T, din, dout), false, true, EPI_BF16, st);
+}
+
+int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, hipStream_t st) {
+  GemmArgs g = gemm_args(x, din, dy[0], dout, dw[0], dout, din, dout, T);
+  g.nb = n;
+  for (int i = 0; i < n; ++i) {
+    g.A[i] = x;
+    g.B[i] = dy[i];
+    g.C[i] = dw[i];
+  }
+  return gemm(g, true, false, EPI_F32, st);
+}
+
+int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void* residual, void* dx, int T, int din,
+           int dout, hipStream_t st) {
+  GemmArgs g = gemm_args(dy[0], dout, w[0], dout, dx32 ? (void*)dx32 : dx, din, T, din, dout);
+  g.ns = 3;
+  for (int i = 0; i < 3; ++i) {
+    g.A[i] = dy[i];
+    g.B[i] = w[i];
+  }
+  g.residual = residual;
+  return gemm(g, false, true, dx32 ? EPI_F32 : EPI_BF16, st);
+}
+
+int alloc_row_groups(CallResources& R, int T, int block, size_t row_bytes, size_t fixed, int* rows) {
+  const int blocks = T / block;
+  int per = (int)(kGroupBytes / ((size_t)block * row_bytes));
+  per = per < 1 ? 1 : per > blocks ? blocks : per;
+  const int groups = (blocks + per - 1) / per;
+  per = (blocks + groups - 1) / groups;  // groups of equal size
+  int rc = R.alloc((size_t)per * block * row_bytes + fixed);
+  if (rc == RA_ENOMEM && per > 1) {
+    (void)hipGetLastError();
+    g_err.clear();
+    per = 1;
+    rc = R.alloc((size_t)block * row_bytes + fixed);
+  }
+  *rows = per * block;
+  return rc;
 }
 
 int ffn_forward(const void* x, const void* w1, const void* b1, const void* w2, const void* b2, const void* residual,
                 void* y, int T, int d_model, int d_ff, int block, int act, hipStream_t stream) {
-  int rc;
   CallResources R(stream);
-  rc = R.alloc((size_t)block * d_ff * 2);
-  if (rc) return rc;
-  void* a = R.ws;  // activation of one block, bf16 [block, d_ff]
-  for (int r0 = 0; r0 < T; r0 += block) {
-    GemmArgs up{};
-    up.A = (const char*)x + (size_t)r0 * d_model * 2;
-    up.B = w1;
-    up.C = a;
+  int rows, rc;
+  if ((rc = alloc_row_groups(R, T, block, (size_t)d_ff * 2, 0, &rows))) return rc;
+  void* a = R.ws;  // activation of one group of blocks, bf16 [rows, d_ff]
+  for (int r0 = 0; r0 < T; r0 += rows) {
+    const int m = T - r0 < rows ? T - r0 : rows;
+    const size_t off = (size_t)r0 * d_model * 2;
+    GemmArgs up = gemm_args((const char*)x + off, d_model, w1, d_ff, a, d_ff, m, d_ff, d_model);
     up.bias = b1;
-    up.lda = d_model;
-    up.ldb = d_ff;
-    up.ldc = d_ff;
-    up.M = block;
-    up.N = d_ff;
-    up.K = d_model;
     up.act = act;
-    rc = gemm(up, false, false, EPI_ACT_BF16, stream);
-    if (rc) return rc;
-    GemmArgs dn{};
-    dn.A = a;
-    dn.B = w2;
-    dn.C = (char*)y + (size_t)r0 * d_model * 2;
+    if ((rc = gemm(up, false, false, EPI_ACT_BF16, stream))) return rc;
+    GemmArgs dn = gemm_args(a, d_ff, w2, d_model, (char*)y + off, d_model, m, d_model, d_ff);
     dn.bias = b2;
-    dn.residual = residual ? (const char*)residual + (size_t)r0 * d_model * 2 : nullptr;
-    dn.lda = d_ff;
-    dn.ldb = d_model;
-    dn.ldc = d_model;
-    dn.M = block;
-    dn.N = d_model;
-    dn.K = d_ff;
-    rc = gemm(dn, false, false, EPI_BF16, stream);
-    if (rc) return rc;
+    dn.residual = residual ? (const char*)residual + off : nullptr;
+    if ((rc = gemm(dn, false, false, EPI_BF16, stream))) return rc;
   }
   return RA_OK;
 }
@@ -135,83 +130,44 @@ int ffn_forward(const void* x, const void* w1, const void* b1, const void* w2, c
 int ffn_backward(const void* x, const void* w1, const void* b1, const void* w2, const void* dy, const void* dx_residual,
                  void* dx, float* dw1, float* db1, float* dw2, float* db2, int T, int d_model, int d_ff, int block,
                  int act, hipStream_t stream) {
-  int rc;
-  const size_t nb = (size_t)block * d_ff;
   const size_t part = colsum_workspace_floats(d_ff > d_model ? d_ff : d_model);
   CallResources R(stream);
-  rc = R.alloc(nb * 4 + nb * 2 + nb * 2 + part * 4);
-  if (rc) return rc;
-  float* h = (float*)R.ws;                       // pre-activation, float32 [block, d_ff]
+  int rows, rc;
+  if ((rc = alloc_row_groups(R, T, block, (size_t)d_ff * 8, part * 4, &rows))) return rc;
+  const size_t nb = (size_t)rows * d_ff;
+  float* h = (float*)R.ws;                       // pre-activation, float32 [rows, d_ff]
   void* a = (char*)R.ws + nb * 4;                // activation, bf16
   void* dh = (char*)R.ws + nb * 6;               // gradient of the pre-activation, bf16
   float* parts = (float*)((char*)R.ws + nb * 8);  // column-sum partials
-  for (int bi = 0, r0 = 0; r0 < T; ++bi, r0 += block) {
-    const char* xb = (const char*)x + (size_t)r0 * d_model * 2;
-    const char* dyb = (const char*)dy + (size_t)r0 * d_model * 2;
-    GemmArgs up{};  // recompute H = x W1 + b1 and A = act(H)
-    up.A = xb;
-    up.B = w1;
-    up.C = a;
+  for (int r0 = 0; r0 < T; r0 += rows) {
+    const int m = T - r0 < rows ? T - r0 : rows;
+    const size_t off = (size_t)r0 * d_model * 2;
+    const char* xb = (const char*)x + off;
+    const char* dyb = (const char*)dy + off;
+    // recompute H = x W1 + b1 and A = act(H)
+    GemmArgs up = gemm_args(xb, d_model, w1, d_ff, a, d_ff, m, d_ff, d_model);
     up.bias = b1;
     up.aux_f32 = h;
-    up.lda = d_model;
-    up.ldb = d_ff;
-    up.ldc = d_ff;
-    up.M = block;
-    up.N = d_ff;
-    up.K = d_model;
     up.act = act;
     if ((rc = gemm(up, false, false, EPI_ACT_STORE_H, stream))) return rc;
-    GemmArgs gA{};  // dH = (dy W2^T) * act'(H)
-    gA.A = dyb;
-    gA.B = w2;
-    gA.C = dh;
+    // dH = (dy W2^T) * act'(H)
+    GemmArgs gA = gemm_args(dyb, d_model, w2, d_model, dh, d_ff, m, d_ff, d_model);
     gA.aux_f32 = h;
-    gA.lda = d_model;
-    gA.ldb = d_model;
-    gA.ldc = d_ff;
-    gA.M = block;
-    gA.N = d_ff;
-    gA.K = d_model;
     gA.act = act;
     if ((rc = gemm(gA, false, true, EPI_ACT_GRAD_BF16, stream))) return rc;
-    GemmArgs gw2{};  // dW2 (+)= A^T dy
-    gw2.A = a;
-    gw2.B = dyb;
-    gw2.C = dw2;
-    gw2.lda = d_ff;
-    gw2.ldb = d_model;
-    gw2.ldc = d_model;
-    gw2.M = d_ff;
-    gw2.N = d_model;
-    gw2.K = block;
-    gw2.accumulate = bi > 0;
+    // dW2 (+)= A^T dy
+    GemmArgs gw2 = gemm_args(a, d_ff, dyb, d_model, dw2, d_model, d_ff, d_model, m);
+    gw2.accumulate = r0 > 0;
     if ((rc = gemm(gw2, true, false, EPI_F32, stream))) return rc;
-    if (db2) RA_HIP(launch_colsum_bf16(dyb, parts, db2, block, d_model, bi > 0, stream));
-    GemmArgs gw1{};  // dW1 (+)= x^T dH
-    gw1.A = xb;
-    gw1.B = dh;
-    gw1.C = dw1;
-    gw1.lda = d_model;
-    gw1.ldb = d_ff;
-    gw1.ldc = d_ff;
-    gw1.M = d_model;
-    gw1.N = d_ff;
-    gw1.K = block;
-    gw1.accumulate = bi > 0;
+    if (db2) RA_HIP(launch_colsum_bf16(dyb, parts, db2, m, d_model, r0 > 0, stream));
+    // dW1 (+)= x^T dH
+    GemmArgs gw1 = gemm_args(xb, d_model, dh, d_ff, dw1, d_ff, d_model, d_ff, m);
+    gw1.accumulate = r0 > 0;
     if ((rc = gemm(gw1, true, false, EPI_F32, stream))) return rc;
-    if (db1) RA_HIP(launch_colsum_bf16(dh, parts, db1, block, d_ff, bi > 0, stream));
-    GemmArgs gx{};  // dx = dH W1^T
-    gx.A = dh;
-    gx.B = w1;
-    gx.C = (char*)dx + (size_t)r0 * d_model * 2;
-    gx.residual = dx_residual ? (const char*)dx_residual + (size_t)r0 * d_model * 2 : nullptr;
-    gx.lda = d_ff;
-    gx.ldb = d_ff;
-    gx.ldc = d_model;
-    gx.M = block;
-    gx.N = d_model;
-    gx.K = d_ff;
+    if (db1) RA_HIP(launch_colsum_bf16(dh, parts, db1, m, d_ff, r0 > 0, stream));
+    // dx = dH W1^T
+    GemmArgs gx = gemm_args(dh, d_ff, w1, d_ff, (char*)dx + off, d_model, m, d_model, d_ff);
+    gx.residual = dx_residual ? (const char*)dx_residual + off : nullptr;
     if ((rc = gemm(gx, false, true, EPI_BF16, stream))) return rc;
   }
   return RA_OK;
@@ -253,21 +209,7 @@ int blockwise_linear(const void* x, const void* w, const void* residual, void* y
   if (int e = check_aligned({x, w, residual, y})) return e;
   int rc = check_gemm_dims(T, d_in, d_out, block);
   if (rc) return rc;
-  for (int r0 = 0; r0 < T; r0 += block) {
-    GemmArgs g{};
-    g.A = (const char*)x + (size_t)r0 * d_in * 2;
-    g.B = w;
-    g.C = (char*)y + (size_t)r0 * d_out * 2;
-    g.residual = residual ? (const char*)residual + (size_t)r0 * d_out * 2 : nullptr;
-    g.lda = d_in;
-    g.ldb = d_out;
-    g.ldc = d_out;
-    g.M = block;
-    g.N = d_out;
-    g.K = d_in;
-    if ((rc = gemm(g, false, false, EPI_BF16, stream))) return rc;
-  }
-  return RA_OK;
+  return proj(x, w, residual, y, T, d_in, d_out, stream);
 }
 
 int blockwise_linear_bwd(const void* x, const void* w, const void* dy, void* dx, float* dw, int T, int d_in,
@@ -277,35 +219,8 @@ int blockwise_linear_bwd(const void* x, const void* w, const void* dy, void* dx,
   if (int e = check_aligned({x, w, dy, dx, dw})) return e;
   int rc = check_gemm_dims(T, d_in, d_out, block);
   if (rc) return rc;
-  for (int bi = 0, r0 = 0; r0 < T; ++bi, r0 += block) {
-    const char* dyb = (const char*)dy + (size_t)r0 * d_out * 2;
-    if (dx) {
-      GemmArgs g{};  // dx = dy W^T
-      g.A = dyb;
-      g.B = w;
-      g.C = (char*)dx + (size_t)r0 * d_in * 2;
-      g.lda = d_out;
-      g.ldb = d_out;
-      g.ldc = d_in;
-      g.M = block;
-      g.N = d_in;
-      g.K = d_out;
-      if ((rc = gemm(g, false, true, EPI_BF16, stream))) return rc;
-    }
-    GemmArgs gw{};  // dW (+)= x^T dy
-    gw.A = (const char*)x + (size_t)r0 * d_in * 2;
-    gw.B = dyb;
-    gw.C = dw;
-    gw.lda = d_in;
-    gw.ldb = d_out;
-    gw.ldc = d_out;
-    gw.M = d_in;
-    gw.N = d_out;
-    gw.K = block;
-    gw.accumulate = bi > 0;
-    if ((rc = gemm(gw, true, false, EPI_F32, stream))) return rc;
-  }
-  return RA_OK;
+  if (dx && (rc = dgrad(dy, w, dx, T, d_in, d_out, stream))) return rc;
+  return wgrad(x, &dy, &dw, 1, T, d_in, d_out, stream);
 }
 
 }  // extern "C"

@@ -6,12 +6,17 @@
 // accumulators of 32 x 32): while one wave waits for operands or the barrier, the other
 // keeps the matrix core busy.  K advances 32 at a time through a ring of five LDS stages
 // (all 160 KB of the CU's LDS) filled by direct-to-LDS buffer loads four steps ahead of
-// their use.  Tiles are kept in their
+// their use.  Products with too few such tiles for the chip's 256 CUs take 128 x 128 tiles,
+// 4 waves of 64 x 64, two workgroups a CU (see tile_size).  Tiles are kept in their
 // memory layout, unpadded, with 16-byte chunks XOR-swizzled per row so that both the row
 // reads and the transpose reads (an operand whose registers must run along its contiguous
 // dimension) are free of bank conflicts.  Each wave computes C^T = B^T A^T so that a lane
 // owns one row m of C and four consecutive columns n per register group: epilogues then
 // read bias / residual / pre-activation and write C with vector accesses.
+//
+// One launch covers up to three products of one shape (the query, key and value projections
+// of a layer) or one product whose reduction runs over up to three operand pairs (the sum of
+// their input gradients, which so stays in the accumulators).
 #include "ra_common.h"
 #include "ra_dma.h"
 #include "ra_gemm.h"
@@ -20,17 +25,16 @@
 namespace ra {
 namespace {
 
-constexpr int kTM = 256, kTN = 256, kTK = 32, kGT = 512;
-constexpr int kNS = 5;                      // ring stages
-constexpr int kTileB = 256 * kTK * 2;       // bytes of one operand tile (16 KB)
-constexpr int kLoadsPerTile = kTileB / 1024 / (kGT / 64);  // 1 KB loads per wave per tile
+constexpr int kTK = 32;
+constexpr int kNS = 5;             // ring stages
+constexpr int kLoadsPerTile = 2;   // 1 KB loads per wave per operand tile (T = 256: 16 by 8 waves, 128: 8 by 4)
 
 // Tile layouts in LDS (no padding; chunk = 16 bytes = 8 elements):
-//   row tile   [256][32] (A with TA = 0, B with TB = 1): 64-byte rows of 4 chunks, logical
+//   row tile   [T][32] (A with TA = 0, B with TB = 1): 64-byte rows of 4 chunks, logical
 //              chunk c of row r stored at c ^ ((r >> 2) & 3);
-//   k-major    [32][256] (A with TA = 1, B with TB = 0): 512-byte rows of 32 chunks,
+//   k-major    [32][T] (A with TA = 1, B with TB = 0): rows of T / 8 chunks,
 //              logical chunk c of row r stored at c ^ (4 (r & 3)).
-// A one-wave direct-to-LDS load fills 1 KB: 16 rows of a row tile, or 2 rows of a k-major
+// A one-wave direct-to-LDS load fills 1 KB: 16 rows of a row tile, or 512 / T rows of a k-major
 // tile, lane i landing at byte 16 i; the swizzle is applied to the global address.
 __device__ __forceinline__ int swz_row(int r) { return (r >> 2) & 3; }
 __device__ __forceinline__ int swz_kmaj(int r) { return 4 * (r & 3); }
@@ -95,8 +99,20 @@ __device__ __forceinline__ float act_grad(float h) {
 
 // ACT: the activation of the ACT epilogues (an ra_act value, fixed at compile time so
 // that each kernel holds the code of one activation only).
-template <bool TA, bool TB, int EPI, int ACT>
-__global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
+// EPI_GLU_BF16 (T = 256, TB = 0) forms two products over the same A at once: the B tile is 128
+// columns of B[0] beside the same 128 columns of B[1], two k-major [32][128] tiles, so that the
+// epilogue finds u = A B[0] and w = A B[1] of an element in one row of the transposed tile.
+template <int T, bool TA, bool TB, int EPI, int ACT>
+__global__ __launch_bounds__(T == 256 ? 512 : 256, T == 256 ? 1 : 2) void gemm_kernel(const GemmArgs g) {
+  constexpr bool DUAL = EPI == EPI_GLU_BF16;
+  static_assert(!DUAL || (T == 256 && !TB), "two-product tiles are 256 x (128 + 128), k-major");
+  constexpr int NWAVE = T == 256 ? 8 : 4;
+  constexpr int WN = T == 256 ? 4 : 2;         // waves across N (two across M)
+  constexpr int NI = 2;                        // 32-column groups of a wave (64 columns)
+  constexpr int MI = T / 64;                   // 32-row groups of a wave (T / 2 rows)
+  constexpr int TNC = DUAL ? T / 2 : T;        // columns of C per workgroup
+  constexpr int BW = DUAL ? T / 2 : T;         // columns of a k-major B tile
+  constexpr int kTileB = T * kTK * 2;          // bytes of one operand tile
   // one LDS object per stage (A tile, then B tile), so that reads of one stage are known not
   // to alias the direct-to-LDS loads in flight into the others
   __shared__ __attribute__((aligned(1024))) char sS0[2 * kTileB];
@@ -110,64 +126,84 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
     else if constexpr (S == 3) return sS3; else return sS4;
   };
 
-  // tile order: XCD-contiguous ranges, then groups of 8 tile-rows sweeping across N
-  const int tiles_m = g.M / kTM, tiles_n = g.N / kTN;
+  // tile order: XCD-contiguous ranges over the products of the launch, then groups of 8
+  // tile-rows sweeping across N
+  const int tiles_m = g.M / T, tiles_n = g.N / TNC;
   const int total = tiles_m * tiles_n;
-  const int L = xcd_swizzle(blockIdx.x, total);
-  const int GM = 8;
+  const int Lz = xcd_swizzle(blockIdx.x, total * g.nb);
+  const int z = Lz / total, L = Lz - z * total;
+  const int GM = 2048 / T;
   const int group = L / (GM * tiles_n);
   const int first_m = group * GM;
   const int gsize = min(GM, tiles_m - first_m);
   const int tm = first_m + (L % (GM * tiles_n)) % gsize;
   const int tn = (L % (GM * tiles_n)) / gsize;
-  const int m0 = tm * kTM, n0 = tn * kTN;
+  const int m0 = tm * T, n0 = tn * TNC;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
-  const int wm = wave >> 2, wn = wave & 3;  // 128 rows x 64 columns per wave
-  const bf16* A = (const bf16*)g.A;
-  const bf16* B = (const bf16*)g.B;
-  const int nk = g.K / kTK;
+  const int wm = wave / WN, wn = wave % WN;  // T / 2 rows x 64 columns per wave
+  void* const Cz = g.C[z];
+  const int nk1 = g.K / kTK, nk = nk1 * g.ns;  // steps of one operand pair, of all
 
-  f32x16 acc[2][4];  // [n tile][m tile] of C^T
+  f32x16 acc[NI][MI];  // [n tile][m tile] of C^T
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < NI; ++a)
 #pragma unroll
-    for (int b = 0; b < 4; ++b)
+    for (int b = 0; b < MI; ++b)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
 
   // ---- direct-to-LDS loads: per-lane byte offsets from the tile origin (fixed), and
   // the tile origin, which moves by kTK along K (scalar) ------------------------------
-  // load j of this wave fills LDS bytes [(wave * kLoadsPerTile + j) * 1024, +1024)
-  auto lane_off = [&](bool kmajor, long long ld, int j) __attribute__((always_inline)) -> int {
-    const int blk = wave * kLoadsPerTile + j;
+  // load j of this wave fills LDS bytes [blk * 1024, +1024) of the operand tile, blk = wave *
+  // kLoadsPerTile + j (two-product B tiles: blk = j * 8 + wave, so that load j is of B[j])
+  auto lane_off = [&](bool kmajor, int width, long long ld, int blk) __attribute__((always_inline)) -> int {
     if (!kmajor) {  // 16 rows x 4 chunks
       const int r = blk * 16 + (lane >> 2), pc = lane & 3;
       return (int)(2 * (r * ld + 8 * (pc ^ swz_row(r))));
     }
-    const int r = blk * 2 + (lane >> 5), pc = lane & 31;  // 2 rows x 32 chunks
+    const int cpr = width / 8;
+    const int r = blk * (64 / cpr) + lane / cpr, pc = lane % cpr;
     return (int)(2 * (r * ld + 8 * (pc ^ swz_kmaj(r))));
   };
   int aoff[kLoadsPerTile], boff[kLoadsPerTile];
 #pragma unroll
   for (int j = 0; j < kLoadsPerTile; ++j) {
-    aoff[j] = lane_off(TA, g.lda, j);
-    boff[j] = lane_off(!TB, g.ldb, j);
+    aoff[j] = lane_off(TA, T, g.lda, wave * kLoadsPerTile + j);
+    boff[j] = lane_off(!TB, BW, g.ldb, DUAL ? wave : wave * kLoadsPerTile + j);
   }
   // extent of a tile's reads (bytes from its origin), for the buffer descriptors
-  const int a_ext = (int)(2 * (TA ? (long long)(kTK - 1) * g.lda + kTM : (long long)(kTM - 1) * g.lda + kTK));
-  const int b_ext = (int)(2 * (TB ? (long long)(kTN - 1) * g.ldb + kTK : (long long)(kTK - 1) * g.ldb + kTN));
+  const int a_ext = (int)(2 * (TA ? (long long)(kTK - 1) * g.lda + T : (long long)(T - 1) * g.lda + kTK));
+  const int b_ext = (int)(2 * (TB ? (long long)(T - 1) * g.ldb + kTK : (long long)(kTK - 1) * g.ldb + BW));
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const bf16* const A0 = (const bf16*)g.A[z];
+  const bf16* const B0 = (const bf16*)g.B[z];
   auto load_stage = [&](int kt, auto Sc) __attribute__((always_inline)) {
-    const int k0 = kt * kTK;
+    const bf16 *A = A0, *B = B0;
+    int k0 = kt * kTK;
+    if (g.ns > 1 && kt >= nk1) {  // the second or third operand pair
+      const int sgm = kt >= 2 * nk1 ? 2 : 1;
+      A = (const bf16*)g.A[sgm];
+      B = (const bf16*)g.B[sgm];
+      k0 -= sgm * g.K;
+    }
     const bf16* at = TA ? A + (long long)k0 * g.lda + m0 : A + (long long)m0 * g.lda + k0;
-    const bf16* bt = TB ? B + (long long)n0 * g.ldb + k0 : B + (long long)k0 * g.ldb + n0;
-    const __amdgpu_buffer_rsrc_t ra_ = make_rsrc(at, a_ext), rb_ = make_rsrc(bt, b_ext);
-    const unsigned st = lds_addr(stage(Sc)) + wave_u * kLoadsPerTile * 1024;
+    const long long boffs = TB ? (long long)n0 * g.ldb + k0 : (long long)k0 * g.ldb + n0;
+    const __amdgpu_buffer_rsrc_t ra_ = make_rsrc(at, a_ext), rb_ = make_rsrc(B + boffs, b_ext);
+    const unsigned st = lds_addr(stage(Sc));
+    const unsigned sw = st + wave_u * kLoadsPerTile * 1024;
+    if constexpr (DUAL) {
+      const __amdgpu_buffer_rsrc_t rb2 = make_rsrc((const bf16*)g.B[1] + boffs, b_ext);
+      dma_lds16(ra_, sw, aoff[0]);
+      dma_lds16(rb_, st + kTileB + wave_u * 1024, boff[0]);
+      dma_lds16(ra_, sw + 1024, aoff[1]);
+      dma_lds16(rb2, st + kTileB + kTileB / 2 + wave_u * 1024, boff[1]);
+    } else {
 #pragma unroll
-    for (int j = 0; j < kLoadsPerTile; ++j) {
-      dma_lds16(ra_, st + j * 1024, aoff[j]);  // tile loads the loop waits for itself
-      dma_lds16(rb_, st + kTileB + j * 1024, boff[j]);
+      for (int j = 0; j < kLoadsPerTile; ++j) {
+        dma_lds16(ra_, sw + j * 1024, aoff[j]);  // tile loads the loop waits for itself
+        dma_lds16(rb_, sw + kTileB + j * 1024, boff[j]);
+      }
     }
   };
 
@@ -177,51 +213,50 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
 #pragma unroll
   for (int kk = 0; kk < 2; ++kk) roff[kk] = l32 * 64 + 16 * ((2 * kk + hi) ^ swz_row(l32));
   // k-major operand by transpose reads: rows 16 kk + 8 hi + li / 4 (and + 4), columns
-  // base + 32 t + 16 (gq & 1) + 4 (li & 3) for t = 0..3 (A: base 128 wm, a multiple of 128,
-  // which the swizzle leaves in place) or t = 0..1 (B: columns 64 wn + ..., swizzled whole)
+  // base + 32 t + 16 (gq & 1) + 4 (li & 3) for t < MI (A: base T / 2 wm) or t < NI (B: base 64 wn)
   const int gq = lane >> 4, li = lane & 15;
   const int trow = 8 * hi + (li >> 2);
-  int toff[4], tboff[2];
+  auto tr_off = [&](int width, int col) __attribute__((always_inline)) -> int {
+    return trow * width * 2 + 16 * ((col >> 3) ^ swz_kmaj(trow)) + 2 * (col & 7);
+  };
+  int toff[MI], tboff[NI];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int col = 32 * t + 16 * (gq & 1) + 4 * (li & 3);
-    toff[t] = trow * 512 + 16 * ((col >> 3) ^ swz_kmaj(trow)) + 2 * (col & 7);
-  }
+  for (int t = 0; t < MI; ++t) toff[t] = tr_off(T, wm * (T / 2) + 32 * t + 16 * (gq & 1) + 4 * (li & 3));
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
+  for (int t = 0; t < NI; ++t) {
     const int col = 64 * wn + 32 * t + 16 * (gq & 1) + 4 * (li & 3);
-    tboff[t] = trow * 512 + 16 * ((col >> 3) ^ swz_kmaj(trow)) + 2 * (col & 7);
+    tboff[t] = DUAL ? (wn >> 1) * (kTileB / 2) + tr_off(BW, col & (BW - 1)) : tr_off(BW, col);
   }
   // operand fetch for k-slice kk of a stage: A operand rows m (bop: B^T rows n)
   auto fetch = [&](const char* st, int kk, bf16x8* aop, bf16x8* bop) __attribute__((always_inline)) {
     const char* as = st;
     const char* bs = st + kTileB;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MI; ++i) {
       if (!TA) {
-        aop[i] = *(const bf16x8*)(as + (wm * 128 + 32 * i) * 64 + roff[kk]);
+        aop[i] = *(const bf16x8*)(as + (wm * (T / 2) + 32 * i) * 64 + roff[kk]);
       } else {
-        const char* p = as + kk * 16 * 512 + wm * 256 + toff[i];
-        const bf16x4 lo = lds_read_tr16((const bf16*)p), up = lds_read_tr16((const bf16*)(p + 4 * 512));
+        const char* p = as + kk * 16 * T * 2 + toff[i];
+        const bf16x4 lo = lds_read_tr16((const bf16*)p), up = lds_read_tr16((const bf16*)(p + 4 * T * 2));
         aop[i] = bf16x8{lo[0], lo[1], lo[2], lo[3], up[0], up[1], up[2], up[3]};
       }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < NI; ++i) {
       if (TB) {
         bop[i] = *(const bf16x8*)(bs + (wn * 64 + 32 * i) * 64 + roff[kk]);
       } else {
-        const char* p = bs + kk * 16 * 512 + tboff[i];
-        const bf16x4 lo = lds_read_tr16((const bf16*)p), up = lds_read_tr16((const bf16*)(p + 4 * 512));
+        const char* p = bs + kk * 16 * BW * 2 + tboff[i];
+        const bf16x4 lo = lds_read_tr16((const bf16*)p), up = lds_read_tr16((const bf16*)(p + 4 * BW * 2));
         bop[i] = bf16x8{lo[0], lo[1], lo[2], lo[3], up[0], up[1], up[2], up[3]};
       }
     }
   };
-  auto mfmas = [&](const bf16x8* aop, const bf16x8* bop, int n0i, int n1i) __attribute__((always_inline)) {
+  auto mfmas = [&](const bf16x8* aop, const bf16x8* bop) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ni = n0i; ni < n1i; ++ni)
+    for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) acc[ni][mi] = mfma32(bop[ni], aop[mi], acc[ni][mi]);
+      for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = mfma32(bop[ni], aop[mi], acc[ni][mi]);
   };
 
   // ---- main loop ----------------------------------------------------------------------
@@ -230,7 +265,7 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
   // (those of kt+2 .. kt+4 may stay in flight -- loads complete in issue order), the
   // barrier (every read of this stage has been issued by now), and step kt+1's slice-0
   // reads, covered by slice 1's products.
-  bf16x8 a0[4], b0[2], a1[4], b1[2];
+  bf16x8 a0[MI], b0[NI], a1[MI], b1[NI];
 #pragma unroll
   for (int s = 0; s < kNS - 1; ++s)
     if (s < nk) {
@@ -246,7 +281,7 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
     constexpr int S = decltype(Sc)::value;
     if (kt + kNS - 1 < nk) load_stage(kt + kNS - 1, std::integral_constant<int, (S + kNS - 1) % kNS>{});
     fetch(stage(Sc), 1, a1, b1);
-    mfmas(a0, b0, 0, 2);
+    mfmas(a0, b0);
     // step kt+1 must have landed: at most the loads of steps kt+2 .. kt+4 outstanding
     constexpr int LPS = 2 * kLoadsPerTile;  // loads per step per wave
     if (kt + 4 < nk)
@@ -259,7 +294,7 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     lds_barrier();
     if (kt + 1 < nk) fetch(stage(std::integral_constant<int, S + 1>{}), 0, a0, b0);
-    mfmas(a1, b1, 0, 2);
+    mfmas(a1, b1);
   };
   int kt = 0;
   for (; kt + kNS - 1 < nk; kt += kNS) {
@@ -275,13 +310,13 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
   if (kt < nk) step(std::integral_constant<int, 3>{}, kt++);
 
   // ---- epilogue --------------------------------------------------------------------
-  // The float32 accumulators pass through LDS (the stage buffers are free now) in two
-  // passes of 128 rows: the two waves owning those rows write them, 32 rows per stage
-  // buffer (1 KB rows; 16-byte chunk c of row r stored at c ^ (r & 15), so both the
-  // writes -- 32 rows at one column -- and the row reads are free of bank conflicts);
-  // then every wave takes 4 rows of each buffer and a lane handles 4 consecutive columns,
-  // so bias, residual, pre-activation and output accesses are contiguous along rows.
-  auto epi4 = [&](int m, int n, float* v) __attribute__((always_inline)) {
+  // The float32 accumulators pass through LDS (the stage buffers are free now) in passes of
+  // 128 rows, 32 rows per stage buffer (rows of T floats; 16-byte chunk c of row r stored at
+  // c ^ (r & 15), so both the writes -- 32 rows at one column -- and the row reads are free of
+  // bank conflicts): the waves owning those rows write them, then every wave takes a share of
+  // each buffer's rows and a lane handles 4 consecutive columns, so bias, residual,
+  // pre-activation and output accesses are contiguous along rows.
+  auto epi4 = [&](int m, int n, float* v, const float* v2) __attribute__((always_inline)) {
     const long long off = (long long)m * g.ldc + n;
     if (EPI == EPI_BF16 || EPI == EPI_ACT_BF16 || EPI == EPI_ACT_STORE_H) {
       if (g.bias) {
@@ -299,18 +334,19 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] += (float)rr[e];
       }
-      *(u32x2*)((bf16*)g.C + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      *(u32x2*)((bf16*)Cz + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     } else if (EPI == EPI_ACT_GRAD_BF16) {
       const f32x4 h = *(const f32x4*)(g.aux_f32 + off);
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] *= act_grad<ACT>(h[e]);
-      *(u32x2*)((bf16*)g.C + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      *(u32x2*)((bf16*)Cz + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
     } else if (EPI == EPI_GLU_BF16) {
-      const f32x4 u = *(const f32x4*)(g.aux_f32 + off);
-      if (g.aux2_f32) *(f32x4*)(g.aux2_f32 + off) = f32x4{v[0], v[1], v[2], v[3]};
+      if (g.aux_f32) *(f32x4*)(g.aux_f32 + off) = f32x4{v[0], v[1], v[2], v[3]};
+      if (g.aux2_f32) *(f32x4*)(g.aux2_f32 + off) = f32x4{v2[0], v2[1], v2[2], v2[3]};
+      float o[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] *= u[e] * sigmoid_f(u[e]);
-      *(u32x2*)((bf16*)g.C + off) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+      for (int e = 0; e < 4; ++e) o[e] = v2[e] * (v[e] * sigmoid_f(v[e]));
+      *(u32x2*)((bf16*)Cz + off) = u32x2{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3])};
     } else if (EPI == EPI_GLU_GRAD) {
       const f32x4 u = *(const f32x4*)(g.aux_f32 + off);
       const f32x4 w = *(const f32x4*)(g.aux2_f32 + off);
@@ -321,10 +357,10 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
         du[e] = v[e] * w[e] * sg * (1.f + u[e] * (1.f - sg));
         dw[e] = v[e] * u[e] * sg;
       }
-      *(u32x2*)((bf16*)g.C + off) = u32x2{pack_bf16x2(du[0], du[1]), pack_bf16x2(du[2], du[3])};
+      *(u32x2*)((bf16*)Cz + off) = u32x2{pack_bf16x2(du[0], du[1]), pack_bf16x2(du[2], du[3])};
       *(u32x2*)((bf16*)g.C2 + off) = u32x2{pack_bf16x2(dw[0], dw[1]), pack_bf16x2(dw[2], dw[3])};
     } else {  // EPI_F32: overwrite, or add into C
-      f32x4* cp = (f32x4*)((float*)g.C + off);
+      f32x4* cp = (f32x4*)((float*)Cz + off);
       if (g.accumulate) {
         const f32x4 c = *cp;
         *cp = f32x4{c[0] + v[0], c[1] + v[1], c[2] + v[2], c[3] + v[3]};
@@ -333,73 +369,123 @@ __global__ __launch_bounds__(kGT, 1) void gemm_kernel(const GemmArgs g) {
       }
     }
   };
+  constexpr int ROWB = T * 4;                // bytes of a row in LDS
+  constexpr int LPR = TNC / 4;               // lanes per row
+  constexpr int RPI = 64 / LPR;              // rows a wave handles at once
+  constexpr int RPWV = 32 / NWAVE;           // rows of a buffer per wave
+  constexpr int PASSES = T / 128;
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
-    if (wm == pass) {
-      // lane: row 32 mi + l32 of the pass (stage buffer mi, local row l32), columns
-      // 64 wn + 32 ni + 8 q4 + 4 hi .. +3 (chunk 16 wn + 8 ni + 2 q4 + hi)
-      static_for<0, 4>([&](auto Mi) __attribute__((always_inline)) {
-        constexpr int mi = decltype(Mi)::value;
-        char* sb = stage(std::integral_constant<int, mi>{}) + l32 * 1024;
+  for (int pass = 0; pass < PASSES; ++pass) {
+    // the rows of wave row wmp: m groups wmp * MI + mi of the tile, buffer (that) % 4
+    static_for<0, 2>([&](auto Wp) __attribute__((always_inline)) {
+      constexpr int wmp = decltype(Wp)::value;
+      if (wm == wmp && (PASSES == 1 || wmp == pass)) {
+        // lane: row l32 of the buffer, columns 64 wn + 32 ni + 8 q4 + 4 hi .. +3
+        static_for<0, MI>([&](auto Mi) __attribute__((always_inline)) {
+          constexpr int mi = decltype(Mi)::value;
+          char* sb = stage(std::integral_constant<int, (wmp * MI + mi) % 4>{}) + l32 * ROWB;
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
+          for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-          for (int q4 = 0; q4 < 4; ++q4) {
-            const int c = 16 * wn + 8 * ni + 2 * q4 + hi;
-            *(f32x4*)(sb + 16 * (c ^ (l32 & 15))) =
-                f32x4{acc[ni][mi][4 * q4], acc[ni][mi][4 * q4 + 1], acc[ni][mi][4 * q4 + 2], acc[ni][mi][4 * q4 + 3]};
-          }
-      });
-    }
+            for (int q4 = 0; q4 < 4; ++q4) {
+              const int c = 16 * wn + 8 * ni + 2 * q4 + hi;
+              *(f32x4*)(sb + 16 * (c ^ (l32 & 15))) =
+                  f32x4{acc[ni][mi][4 * q4], acc[ni][mi][4 * q4 + 1], acc[ni][mi][4 * q4 + 2], acc[ni][mi][4 * q4 + 3]};
+            }
+        });
+      }
+    });
     __syncthreads();
     static_for<0, 4>([&](auto Bi) __attribute__((always_inline)) {
       constexpr int bi = decltype(Bi)::value;
       const char* sb = stage(std::integral_constant<int, bi>{});
 #pragma unroll 2
-      for (int rr = 0; rr < 4; ++rr) {
-        const int lr = 4 * wave + rr;  // local row of the buffer
-        const f32x4 t = *(const f32x4*)(sb + lr * 1024 + 16 * (lane ^ (lr & 15)));
-        float v[4] = {t[0], t[1], t[2], t[3]};
-        epi4(m0 + 128 * pass + 32 * bi + lr, n0 + 4 * lane, v);
+      for (int rr = 0; rr < RPWV / RPI; ++rr) {
+        const int lr = RPWV * wave + rr * RPI + lane / LPR;  // local row of the buffer
+        const int c = lane % LPR;
+        const f32x4 t = *(const f32x4*)(sb + lr * ROWB + 16 * (c ^ (lr & 15)));
+        float v[4] = {t[0], t[1], t[2], t[3]}, v2[4] = {};
+        if constexpr (DUAL) {
+          const f32x4 t2 = *(const f32x4*)(sb + lr * ROWB + 16 * ((c + LPR) ^ (lr & 15)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v2[e] = t2[e];
+        }
+        epi4(m0 + 128 * pass + 32 * bi + lr, n0 + 4 * c, v, v2);
       }
     });
-    if (pass == 0) __syncthreads();
+    if (pass + 1 < PASSES) __syncthreads();
   }
 }
 
-// Column sums of a [M, N] matrix (bf16 or float32), deterministic two-pass reduction:
-// pass 1 writes partial sums of row slabs, pass 2 adds the slabs into out (+= or =).
+// Column sums of a bf16 [M, N] matrix (N a multiple of 8), deterministic two-pass reduction:
+// pass 1 writes partial sums of row slabs, a thread taking 8 columns (16-byte loads) of every
+// fourth row of its slab; pass 2 adds the slabs into out (+= or =).  HBM-bound.
 constexpr int kCS = 64;  // row slabs
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_partial_kernel(const T* x, float* part, int M, int N) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
+__global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16* x, float* part, int M, int N) {
+  __shared__ float red[4][64][9];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = (blockIdx.x * 64 + lane) * 8;
   const int slab = blockIdx.y;
-  if (n >= N) return;
   const int rows = (M + kCS - 1) / kCS;
   const int r0 = slab * rows, r1 = min(M, r0 + rows);
-  float s = 0.f;
-  for (int r = r0; r < r1; ++r) s += (float)x[(long long)r * N + n];
-  part[(long long)slab * N + n] = s;
+  float s[8] = {};
+  if (n < N)
+    for (int r = r0 + wave; r < r1; r += 4) {
+      const bf16x8 v = *(const bf16x8*)(x + (long long)r * N + n);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += (float)v[e];
+    }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[wave][lane][e] = s[e];
+  __syncthreads();
+  for (int i = threadIdx.x; i < 512; i += 256) {
+    const int l = i >> 3, e = i & 7, c = blockIdx.x * 512 + i;
+    if (c < N) part[(long long)slab * N + c] = (red[0][l][e] + red[1][l][e]) + (red[2][l][e] + red[3][l][e]);
+  }
 }
 __global__ __launch_bounds__(256) void colsum_final_kernel(const float* part, float* out, int N, int accumulate) {
   const int n = blockIdx.x * 256 + threadIdx.x;
   if (n >= N) return;
   float s = 0.f;
+#pragma unroll 8
   for (int sl = 0; sl < kCS; ++sl) s += part[(long long)sl * N + n];
   out[n] = accumulate ? out[n] + s : s;
 }
 
+// 256 x 256 tiles, or 128 x 128 where they finish sooner.  A round of the chip is 256 big
+// tiles, one a CU, or 512 small ones, two a CU, which hold half the work and run at 1 / kSmall
+// of the big tiles' rate (8192 x 4096 x 4096: 219 us in big tiles, 288 in small ones).  Big
+// tiles against small ones where the rule turns, us: 2048 x 4096 x 4096 (128 big tiles) 83, 72;
+// 4096^3 (256) 113, 145; 5120 x 1280 x 4864 (380) 74.4, 76.2; 2048 x 1024 x 1024 (32) 25.7, 13.6;
+// 2048 x 4096 x 1024 (32, deep) 76, 37.
+constexpr double kSmall = 1.35;
+int tile_size(const GemmArgs& g) {
+  const long long big = (long long)(g.M / 256) * (g.N / 256) * g.nb;
+  const long long r256 = (big + 255) / 256, r128 = (4 * big + 511) / 512;
+  return 0.5 * kSmall * (double)r128 < (double)r256 ? 128 : 256;
+}
+
 template <bool TA, bool TB, int EPI, int ACT>
 hipError_t launch_t(const GemmArgs& g, hipStream_t st) {
-  const int total = (g.M / kTM) * (g.N / kTN);
-  hipLaunchKernelGGL((gemm_kernel<TA, TB, EPI, ACT>), dim3(total), dim3(kGT), 0, st, g);
+  if constexpr (EPI == EPI_GLU_BF16) {
+    hipLaunchKernelGGL((gemm_kernel<256, TA, TB, EPI, ACT>), dim3((g.M / 256) * (g.N / 128)), dim3(512), 0, st, g);
+  } else {
+    const int t = tile_size(g);
+    const dim3 grid((unsigned)((g.M / t) * (g.N / t) * g.nb));
+    if (t == 256)
+      hipLaunchKernelGGL((gemm_kernel<256, TA, TB, EPI, ACT>), grid, dim3(512), 0, st, g);
+    else
+      hipLaunchKernelGGL((gemm_kernel<128, TA, TB, EPI, ACT>), grid, dim3(256), 0, st, g);
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st) {
-  if (g.M % kTM || g.N % kTN || g.K % kTK) return hipErrorInvalidValue;
+  if (g.M % 256 || g.N % 256 || g.K % kTK || g.nb < 1 || g.nb > 3 || g.ns < 1 || g.ns > 3 || (g.nb > 1 && g.ns > 1))
+    return hipErrorInvalidValue;
+  if (epi == EPI_GLU_BF16 && (g.nb > 1 || g.ns > 1)) return hipErrorInvalidValue;
 #define RA_GEMM_CASE(TA_, TB_, E_) \
   if (ta == TA_ && tb == TB_ && epi == E_) return launch_t<TA_, TB_, E_, 0>(g, st);
 #define RA_GEMM_CASE_ACT(TA_, TB_, E_)                                                 \
@@ -415,7 +501,6 @@ hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t
   RA_GEMM_CASE_ACT(false, true, EPI_ACT_GRAD_BF16)
   RA_GEMM_CASE(true, false, EPI_F32)
   RA_GEMM_CASE(false, true, EPI_F32)
-  RA_GEMM_CASE(false, false, EPI_F32)
   RA_GEMM_CASE(false, false, EPI_GLU_BF16)
   RA_GEMM_CASE(false, true, EPI_GLU_GRAD)
 #undef RA_GEMM_CASE
@@ -423,38 +508,14 @@ hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t
   return hipErrorInvalidValue;
 }
 
-int gemm_tile_m() { return kTM; }
-int gemm_tile_n() { return kTN; }
-int gemm_tile_k() { return kTK; }
-
 hipError_t launch_colsum_bf16(const void* x, float* part, float* out, int M, int N, int accumulate,
                               hipStream_t st) {
-  hipLaunchKernelGGL(colsum_partial_kernel<bf16>, dim3((N + 255) / 256, kCS), dim3(256), 0, st, (const bf16*)x,
-                     part, M, N);
+  hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 511) / 512, kCS), dim3(256), 0, st, (const bf16*)x, part, M,
+                     N);
   hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 255) / 256), dim3(256), 0, st, part, out, N, accumulate);
   return hipGetLastError();
 }
 
 size_t colsum_workspace_floats(int N) { return (size_t)kCS * N; }
-
-namespace {
-__global__ __launch_bounds__(256) void add_cast_kernel(const float* a, const bf16* b, bf16* out, long long n) {
-  const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i + 3 < n) {
-    const f32x4 x = *(const f32x4*)(a + i);
-    const bf16x4 y = *(const bf16x4*)(b + i);
-    *(u32x2*)(out + i) = u32x2{pack_bf16x2(x[0] + (float)y[0], x[1] + (float)y[1]),
-                               pack_bf16x2(x[2] + (float)y[2], x[3] + (float)y[3])};
-  } else {
-    for (long long j = i; j < n; ++j) out[j] = (bf16)(a[j] + (float)b[j]);
-  }
-}
-}  // namespace
-
-hipError_t launch_add_cast_bf16(const float* a, const void* b, void* out, long long n, hipStream_t st) {
-  const long long blocks = (n / 4 + 255) / 256 + 1;
-  hipLaunchKernelGGL(add_cast_kernel, dim3(blocks), dim3(256), 0, st, a, (const bf16*)b, (bf16*)out, n);
-  return hipGetLastError();
-}
 
 }  // namespace ra

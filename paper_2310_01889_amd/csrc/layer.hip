@@ -49,13 +49,12 @@ struct LayerActs {
 
 static int layer_acts(const void* x, const void* wq, const void* wk, const void* wv, const void* wo, LayerActs& a,
                       int S, int dm, int H, int N, int causal, hipStream_t st) {
-  const int c = S / N;
   int rc;
-  if ((rc = proj(x, wq, nullptr, a.q, S, dm, dm, c, st))) return rc;
-  if ((rc = proj(x, wk, nullptr, a.k, S, dm, dm, c, st))) return rc;
-  if ((rc = proj(x, wv, nullptr, a.v, S, dm, dm, c, st))) return rc;
+  const void* const w[3] = {wq, wk, wv};
+  void* const qkv[3] = {a.q, a.k, a.v};
+  if ((rc = proj3(x, w, qkv, S, dm, dm, st))) return rc;
   if ((rc = ring_attn_fwd(a.q, a.k, a.v, a.o, a.lse, 1, H, S, dm / H, N, causal, st))) return rc;
-  return proj(a.o, wo, x, a.y, S, dm, dm, c, st);  // Y = X + A Wo
+  return proj(a.o, wo, x, a.y, S, dm, dm, st);  // Y = X + A Wo
 }
 
 }  // namespace ra
@@ -94,8 +93,8 @@ int ring_layer_bwd(const void* x, const void* wq, const void* wk, const void* wv
   const int c = S / n_hosts, H = n_heads, dm = d_model;
   const size_t t = (size_t)S * dm;
   CallResources R(stream);
-  // activations, then dY, dO, dQ, dK, dV (bf16) and dX accumulated in float32
-  if ((rc = R.alloc(LayerActs::bytes(S, dm, H) + 5 * t * 2 + t * 4))) return rc;
+  // activations, then dY, dO, dQ, dK, dV (bf16)
+  if ((rc = R.alloc(LayerActs::bytes(S, dm, H) + 5 * t * 2))) return rc;
   LayerActs a;
   a.carve(R.ws, S, dm);
   char* dy = (char*)R.ws + LayerActs::bytes(S, dm, H);
@@ -103,38 +102,23 @@ int ring_layer_bwd(const void* x, const void* wq, const void* wk, const void* wv
   char* dq = dO + t * 2;
   char* dk = dq + t * 2;
   char* dv = dk + t * 2;
-  float* dx32 = (float*)(dv + t * 2);
   if ((rc = layer_acts(x, wq, wk, wv, wo, a, S, dm, H, n_hosts, causal, stream))) return rc;
   // Z = Y + FFN(Y):  dY = dZ + FFN'(Y)^T dZ
   if ((rc = ffn_backward(a.y, w1, nullptr, w2, dz, dz, dy, dw1, nullptr, dw2, nullptr, S, dm, d_ff, c, act, stream)))
     return rc;
   // Y = X + A Wo:  dWo = A^T dY,  dA = dY Wo^T
-  if ((rc = wgrad(a.o, dy, dwo, S, dm, dm, c, stream))) return rc;
-  for (int r0 = 0; r0 < S; r0 += c) {
-    GemmArgs g{};
-    g.A = dy + (size_t)r0 * dm * 2;
-    g.B = wo;
-    g.C = dO + (size_t)r0 * dm * 2;
-    g.lda = dm;
-    g.ldb = dm;
-    g.ldc = dm;
-    g.M = c;
-    g.N = dm;
-    g.K = dm;
-    if ((rc = gemm(g, false, true, EPI_BF16, stream))) return rc;
-  }
+  const void* const dY = dy;
+  if ((rc = wgrad(a.o, &dY, &dwo, 1, S, dm, dm, stream))) return rc;
+  if ((rc = dgrad(dy, wo, dO, S, dm, dm, stream))) return rc;
   // ring attention backward
   if ((rc = ring_attn_bwd(a.q, a.k, a.v, a.o, a.lse, dO, dq, dk, dv, 1, H, S, dm / H, n_hosts, causal, stream)))
     return rc;
   // projections: dW* = X^T d*, dX = dY + dQ Wq^T + dK Wk^T + dV Wv^T (float32 sum, one rounding)
-  if ((rc = wgrad(x, dq, dwq, S, dm, dm, c, stream))) return rc;
-  if ((rc = wgrad(x, dk, dwk, S, dm, dm, c, stream))) return rc;
-  if ((rc = wgrad(x, dv, dwv, S, dm, dm, c, stream))) return rc;
-  if ((rc = dgrad32(dq, wq, dx32, 0, S, dm, dm, c, stream))) return rc;
-  if ((rc = dgrad32(dk, wk, dx32, 1, S, dm, dm, c, stream))) return rc;
-  if ((rc = dgrad32(dv, wv, dx32, 1, S, dm, dm, c, stream))) return rc;
-  RA_HIP(launch_add_cast_bf16(dx32, dy, dx, (long long)t, stream));
-  return RA_OK;
+  const void* const dqkv[3] = {dq, dk, dv};
+  const void* const w[3] = {wq, wk, wv};
+  float* const dw[3] = {dwq, dwk, dwv};
+  if ((rc = wgrad(x, dqkv, dw, 3, S, dm, dm, stream))) return rc;
+  return dgrad3(dqkv, w, nullptr, dy, dx, S, dm, dm, stream);
 }
 
 }  // extern "C"

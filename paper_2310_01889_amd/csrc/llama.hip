@@ -227,136 +227,73 @@ static int rope_run(void* x, const float2* table, int S, int H, int D, int inver
 // SwiGLU forward over row blocks: y = (silu(x W1) * (x W3)) W2 (+ residual).
 static int swiglu_forward(const void* x, const void* w1, const void* w3, const void* w2, const void* residual, void* y,
                           int T, int dm, int dff, int block, hipStream_t st) {
-  const size_t nb = (size_t)block * dff;
   CallResources R(st);
-  int rc = R.alloc(nb * 4 + nb * 2);
-  if (rc) return rc;
-  float* u = (float*)R.ws;              // x W1, float32 [block, d_ff]
-  void* gte = (char*)R.ws + nb * 4;     // gate output, bf16
-  for (int r0 = 0; r0 < T; r0 += block) {
-    const char* xb = (const char*)x + (size_t)r0 * dm * 2;
-    GemmArgs a{};
-    a.A = xb;
-    a.B = w1;
-    a.C = u;
-    a.lda = dm;
-    a.ldb = dff;
-    a.ldc = dff;
-    a.M = block;
-    a.N = dff;
-    a.K = dm;
-    if ((rc = gemm(a, false, false, EPI_F32, st))) return rc;
-    GemmArgs b = a;  // gte = silu(u) * (x W3)
-    b.B = w3;
-    b.C = gte;
-    b.aux_f32 = u;
-    if ((rc = gemm(b, false, false, EPI_GLU_BF16, st))) return rc;
-    GemmArgs c{};
-    c.A = gte;
-    c.B = w2;
-    c.C = (char*)y + (size_t)r0 * dm * 2;
-    c.residual = residual ? (const char*)residual + (size_t)r0 * dm * 2 : nullptr;
-    c.lda = dff;
-    c.ldb = dm;
-    c.ldc = dm;
-    c.M = block;
-    c.N = dm;
-    c.K = dff;
+  int rows, rc;
+  if ((rc = alloc_row_groups(R, T, block, (size_t)dff * 2, 0, &rows))) return rc;
+  void* gte = R.ws;  // gate output, bf16 [rows, d_ff]
+  for (int r0 = 0; r0 < T; r0 += rows) {
+    const int m = T - r0 < rows ? T - r0 : rows;
+    const size_t off = (size_t)r0 * dm * 2;
+    GemmArgs a = gemm_args((const char*)x + off, dm, w1, dff, gte, dff, m, dff, dm);
+    a.B[1] = w3;
+    if ((rc = gemm(a, false, false, EPI_GLU_BF16, st))) return rc;
+    GemmArgs c = gemm_args(gte, dff, w2, dm, (char*)y + off, dm, m, dm, dff);
+    c.residual = residual ? (const char*)residual + off : nullptr;
     if ((rc = gemm(c, false, false, EPI_BF16, st))) return rc;
   }
   return RA_OK;
 }
 
-// SwiGLU backward over row blocks: dx32 (float32, overwritten) = du W1^T + dw W3^T and the
-// weight gradients (float32, overwritten), recomputing u = x W1 and w = x W3 per block.
+// SwiGLU backward over row blocks: dx = du W1^T + dw W3^T (float32 dx32 or bf16 dx16,
+// overwritten) and the weight gradients (float32, overwritten), recomputing u = x W1 and
+// w = x W3 per group of blocks.
 static int swiglu_backward(const void* x, const void* w1, const void* w3, const void* w2, const void* dy, float* dx32,
-                           float* dw1, float* dw3, float* dw2, int T, int dm, int dff, int block, hipStream_t st) {
-  const size_t nb = (size_t)block * dff;
+                           void* dx16, float* dw1, float* dw3, float* dw2, int T, int dm, int dff, int block,
+                           hipStream_t st) {
   CallResources R(st);
-  int rc = R.alloc(nb * 4 * 2 + nb * 2 * 3);
-  if (rc) return rc;
+  int rows, rc;
+  if ((rc = alloc_row_groups(R, T, block, (size_t)dff * 14, 0, &rows))) return rc;
+  const size_t nb = (size_t)rows * dff;
   float* u = (float*)R.ws;
   float* w = u + nb;
   char* gte = (char*)(w + nb);
   char* du = gte + nb * 2;
   char* dw = du + nb * 2;
-  for (int bi = 0, r0 = 0; r0 < T; ++bi, r0 += block) {
-    const char* xb = (const char*)x + (size_t)r0 * dm * 2;
-    const char* dyb = (const char*)dy + (size_t)r0 * dm * 2;
-    GemmArgs a{};
-    a.A = xb;
-    a.B = w1;
-    a.C = u;
-    a.lda = dm;
-    a.ldb = dff;
-    a.ldc = dff;
-    a.M = block;
-    a.N = dff;
-    a.K = dm;
-    if ((rc = gemm(a, false, false, EPI_F32, st))) return rc;
-    GemmArgs b = a;  // gte = silu(u) * w, and w itself
-    b.B = w3;
-    b.C = gte;
-    b.aux_f32 = u;
-    b.aux2_f32 = w;
-    if ((rc = gemm(b, false, false, EPI_GLU_BF16, st))) return rc;
-    GemmArgs g2{};  // dW2 (+)= gte^T dy
-    g2.A = gte;
-    g2.B = dyb;
-    g2.C = dw2;
-    g2.lda = dff;
-    g2.ldb = dm;
-    g2.ldc = dm;
-    g2.M = dff;
-    g2.N = dm;
-    g2.K = block;
-    g2.accumulate = bi > 0;
+  for (int r0 = 0; r0 < T; r0 += rows) {
+    const int m = T - r0 < rows ? T - r0 : rows;
+    const size_t off = (size_t)r0 * dm;
+    const char* xb = (const char*)x + off * 2;
+    const char* dyb = (const char*)dy + off * 2;
+    // gte = silu(u) * w, with u and w themselves
+    GemmArgs a = gemm_args(xb, dm, w1, dff, gte, dff, m, dff, dm);
+    a.B[1] = w3;
+    a.aux_f32 = u;
+    a.aux2_f32 = w;
+    if ((rc = gemm(a, false, false, EPI_GLU_BF16, st))) return rc;
+    // dW2 (+)= gte^T dy
+    GemmArgs g2 = gemm_args(gte, dff, dyb, dm, dw2, dm, dff, dm, m);
+    g2.accumulate = r0 > 0;
     if ((rc = gemm(g2, true, false, EPI_F32, st))) return rc;
-    GemmArgs gg{};  // dgte = dy W2^T  ->  du = dgte w silu'(u),  dw = dgte silu(u)
-    gg.A = dyb;
-    gg.B = w2;
-    gg.C = du;
+    // dgte = dy W2^T  ->  du = dgte w silu'(u),  dw = dgte silu(u)
+    GemmArgs gg = gemm_args(dyb, dm, w2, dm, du, dff, m, dff, dm);
     gg.C2 = dw;
     gg.aux_f32 = u;
     gg.aux2_f32 = w;
-    gg.lda = dm;
-    gg.ldb = dm;
-    gg.ldc = dff;
-    gg.M = block;
-    gg.N = dff;
-    gg.K = dm;
     if ((rc = gemm(gg, false, true, EPI_GLU_GRAD, st))) return rc;
-    GemmArgs g1{};  // dW1 (+)= x^T du, dW3 (+)= x^T dw
-    g1.A = xb;
-    g1.B = du;
-    g1.C = dw1;
-    g1.lda = dm;
-    g1.ldb = dff;
-    g1.ldc = dff;
-    g1.M = dm;
-    g1.N = dff;
-    g1.K = block;
-    g1.accumulate = bi > 0;
+    // dW1 (+)= x^T du, dW3 (+)= x^T dw
+    GemmArgs g1 = gemm_args(xb, dm, du, dff, dw1, dff, dm, dff, m);
+    g1.nb = 2;
+    g1.A[1] = xb;
+    g1.B[1] = dw;
+    g1.C[1] = dw3;
+    g1.accumulate = r0 > 0;
     if ((rc = gemm(g1, true, false, EPI_F32, st))) return rc;
-    GemmArgs g3 = g1;
-    g3.B = dw;
-    g3.C = dw3;
-    if ((rc = gemm(g3, true, false, EPI_F32, st))) return rc;
-    GemmArgs gx{};  // dx = du W1^T + dw W3^T (float32)
-    gx.A = du;
-    gx.B = w1;
-    gx.C = dx32 + (size_t)r0 * dm;
-    gx.lda = dff;
-    gx.ldb = dff;
-    gx.ldc = dm;
-    gx.M = block;
-    gx.N = dm;
-    gx.K = dff;
-    if ((rc = gemm(gx, false, true, EPI_F32, st))) return rc;
-    gx.A = dw;
-    gx.B = w3;
-    gx.accumulate = 1;
-    if ((rc = gemm(gx, false, true, EPI_F32, st))) return rc;
+    // dx = du W1^T + dw W3^T
+    GemmArgs gx = gemm_args(du, dff, w1, dff, dx32 ? (void*)(dx32 + off) : (char*)dx16 + off * 2, dm, m, dm, dff);
+    gx.ns = 2;
+    gx.A[1] = dw;
+    gx.B[1] = w3;
+    if ((rc = gemm(gx, false, true, dx32 ? EPI_F32 : EPI_BF16, st))) return rc;
   }
   return RA_OK;
 }
@@ -403,14 +340,14 @@ static int llama_forward(const void* x, const void* const* p, void* z, LlamaActs
   const int c = S / N, D = dm / H;
   int rc;
   if ((rc = norm_fwd(x, g1, a.n1, nullptr, S, dm, st))) return rc;
-  if ((rc = proj(a.n1, wq, nullptr, a.q, S, dm, dm, c, st))) return rc;
-  if ((rc = proj(a.n1, wk, nullptr, a.k, S, dm, dm, c, st))) return rc;
-  if ((rc = proj(a.n1, wv, nullptr, a.v, S, dm, dm, c, st))) return rc;
+  const void* const w[3] = {wq, wk, wv};
+  void* const qkv[3] = {a.q, a.k, a.v};
+  if ((rc = proj3(a.n1, w, qkv, S, dm, dm, st))) return rc;
   if ((rc = rope_table(a.rope, S, D, 0, st))) return rc;
   if ((rc = rope_run(a.q, a.rope, S, H, D, 0, st))) return rc;
   if ((rc = rope_run(a.k, a.rope, S, H, D, 0, st))) return rc;
   if ((rc = ring_attn_fwd(a.q, a.k, a.v, a.o, a.lse, 1, H, S, D, N, causal, st))) return rc;
-  if ((rc = proj(a.o, wo, x, a.h, S, dm, dm, c, st))) return rc;  // h = x + o Wo
+  if ((rc = proj(a.o, wo, x, a.h, S, dm, dm, st))) return rc;  // h = x + o Wo
   if ((rc = norm_fwd(a.h, g2, a.n2, nullptr, S, dm, st))) return rc;
   if (!z) return RA_OK;
   return swiglu_forward(a.n2, w1, w3, w2, a.h, z, S, dm, dff, c, st);  // z = h + SwiGLU(n2)
@@ -438,33 +375,21 @@ static int llama_backward(const void* x, const void* const* p, const void* dz, v
   float* part = dn32 + t;
   if ((rc = llama_forward(x, p, nullptr, a, S, dm, H, dff, N, causal, st))) return rc;
   // z = h + SwiGLU(n2):  dn2 = SwiGLU'(n2)^T dz;  dh = dz + RMSNorm'(h)^T dn2
-  if ((rc = swiglu_backward(a.n2, w1, w3, w2, dz, dn32, dw1, dw3, dw2, S, dm, dff, c, st))) return rc;
+  if ((rc = swiglu_backward(a.n2, w1, w3, w2, dz, dn32, nullptr, dw1, dw3, dw2, S, dm, dff, c, st))) return rc;
   if ((rc = norm_bwd(a.h, g2, dn32, dz, dh, dg2, part, S, dm, st))) return rc;
   // h = x + o Wo:  dWo = o^T dh,  dO = dh Wo^T
-  if ((rc = wgrad(a.o, dh, dwo, S, dm, dm, c, st))) return rc;
-  for (int r0 = 0; r0 < S; r0 += c) {
-    GemmArgs g{};
-    g.A = dh + (size_t)r0 * dm * 2;
-    g.B = wo;
-    g.C = dO + (size_t)r0 * dm * 2;
-    g.lda = dm;
-    g.ldb = dm;
-    g.ldc = dm;
-    g.M = c;
-    g.N = dm;
-    g.K = dm;
-    if ((rc = gemm(g, false, true, EPI_BF16, st))) return rc;
-  }
+  const void* const dH = dh;
+  if ((rc = wgrad(a.o, &dH, &dwo, 1, S, dm, dm, st))) return rc;
+  if ((rc = dgrad(dh, wo, dO, S, dm, dm, st))) return rc;
   if ((rc = ring_attn_bwd(a.q, a.k, a.v, a.o, a.lse, dO, dq, dk, dv, 1, H, S, D, N, causal, st))) return rc;
   // undo the rotation on the gradients of the rotated q and k (its transpose)
   if ((rc = rope_run(dq, a.rope, S, H, D, 1, st))) return rc;
   if ((rc = rope_run(dk, a.rope, S, H, D, 1, st))) return rc;
-  if ((rc = wgrad(a.n1, dq, dwq, S, dm, dm, c, st))) return rc;
-  if ((rc = wgrad(a.n1, dk, dwk, S, dm, dm, c, st))) return rc;
-  if ((rc = wgrad(a.n1, dv, dwv, S, dm, dm, c, st))) return rc;
-  if ((rc = dgrad32(dq, wq, dn32, 0, S, dm, dm, c, st))) return rc;
-  if ((rc = dgrad32(dk, wk, dn32, 1, S, dm, dm, c, st))) return rc;
-  if ((rc = dgrad32(dv, wv, dn32, 1, S, dm, dm, c, st))) return rc;
+  const void* const dqkv[3] = {dq, dk, dv};
+  const void* const w[3] = {wq, wk, wv};
+  float* const dw[3] = {dwq, dwk, dwv};
+  if ((rc = wgrad(a.n1, dqkv, dw, 3, S, dm, dm, st))) return rc;
+  if ((rc = dgrad3(dqkv, w, dn32, nullptr, nullptr, S, dm, dm, st))) return rc;
   // dx = dh + RMSNorm'(x)^T dn1
   return norm_bwd(x, g1, dn32, dh, dx, dg1, part, S, dm, st);
 }
@@ -529,12 +454,7 @@ int swiglu_ffn_bwd(const void* x, const void* w1, const void* w3, const void* w2
   if (int e = check_aligned({x, w1, w3, w2, dy, dx, dw1, dw3, dw2})) return e;
   int rc = check_gemm_dims(T, d_model, d_ff, block);
   if (rc) return rc;
-  CallResources R(stream);
-  if ((rc = R.alloc((size_t)T * d_model * 4))) return rc;
-  if ((rc = swiglu_backward(x, w1, w3, w2, dy, (float*)R.ws, dw1, dw3, dw2, T, d_model, d_ff, block, stream)))
-    return rc;
-  RA_HIP(launch_cast_f32_bf16((const float*)R.ws, dx, (long long)T * d_model, stream));
-  return RA_OK;
+  return swiglu_backward(x, w1, w3, w2, dy, nullptr, dx, dw1, dw3, dw2, T, d_model, d_ff, block, stream);
 }
 
 int llama_layer_fwd(const void* x, const void* const* params, void* z, int S, int d_model, int n_heads, int d_ff,

@@ -12,14 +12,16 @@ enum GemmEpilogue {
   EPI_ACT_STORE_H = 2,    // aux_f32 = acc + bias (pre-activation, float32); C = act(aux_f32), bf16
   EPI_ACT_GRAD_BF16 = 3,  // C = acc * act'(aux_f32[m][n]), stored bf16
   EPI_F32 = 4,            // C = acc (or C += acc if accumulate), float32
-  EPI_GLU_BF16 = 5,       // C = silu(aux_f32[m][n]) * acc, bf16; aux2_f32 = acc if aux2_f32 != null
+  EPI_GLU_BF16 = 5,       // with u = A B[0], w = A B[1]: C = silu(u) * w, bf16; aux_f32 = u, aux2_f32 = w unless null
   EPI_GLU_GRAD = 6        // with u = aux_f32, w = aux2_f32: C = acc * w * silu'(u), C2 = acc * silu(u) (bf16)
 };
 
 struct GemmArgs {
-  const void* A;          // bf16, [M][lda] (or [K][lda] when transposed)
-  const void* B;          // bf16, [K][ldb] (or [N][ldb] when transposed)
-  void* C;                // bf16 or float32 [M][ldc]
+  // nb products C[z] = A[z] B[z] of one shape in one launch, or (ns > 1) one product
+  // C[0] = sum over s < ns of A[s] B[s]
+  const void* A[3];       // bf16, [M][lda] (or [K][lda] when transposed)
+  const void* B[3];       // bf16, [K][ldb] (or [N][ldb] when transposed)
+  void* C[3];             // bf16 or float32 [M][ldc]
   const void* bias;       // bf16 [N] or null
   const void* residual;   // bf16 [M][ldc] or null
   float* aux_f32;         // float32 [M][ldc]: pre-activation (written or read)
@@ -27,20 +29,15 @@ struct GemmArgs {
   void* C2;               // bf16 [M][ldc]: second output of EPI_GLU_GRAD
   long long lda, ldb, ldc;
   int M, N, K, act, accumulate;
+  int nb = 1, ns = 1;
 };
 
-// ta: A stored as [K][M]; tb: B stored as [N][K].  M % 256, N % 256, K % 64 must be 0.
+// ta: A stored as [K][M]; tb: B stored as [N][K].  M % 256, N % 256, K % 32 must be 0.
 hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st);
-int gemm_tile_m();
-int gemm_tile_n();
-int gemm_tile_k();
 
 // out[n] (+)= sum_m x[m][n] for bf16 x [M][N]; part: colsum_workspace_floats(N) floats.
 hipError_t launch_colsum_bf16(const void* x, float* part, float* out, int M, int N, int accumulate,
                               hipStream_t st);
 size_t colsum_workspace_floats(int N);
-
-// out = bf16(a + b) elementwise for float32 a and bf16 b (n elements).
-hipError_t launch_add_cast_bf16(const float* a, const void* b, void* out, long long n, hipStream_t st);
 
 }  // namespace ra

@@ -97,7 +97,6 @@ hipError_t launch_bwd_pre_f32(const float* o, const float* dO, float* delta, int
 hipError_t launch_bwd_bf16(const BwdStep& s, int D, hipStream_t st);
 hipError_t launch_bwd_ring_bf16(const BwdRing& s, int D, hipStream_t st);
 hipError_t launch_bwd_f32(const BwdStep& s, int D, hipStream_t st);
-hipError_t launch_cast_f32_bf16(const float* src, void* dst, long long n, hipStream_t st);
 hipError_t launch_zero_f32(float* p, long long n, hipStream_t st);
 
 }  // namespace ra

@@ -12,15 +12,31 @@ int check_gemm_dims(int T, int d_in, int d_out, int block);
 // One GEMM launch (timed when kernel timing is enabled); RA_OK or an ra_status.
 int gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st);
 
-// Row-blocked products (bf16 operands, blocks of `block` rows):
-//   proj:    y (bf16) = x w (+ residual)
-//   wgrad:   dw (f32, overwritten) = x^T dy, accumulated over the row blocks
-//   dgrad32: dx32 (f32) = dy w^T, or += when accumulate
-int proj(const void* x, const void* w, const void* residual, void* y, int T, int din, int dout, int block,
-         hipStream_t st);
-int wgrad(const void* x, const void* dy, float* dw, int T, int din, int dout, int block, hipStream_t st);
-int dgrad32(const void* dy, const void* w, float* dx32, int accumulate, int T, int din, int dout, int block,
-            hipStream_t st);
+// A product C [M, N] = A B (K deep) with the leading dimensions of its operands.
+GemmArgs gemm_args(const void* A, long long lda, const void* B, long long ldb, void* C, long long ldc, int M, int N,
+                   int K);
+
+// Row-wise products of bf16 operands (x [T, din], dy and y [T, dout], w [din, dout]).  They have
+// no intermediate, so all row blocks go in one launch:
+//   proj:  y (bf16) = x w (+ residual)       dgrad: dx (bf16) = dy w^T
+//   wgrad: dw (f32, overwritten) = x^T dy    (n of them with one x: n <= 3)
+int proj(const void* x, const void* w, const void* residual, void* y, int T, int din, int dout, hipStream_t st);
+int proj3(const void* x, const void* const* w, void* const* y, int T, int din, int dout, hipStream_t st);
+int dgrad(const void* dy, const void* w, void* dx, int T, int din, int dout, hipStream_t st);
+int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, hipStream_t st);
+// The input gradient of three projections of one input: dq wq^T + dk wk^T + dv wv^T as one
+// product, either float32 (dx32) or bf16 with a residual added before the one rounding (dx).
+int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void* residual, void* dx, int T, int din,
+           int dout, hipStream_t st);
+
+// Workspace of a feed-forward network: row_bytes of intermediates per row plus fixed bytes.
+// The rows are worked on in groups of whole blocks, as many as kGroupBytes hold (more rows per
+// launch fill the chip: at 4096 x 11008 a 2048-row block is 128 to 344 tiles of 256 x 256 for
+// 256 CUs); one block at a time where a block needs more or memory is short.  *rows: rows of a
+// group (the last one may have fewer).
+constexpr size_t kGroupBytes = (size_t)4 << 30;
+struct CallResources;
+int alloc_row_groups(CallResources& R, int T, int block, size_t row_bytes, size_t fixed, int* rows);
 
 // Blockwise FFN forward: y = act(x W1 + b1) W2 + b2 (+ residual); arguments validated.
 int ffn_forward(const void* x, const void* w1, const void* b1, const void* w2, const void* b2, const void* residual,
