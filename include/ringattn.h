@@ -11,10 +11,10 @@
  * dQ on the host and dK/dV with the rotating block.  A blockwise feed-forward network
  * (Section 2 equation; Algorithm 1) follows the attention of the same query block.
  *
- * On one GPU the ring is virtual: all hosts' blocks live in device memory.  bf16 calls over
- * the whole ring are one launch (backward: one for dK/dV, one for dQ) that folds every
- * host's blocks, in ring order, where they lie; while ring_attn_timing_enable is on, one
- * launch a ring step.  Every other
+ * On one GPU the ring is virtual: all hosts' blocks live in device memory.  Calls over
+ * the whole ring are one launch (bf16 backward: one for dK/dV, one for dQ) that folds every
+ * host's blocks, in ring order, where they lie; bf16 ones, while ring_attn_timing_enable is
+ * on, one launch a ring step.  Every other
  * call runs n_hosts ring steps, each one kernel launch covering every host that has work at
  * that step, and the block each host needs at the next step reaches its per-host receive
  * buffer (double buffer) during the current step by device-to-device copies on a

@@ -1145,144 +1145,6 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const P p) {
   }
 }
 
-// =====================================================================================
-// float32 backward (exact float32, no matrix cores).  dK/dV: one thread per key;
-// dQ: one thread per query.  Query / key rows are staged through LDS 32 at a time.
-// =====================================================================================
-constexpr int kF = 64, kFT = 32;
-
-template <int D>
-__global__ __launch_bounds__(64) void bwd_dkdv_f32_kernel(const BwdStep p) {
-  __shared__ float sQ[kFT * D], sO[kFT * D], sL[kFT], sD[kFT];
-  const int n_kt = p.c / kF;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_kt;
-  const int L = blockIdx.x;
-  if (L >= total) return;
-  const int grp = L / n_kt, kt = L % n_kt;
-  const int slot = grp / BH, bh = grp % BH;
-  const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
-  const int t = threadIdx.x, rs = p.H * D;
-  const int key = kt * kF + t;
-  const int kpos = hs.k_pos0 + key;
-  const float* kr = (const float*)hs.k + (long long)b * hs.kv_bstride + (long long)key * rs + h * D;
-  const float* vr = (const float*)hs.v + (long long)b * hs.kv_bstride + (long long)key * rs + h * D;
-  float k[D], v[D], dk[D], dv[D];
-  #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    k[d] = kr[d];
-    v[d] = vr[d];
-    dk[d] = 0.f;
-    dv[d] = 0.f;
-  }
-  const float* qb = (const float*)p.q + (long long)b * p.q_bstride + h * D;
-  const float* ob = (const float*)p.dO + (long long)b * p.q_bstride + h * D;
-  const long long lrow0 = (long long)bh * p.Sq + hs.q_row0;
-  for (int q0 = 0; q0 < p.c; q0 += kFT) {
-    if (p.causal && hs.q_pos0 + q0 + kFT - 1 < hs.k_pos0 + kt * kF) continue;  // uniform
-    __syncthreads();
-    for (int e = t; e < kFT * D; e += 64) {
-      const int r = e / D, d = e % D;
-      const long long off = (long long)(hs.q_row0 + q0 + r) * rs + d;
-      sQ[e] = qb[off];
-      sO[e] = ob[off];
-    }
-    if (t < kFT) {
-      sL[t] = p.lse[lrow0 + q0 + t];
-      sD[t] = p.delta[lrow0 + q0 + t];
-    }
-    __syncthreads();
-    for (int j = 0; j < kFT; ++j) {
-      const int qpos = hs.q_pos0 + q0 + j;
-      if (p.causal && kpos > qpos) continue;
-      float s = 0.f, dp = 0.f;
-      #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        s = fmaf(sQ[j * D + d], k[d], s);
-        dp = fmaf(sO[j * D + d], v[d], dp);
-      }
-      const float pr = expf(s * p.scale - sL[j]);
-      const float ds = pr * (dp - sD[j]);
-      #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        dv[d] = fmaf(pr, sO[j * D + d], dv[d]);
-        dk[d] = fmaf(ds, sQ[j * D + d], dk[d]);
-      }
-    }
-  }
-  const long long grow = (long long)b * p.dkv_bstride + (long long)(p.dkv_row0[slot] + key) * rs + h * D;
-  #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    p.dk[grow + d] += dk[d] * p.scale;
-    p.dv[grow + d] += dv[d];
-  }
-}
-
-template <int D>
-__global__ __launch_bounds__(64) void bwd_dq_f32_kernel(const BwdStep p) {
-  __shared__ float sK[kFT * D], sV[kFT * D];
-  const int n_qt = p.c / kF;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_qt;
-  const int L = blockIdx.x;
-  if (L >= total) return;
-  const int grp = L / n_qt, qt = L % n_qt;
-  const int slot = grp / BH, bh = grp % BH;
-  const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
-  const int t = threadIdx.x, rs = p.H * D;
-  const int qr = hs.q_row0 + qt * kF + t;
-  const int qpos = hs.q_pos0 + qt * kF + t;
-  const long long lrow = (long long)bh * p.Sq + qr;
-  const float lse = p.lse[lrow], dlt = p.delta[lrow];
-  const long long qoff = (long long)b * p.q_bstride + (long long)qr * rs + h * D;
-  float q[D], o[D], dq[D];
-  #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    q[d] = ((const float*)p.q)[qoff + d];
-    o[d] = ((const float*)p.dO)[qoff + d];
-    dq[d] = 0.f;
-  }
-  const float* kb = (const float*)hs.k + (long long)b * hs.kv_bstride + h * D;
-  const float* vb = (const float*)hs.v + (long long)b * hs.kv_bstride + h * D;
-  for (int k0 = 0; k0 < p.c; k0 += kFT) {
-    if (p.causal && hs.k_pos0 + k0 > hs.q_pos0 + qt * kF + kF - 1) break;  // uniform
-    __syncthreads();
-    for (int e = t; e < kFT * D; e += 64) {
-      const int r = e / D, d = e % D;
-      const long long off = (long long)(k0 + r) * rs + d;
-      sK[e] = kb[off];
-      sV[e] = vb[off];
-    }
-    __syncthreads();
-    for (int j = 0; j < kFT; ++j) {
-      if (p.causal && hs.k_pos0 + k0 + j > qpos) continue;
-      float s = 0.f, dp = 0.f;
-      #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        s = fmaf(q[d], sK[j * D + d], s);
-        dp = fmaf(o[d], sV[j * D + d], dp);
-      }
-      const float ds = expf(s * p.scale - lse) * (dp - dlt);
-      #pragma unroll
-      for (int d = 0; d < D; ++d) dq[d] = fmaf(ds, sK[j * D + d], dq[d]);
-    }
-  }
-  float* dqrow = p.dq + qoff;
-  #pragma unroll
-  for (int d = 0; d < D; ++d) dqrow[d] += dq[d] * p.scale;
-}
-
-__global__ void zero_f32_kernel(float* p, long long n) {
-  const long long i = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i + 3 < n) {
-    *(f32x4*)(p + i) = f32x4{0.f, 0.f, 0.f, 0.f};
-  } else {
-    for (long long j = i; j < n; ++j) p[j] = 0.f;
-  }
-}
-
 }  // namespace
 
 hipError_t launch_bwd_pre_bf16(const void* o, const void* dO, const float* lse, float* delta, float* nlse_s, int B,
@@ -1331,25 +1193,6 @@ hipError_t launch_bwd_ring_bf16(const BwdRing& s, int D, hipStream_t st) {
     hipLaunchKernelGGL((bwd_dkdv_bf16_kernel<64, BwdRing>), dim3(g1), dim3(kBT), 0, st, s);
     hipLaunchKernelGGL((bwd_dq_bf16_kernel<64, BwdRing>), dim3(g2), dim3(kBT), 0, st, s);
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_f32(const BwdStep& s, int D, hipStream_t st) {
-  if (s.n_slots == 0) return hipSuccess;
-  const int g = s.n_slots * s.B * s.H * (s.c / kF);
-  if (D == 128) {
-    hipLaunchKernelGGL(bwd_dkdv_f32_kernel<128>, dim3(g), dim3(64), 0, st, s);
-    hipLaunchKernelGGL(bwd_dq_f32_kernel<128>, dim3(g), dim3(64), 0, st, s);
-  } else {
-    hipLaunchKernelGGL(bwd_dkdv_f32_kernel<64>, dim3(g), dim3(64), 0, st, s);
-    hipLaunchKernelGGL(bwd_dq_f32_kernel<64>, dim3(g), dim3(64), 0, st, s);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_zero_f32(float* p, long long n, hipStream_t st) {
-  const long long blocks = (n / 4 + 255) / 256 + 1;
-  hipLaunchKernelGGL(zero_f32_kernel, dim3(blocks), dim3(256), 0, st, p, n);
   return hipGetLastError();
 }
 

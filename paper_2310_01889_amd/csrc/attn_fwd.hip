@@ -498,105 +498,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
   }
 }
 
-// ===================================================================================
-// float32 kernel (exact float32 arithmetic, no matrix cores): one thread per query,
-// 64 queries per workgroup, 32-key tiles staged in LDS.  Natural-log state.
-// ===================================================================================
-constexpr int kF32BM = 64, kF32BN = 32;
-
-template <int D>
-__global__ __launch_bounds__(64) void fwd_f32_kernel(const FwdStep p) {
-  __shared__ float sK[kF32BN * D];
-  __shared__ float sV[kF32BN * D];
-  const int n_qt = p.c / kF32BM;
-  const int BH = p.B * p.H;
-  const int total = p.n_slots * BH * n_qt;
-  const int L = blockIdx.x;
-  if (L >= total) return;
-  const int grp = L / n_qt, qt = L % n_qt;
-  const int slot = grp / BH, bh = grp % BH;
-  const int b = bh / p.H, h = bh % p.H;
-  const StepHost hs = p.host[slot];
-  const int t = threadIdx.x;
-  const int rs = p.H * D;
-  const int qr = hs.q_row0 + qt * kF32BM + t;
-  const int qpos = hs.q_pos0 + qt * kF32BM + t;
-  const long long st_row = (long long)bh * p.Sq + qr;
-
-  const float* qrow = (const float*)p.q + (long long)b * p.q_bstride + (long long)qr * rs + h * D;
-  const float* kbase = (const float*)hs.k + (long long)b * hs.kv_bstride + h * D;
-  const float* vbase = (const float*)hs.v + (long long)b * hs.kv_bstride + h * D;
-  float* accrow = p.acc + st_row * D;
-
-  float q[D], acc[D];
-  #pragma unroll
-  for (int d = 0; d < D; ++d) q[d] = qrow[d];
-  float m_run, l_run;
-  if (hs.flags & kFirst) {
-    #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = 0.f;
-    m_run = -INFINITY;
-    l_run = 0.f;
-  } else {
-    #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] = accrow[d];
-    m_run = p.m[st_row];
-    l_run = p.l[st_row];
-  }
-
-  int nt = p.c / kF32BN;
-  if (p.causal) {
-    const int vis = hs.q_pos0 + qt * kF32BM + kF32BM - hs.k_pos0;
-    nt = min(nt, max(0, (vis + kF32BN - 1) / kF32BN));
-  }
-  for (int it = 0; it < nt; ++it) {
-    __syncthreads();
-    for (int e = t; e < kF32BN * D; e += 64) {
-      const int r = e / D, d = e % D;
-      const long long off = (long long)(it * kF32BN + r) * rs + d;
-      sK[e] = kbase[off];
-      sV[e] = vbase[off];
-    }
-    __syncthreads();
-    float s[kF32BN];
-    float mx = -INFINITY;
-    #pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      float dot = 0.f;
-      #pragma unroll
-      for (int d = 0; d < D; ++d) dot = fmaf(q[d], sK[j * D + d], dot);
-      const int kpos = hs.k_pos0 + it * kF32BN + j;
-      s[j] = (p.causal && kpos > qpos) ? -INFINITY : dot * p.scale;
-      mx = fmaxf(mx, s[j]);
-    }
-    const float m_new = fmaxf(m_run, mx);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = expf(m_run - m_use);
-    m_run = m_new;
-    l_run *= alpha;
-    #pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] *= alpha;
-    #pragma unroll
-    for (int j = 0; j < kF32BN; ++j) {
-      const float pj = expf(s[j] - m_use);
-      l_run += pj;
-      #pragma unroll
-      for (int d = 0; d < D; ++d) acc[d] = fmaf(pj, sV[j * D + d], acc[d]);
-    }
-  }
-  if (hs.flags & kLast) {
-    float* orow = (float*)p.o + (long long)b * p.q_bstride + (long long)qr * rs + h * D;
-    #pragma unroll
-    for (int d = 0; d < D; ++d) orow[d] = acc[d] / l_run;
-    p.lse[st_row] = m_run + logf(l_run);
-  } else {
-    #pragma unroll
-    for (int d = 0; d < D; ++d) accrow[d] = acc[d];
-    p.m[st_row] = m_run;
-    p.l[st_row] = l_run;
-  }
-}
-
 }  // namespace
 
 // Long blocks (D = 128, at least 16384 keys, a multiple of 256) run the eight-wave kernel:
@@ -629,16 +530,6 @@ hipError_t launch_fwd_ring_bf16(const FwdRing& s, int D, hipStream_t st) {
     hipLaunchKernelGGL((fwd_bf16_kernel<128, 4, true>), dim3(ring_grid(G, (s.S + kBM - 1) / kBM)), dim3(kThreads), 0, st, s);
   else
     hipLaunchKernelGGL((fwd_bf16_kernel<64, 4, true>), dim3(ring_grid(G, (s.S + kBM - 1) / kBM)), dim3(kThreads), 0, st, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_fwd_f32(const FwdStep& s, int D, hipStream_t st) {
-  const int total = s.n_slots * s.B * s.H * (s.c / kF32BM);
-  if (total == 0) return hipSuccess;
-  if (D == 128)
-    hipLaunchKernelGGL(fwd_f32_kernel<128>, dim3(total), dim3(64), 0, st, s);
-  else
-    hipLaunchKernelGGL(fwd_f32_kernel<64>, dim3(total), dim3(64), 0, st, s);
   return hipGetLastError();
 }
 

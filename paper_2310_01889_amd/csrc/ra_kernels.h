@@ -23,7 +23,7 @@ struct StepHost {
   int flags;              // kFirst | kLast
 };
 
-// Forward step: fold one key/value block into every listed host's running state.
+// Forward step, bf16: fold one key/value block into every listed host's running state.
 struct FwdStep {
   StepHost host[kMaxSlots];
   const void* q;          // [B, Sq, H, D]
@@ -31,32 +31,32 @@ struct FwdStep {
   float* lse;             // [B, H, Sq]
   float* acc;             // running numerator, float32, B*H*Sp*D
   float* m;               // running max (log2 units of the scaled scores), [B, H, Sp]
-  float* l;               // running denominator, [B, H, Sp] (bf16: its two halves, [B, H, Sp, 2])
+  float* l;               // running denominator in two halves, [B, H, Sp, 2]
   long long q_bstride;    // Sq * H * D
   int n_slots, B, H, Sq, c, causal;
   int Sp;                 // rows of the state: the hosts' blocks in full (Sq, rounded up to blocks)
   float scale;            // 1 / sqrt(D)
 };
 
-// Forward over the whole ring in one launch: every host's queries against every block, read
-// where the blocks lie (rows [j c, (j + 1) c) of k and v).
+// Forward over the whole ring in one launch, bf16 or float32 tensors: every host's queries
+// against every block, read where the blocks lie (rows [j c, (j + 1) c) of k and v).
 struct FwdRing {
   const void *q, *k, *v;  // [B, S, H, D]
   void* o;                // [B, S, H, D]
   float* lse;             // [B, H, S]
   long long bstride;      // S * H * D
-  int B, H, S, c, N, causal;  // causal: S need not fill the N blocks of c rows
+  int B, H, S, c, N, causal;  // bf16, causal: S need not fill the N blocks of c rows
   float scale;            // 1 / sqrt(D)
 };
 
-// Backward step: one key/value block per host; dq accumulates per host, dk/dv per block.
+// Backward step, bf16: one key/value block per host; dq accumulates per host, dk/dv per block.
 struct BwdStep {
   StepHost host[kMaxSlots];
   const void* q;          // [B, Sq, H, D]
   const void* dO;         // [B, Sq, H, D]
-  const float* lse;       // [B, H, Sq]  lse, natural log (float32 kernels); -lse sqrt(D) (bf16)
-  const float* delta;     // [B, H, Sq]  rowsum(dO * o) (float32 kernels); its negative (bf16)
-  float* dq;              // float32 [B, Sq, H, D] (bf16: accumulators between the host's steps)
+  const float* lse;       // [B, H, Sq]  -lse sqrt(D)
+  const float* delta;     // [B, H, Sq]  -rowsum(dO * o)
+  float* dq;              // float32 [B, Sq, H, D]: accumulators between the host's steps
   float* dk;              // float32 [B, Skv, H, D]: gradient of the block each host holds
   float* dv;              //   (home position of that block: see dkv_row0)
   int dkv_row0[kMaxSlots];// first row of the host's current block in dk / dv
@@ -65,7 +65,7 @@ struct BwdStep {
   int n_slots, B, H, Sq, c, causal;
   int Skv;                // rows of dk / dv that exist
   float scale;
-  // bf16 kernels.  whole: the call holds every contribution to dk / dv, so these hold the
+  // whole: the call holds every contribution to dk / dv, so these hold the
   // accumulators between steps; the block a slot holds is touched for the first (kFirst: start
   // from zero) or the last time (kLast: the sum goes out, rounded, to dk_out / dv_out).
   // Otherwise contributions are added into dk / dv.
@@ -76,19 +76,20 @@ struct BwdStep {
   void* dq_out;           // bf16 [B, Sq, H, D], written on a host's kLast step
 };
 
-// Backward over the whole ring, bf16: one launch for dK and dV, one for dQ.
+// Backward over the whole ring: bf16, one launch for dK and dV, one for dQ; float32, one for
+// all three.
 struct BwdRing {
   const void *q, *k, *v, *dO;  // [B, S, H, D]
-  const float *lse, *delta;    // -lse sqrt(D) and -Delta, [B, H, S]
+  const float *lse, *delta;    // [B, H, S]: -lse sqrt(D) and -Delta (bf16), lse and Delta (float32)
   void *dq, *dk, *dv;          // [B, S, H, D]
   long long bstride;           // S * H * D
-  int B, H, S, c, N, causal;   // causal: S need not fill the N blocks of c rows
+  int B, H, S, c, N, causal;   // bf16, causal: S need not fill the N blocks of c rows
   float scale;
 };
 
 hipError_t launch_fwd_bf16(const FwdStep& s, int D, hipStream_t st);
 hipError_t launch_fwd_ring_bf16(const FwdRing& s, int D, hipStream_t st);
-hipError_t launch_fwd_f32(const FwdStep& s, int D, hipStream_t st);
+hipError_t launch_fwd_ring_f32(const FwdRing& s, int D, hipStream_t st);
 // -Delta = -rowsum(dO * o) and -lse * sqrt(D), both [B, H, S] (for the bf16 step kernels)
 hipError_t launch_bwd_pre_bf16(const void* o, const void* dO, const float* lse, float* ndelta, float* nlse_s,
                                int B, int S, int H, int D, hipStream_t st);
@@ -96,7 +97,6 @@ hipError_t launch_bwd_pre_f32(const float* o, const float* dO, float* delta, int
                               int D, hipStream_t st);
 hipError_t launch_bwd_bf16(const BwdStep& s, int D, hipStream_t st);
 hipError_t launch_bwd_ring_bf16(const BwdRing& s, int D, hipStream_t st);
-hipError_t launch_bwd_f32(const BwdStep& s, int D, hipStream_t st);
-hipError_t launch_zero_f32(float* p, long long n, hipStream_t st);
+hipError_t launch_bwd_ring_f32(const BwdRing& s, int D, hipStream_t st);
 
 }  // namespace ra

@@ -4,7 +4,7 @@
 // key/value block live in device memory; host i folds key/value block order(i, t) --
 // (i - t) mod n_hosts for the ring -- at step t.
 //
-// bf16 calls over the whole ring in ring order run as one launch (backward: one for dK/dV,
+// Calls over the whole ring in ring order run as one launch (bf16 backward: one for dK/dV,
 // one for dQ) that walks every query (key) tile over the blocks it meets, read where they
 // lie.  Every other call runs n_hosts steps,
 // every host with work at a step being one slot of a single kernel launch.  Step 0 reads each
@@ -287,16 +287,17 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 // ---------------------------------------------------------------------------------
 // Forward
 // ---------------------------------------------------------------------------------
-// Whole ring in ring order, bf16: all blocks are on this device, so nothing is exchanged and
-// one launch walks each query tile over its host's blocks (launch_fwd_ring_bf16): no receive
+// Whole ring in ring order: all blocks are on this device, so nothing is exchanged and
+// one launch walks each query tile over its host's blocks (launch_fwd_ring_*): no receive
 // buffers, no state between steps, one grid instead of N, each with its own tail.  While
-// launches are being timed it runs as one launch a ring step, reading in place, so that
-// every step has its entry.  RINGATTN_SERIAL_COPY / RINGATTN_POISON ask for the exchange by
-// copies.  All give the same bits.
+// launches are being timed a bf16 call runs as one launch a ring step, reading in place, so that
+// every step has its entry; RINGATTN_SERIAL_COPY / RINGATTN_POISON ask, in bf16, for the
+// exchange by copies.  All give the same bits.
 static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream) {
   const int nh = (int)P.hosts.size();
-  const bool inplace = P.elt == 2 && P.whole() && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
-  if (inplace && !timing_on()) {
+  const bool f32 = P.elt == 4;  // always one launch
+  const bool inplace = f32 || P.whole() && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
+  if (f32 || (inplace && !timing_on())) {
     FwdRing a{};
     a.q = P.q;
     a.k = P.k;
@@ -311,7 +312,9 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
     a.N = P.N;
     a.causal = P.causal;
     a.scale = 1.0f / sqrtf((float)P.D);
-    RA_HIP(launch_fwd_ring_bf16(a, P.D, stream));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] {
+      return f32 ? launch_fwd_ring_f32(a, P.D, stream) : launch_fwd_ring_bf16(a, P.D, stream);
+    }));
     return RA_OK;
   }
   const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
@@ -348,9 +351,7 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
     st.n_slots = (int)hs.size();
     for (size_t s = 0; s < hs.size(); ++s) st.host[s] = hs[s];
     if (!contiguous) chain = nullptr;
-    RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] {
-      return P.elt == 2 ? launch_fwd_bf16(st, P.D, stream) : launch_fwd_f32(st, P.D, stream);
-    }, &chain));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] { return launch_fwd_bf16(st, P.D, stream); }, &chain));
     return RA_OK;
   });
 }
@@ -367,11 +368,11 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
   const int nh = (int)P.hosts.size();
   const size_t nrow = (size_t)P.B * P.H * P.Sq;
   const size_t telems = (size_t)P.B * P.S * P.H * P.D;
-  const bool f32 = P.elt == 4;  // float32 gradients accumulate straight into the outputs
-  const bool inplace = !f32 && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
-  const bool one = inplace && !timing_on();
+  const bool f32 = P.elt == 4;  // always one launch
+  const bool inplace = f32 || (!env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON"));
+  const bool one = f32 || (inplace && !timing_on());
   const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
-  const size_t grads = f32 || one ? 0 : 3 * telems * sizeof(float);
+  const size_t grads = one ? 0 : 3 * telems * sizeof(float);
   CallResources R(stream);
   int rc = R.alloc(recv + 2 * nrow * sizeof(float) + grads);
   if (rc) return rc;
@@ -388,7 +389,7 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
     a.k = P.k;
     a.v = P.v;
     a.dO = dO;
-    a.lse = lse2;
+    a.lse = f32 ? lse : lse2;
     a.delta = delta;
     a.dq = dq;
     a.dk = dk;
@@ -401,31 +402,27 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
     a.N = P.N;
     a.causal = P.causal;
     a.scale = 1.0f / sqrtf((float)P.D);
-    RA_HIP(launch_bwd_ring_bf16(a, P.D, stream));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] {
+      return f32 ? launch_bwd_ring_f32(a, P.D, stream) : launch_bwd_ring_bf16(a, P.D, stream);
+    }));
     return RA_OK;
   }
-  float* gq = f32 ? (float*)dq : lse2 + nrow;
-  float* gk = f32 ? (float*)dk : gq + telems;
-  float* gv = f32 ? (float*)dv : gk + telems;
+  float* gq = lse2 + nrow;
+  float* gk = gq + telems;
+  float* gv = gk + telems;
   std::vector<int> blk_first(P.N, -1), blk_last(P.N, -1);  // steps that touch block j
-  if (f32) {
-    RA_HIP(launch_zero_f32(gq, (long long)telems, stream));
-    RA_HIP(launch_zero_f32(gk, (long long)telems, stream));
-    RA_HIP(launch_zero_f32(gv, (long long)telems, stream));
-  } else {
-    for (int t = 0; t < P.N; ++t)
-      for (int i : P.hosts) {
-        const int j = P.blk(i, t);
-        if (!P.active(i, j)) continue;
-        if (blk_first[j] < 0) blk_first[j] = t;
-        blk_last[j] = t;
-      }
-  }
+  for (int t = 0; t < P.N; ++t)
+    for (int i : P.hosts) {
+      const int j = P.blk(i, t);
+      if (!P.active(i, j)) continue;
+      if (blk_first[j] < 0) blk_first[j] = t;
+      blk_last[j] = t;
+    }
 
   BwdStep st{};
   st.q = P.q;
   st.dO = dO;
-  st.lse = f32 ? lse : lse2;
+  st.lse = lse2;
   st.delta = delta;
   st.dq = gq;
   st.dk = gk;
@@ -439,12 +436,10 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
   st.c = P.c();
   st.causal = P.causal;
   st.scale = 1.0f / sqrtf((float)P.D);
-  if (!f32) {
-    st.whole = 1;
-    st.dq_out = dq;
-    st.dk_out = dk;
-    st.dv_out = dv;
-  }
+  st.whole = 1;
+  st.dq_out = dq;
+  st.dk_out = dk;
+  st.dv_out = dv;
   hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
   return run_ring(P, stream, R, base, inplace, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
                                                   const std::vector<int>& blks, bool contiguous) -> int {
@@ -452,14 +447,11 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
     for (size_t s = 0; s < hs.size(); ++s) {
       st.host[s] = hs[s];
       st.dkv_row0[s] = blks[s] * P.c();
-      st.dkv_flags[s] = f32 ? 0
-                            : (unsigned char)((t == blk_first[blks[s]] ? kFirst : 0) |
-                                              (t == blk_last[blks[s]] ? kLast : 0));
+      st.dkv_flags[s] =
+          (unsigned char)((t == blk_first[blks[s]] ? kFirst : 0) | (t == blk_last[blks[s]] ? kLast : 0));
     }
     if (!contiguous) chain = nullptr;
-    RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] {
-      return f32 ? launch_bwd_f32(st, P.D, stream) : launch_bwd_bf16(st, P.D, stream);
-    }, &chain));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] { return launch_bwd_bf16(st, P.D, stream); }, &chain));
     return RA_OK;
   });
 }
