@@ -31,7 +31,6 @@ namespace {
 constexpr float kNormEps = 1e-6f;
 constexpr double kRopeBase = 10000.0;
 constexpr int kNormMaxD = 8192;       // d_model limit of the RMSNorm kernels
-constexpr int kNormChunks = kNormMaxD / 512;
 constexpr int kNormSlab = 32;         // rows per workgroup of the RMSNorm backward
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -70,35 +69,53 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const bf16* x, const b
 
 // Backward of y = x * rstd * g for upstream dy (float32):
 //   dx = rstd g dy - x rstd^3 / d * sum_j(g_j dy_j x_j),   dg = sum_rows dy x rstd.
-// One wave per slab of kNormSlab rows; out = bf16(dres + dx) (dres may be null);
-// dg_part[slab][d] holds the slab's column sums (added up in slab order afterwards).
-__global__ __launch_bounds__(64) void rmsnorm_bwd_kernel(const bf16* x, const bf16* g, const float* dy,
-                                                         const bf16* dres, bf16* out, float* dg_part, int T,
-                                                         int d, float eps) {
-  const int lane = threadIdx.x, slab = blockIdx.x;
-  float dgacc[kNormChunks][8];
+// A workgroup of 4 waves per slab of kNormSlab rows, a wave taking every fourth row of it; out =
+// bf16(dres + dx) (dres may be null); dg_part[slab][d] holds the slab's column sums (added up in
+// slab order afterwards).  CH: 512-column chunks of a row (a lane holds 8 columns of each).  Up
+// to 8 chunks a row stays in registers between its two passes.  HBM-bound (10 bytes an element):
+// 16384 x 4096 with the column sum below in 188 us; with one wave a slab, two a CU, 514.
+template <int CH>
+__global__ __launch_bounds__(256, CH > 8 ? 1 : 2) void rmsnorm_bwd_kernel(const bf16* x, const bf16* g, const float* dy,
+                                                             const bf16* dres, bf16* out, float* dg_part, int T,
+                                                             int d, float eps) {
+  constexpr bool KEEP = CH <= 8;
+  __shared__ float red[KEEP ? 2 : 1][CH * 512];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, slab = blockIdx.x;
+  float dgacc[CH][8];
 #pragma unroll
-  for (int i = 0; i < kNormChunks; ++i)
+  for (int i = 0; i < CH; ++i)
 #pragma unroll
     for (int e = 0; e < 8; ++e) dgacc[i][e] = 0.f;
-  for (int rr = 0; rr < kNormSlab; ++rr) {
+  for (int rr = wave; rr < kNormSlab; rr += 4) {
     const int row = slab * kNormSlab + rr;
     if (row >= T) break;
     const bf16* xr = x + (long long)row * d;
     const float* dyr = dy + (long long)row * d;
+    bf16x8 xv[KEEP ? CH : 1];
+    f32x4 dv[KEEP ? CH : 1][2];
+    auto fetch = [&](int i, int k) __attribute__((always_inline)) {
+      const int c = lane * 8 + 512 * i;
+      xv[k] = *(const bf16x8*)(xr + c);
+      dv[k][0] = *(const f32x4*)(dyr + c);
+      dv[k][1] = *(const f32x4*)(dyr + c + 4);
+    };
+    if constexpr (KEEP) {
+#pragma unroll
+      for (int i = 0; i < CH; ++i)
+        if (lane * 8 + 512 * i < d) fetch(i, i);
+    }
     float ss = 0.f, sgdx = 0.f;
 #pragma unroll
-    for (int i = 0; i < kNormChunks; ++i) {
-      const int c = lane * 8 + 512 * i;
+    for (int i = 0; i < CH; ++i) {
+      const int c = lane * 8 + 512 * i, k = KEEP ? i : 0;
       if (c < d) {
-        const bf16x8 v = *(const bf16x8*)(xr + c);
+        if constexpr (!KEEP) fetch(i, 0);
         const bf16x8 gg = *(const bf16x8*)(g + c);
-        const f32x4 d0 = *(const f32x4*)(dyr + c), d1 = *(const f32x4*)(dyr + c + 4);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float xv = (float)v[e], dv = e < 4 ? d0[e] : d1[e - 4];
-          ss = fmaf(xv, xv, ss);
-          sgdx = fmaf((float)gg[e] * dv, xv, sgdx);
+          const float xe = (float)xv[k][e], de = dv[k][e >> 2][e & 3];
+          ss = fmaf(xe, xe, ss);
+          sgdx = fmaf((float)gg[e] * de, xe, sgdx);
         }
       }
     }
@@ -108,29 +125,58 @@ __global__ __launch_bounds__(64) void rmsnorm_bwd_kernel(const bf16* x, const bf
     const float coef = r * r * r * sgdx / d;
     bf16* outr = out + (long long)row * d;
 #pragma unroll
-    for (int i = 0; i < kNormChunks; ++i) {
-      const int c = lane * 8 + 512 * i;
+    for (int i = 0; i < CH; ++i) {
+      const int c = lane * 8 + 512 * i, k = KEEP ? i : 0;
       if (c < d) {
-        const bf16x8 v = *(const bf16x8*)(xr + c);
+        if constexpr (!KEEP) fetch(i, 0);
         const bf16x8 gg = *(const bf16x8*)(g + c);
-        const f32x4 d0 = *(const f32x4*)(dyr + c), d1 = *(const f32x4*)(dyr + c + 4);
         bf16x8 rv;
         if (dres) rv = *(const bf16x8*)(dres + (long long)row * d + c);
         float o[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const float xv = (float)v[e], dv = e < 4 ? d0[e] : d1[e - 4];
-          o[e] = r * (float)gg[e] * dv - coef * xv + (dres ? (float)rv[e] : 0.f);
-          dgacc[i][e] = fmaf(dv, xv * r, dgacc[i][e]);
+          const float xe = (float)xv[k][e], de = dv[k][e >> 2][e & 3];
+          o[e] = r * (float)gg[e] * de - coef * xe + (dres ? (float)rv[e] : 0.f);
+          dgacc[i][e] = fmaf(de, xe * r, dgacc[i][e]);
         }
         *(u32x4*)(outr + c) = u32x4{pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
                                      pack_bf16x2(o[6], o[7])};
       }
     }
   }
+  // the four waves' column sums, pairwise through LDS: (0 + 2) + (1 + 3), or one after another
+  auto put = [&](float* s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[i * 512 + e * 64 + lane] = dgacc[i][e];
+  };
+  auto add = [&](const float* s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < CH; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dgacc[i][e] += s[i * 512 + e * 64 + lane];
+  };
+  if constexpr (KEEP) {
+    if (wave >= 2) put(red[wave - 2]);
+    __syncthreads();
+    if (wave < 2) add(red[wave]);
+    __syncthreads();
+    if (wave == 1) put(red[0]);
+    __syncthreads();
+    if (wave == 0) add(red[0]);
+  } else {
+    for (int w = 3; w > 0; --w) {
+      if (wave == w) put(red[0]);
+      __syncthreads();
+      if (wave == w - 1) add(red[0]);
+      __syncthreads();
+    }
+  }
+  if (wave != 0) return;
   float* part = dg_part + (long long)slab * d;
 #pragma unroll
-  for (int i = 0; i < kNormChunks; ++i) {
+  for (int i = 0; i < CH; ++i) {
     const int c = lane * 8 + 512 * i;
     if (c < d) {
       *(f32x4*)(part + c) = f32x4{dgacc[i][0], dgacc[i][1], dgacc[i][2], dgacc[i][3]};
@@ -139,13 +185,24 @@ __global__ __launch_bounds__(64) void rmsnorm_bwd_kernel(const bf16* x, const bf
   }
 }
 
-// dg[c] = sum over slabs (in order) of dg_part[slab][c]
-__global__ __launch_bounds__(256) void slab_sum_kernel(const float* part, float* out, int n_slabs, int d) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= d) return;
+// dg[c] = sum over slabs of dg_part[slab][c] in a fixed order: 16 waves take every 16th slab of
+// 64 columns each, their sums are added in wave order (one thread a column walking every slab
+// was a chain of 512 loads: 124 us at 16384 x 4096).
+__global__ __launch_bounds__(1024) void slab_sum_kernel(const float* part, float* out, int n_slabs, int d) {
+  __shared__ float red[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = blockIdx.x * 64 + lane;
   float s = 0.f;
-  for (int k = 0; k < n_slabs; ++k) s += part[(long long)k * d + c];
-  out[c] = s;
+  if (c < d) {
+#pragma unroll 8
+    for (int k = wave; k < n_slabs; k += 16) s += part[(long long)k * d + c];
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave != 0 || c >= d) return;
+  float t = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < 16; ++w) t += red[w][lane];
+  out[c] = t;
 }
 
 // ---- rotary position embedding --------------------------------------------------------------
@@ -201,10 +258,16 @@ static int norm_fwd(const void* x, const void* g, void* y, float* rstd, int T, i
 static int norm_bwd(const void* x, const void* g, const float* dy, const void* dres, void* out, float* dg,
                     float* part, int T, int d, hipStream_t st) {
   const int slabs = (T + kNormSlab - 1) / kNormSlab;
-  hipLaunchKernelGGL(rmsnorm_bwd_kernel, dim3(slabs), dim3(64), 0, st, (const bf16*)x, (const bf16*)g, dy,
-                     (const bf16*)dres, (bf16*)out, part, T, d, kNormEps);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(slabs), dim3(256), 0, st, (const bf16*)x, (const bf16*)g, dy, (const bf16*)dres,
+                       (bf16*)out, part, T, d, kNormEps);
+  };
+  if (d <= 1024) run(rmsnorm_bwd_kernel<2>);
+  else if (d <= 2048) run(rmsnorm_bwd_kernel<4>);
+  else if (d <= 4096) run(rmsnorm_bwd_kernel<8>);
+  else run(rmsnorm_bwd_kernel<16>);
   RA_HIP(hipGetLastError());
-  hipLaunchKernelGGL(slab_sum_kernel, dim3((d + 255) / 256), dim3(256), 0, st, part, dg, slabs, d);
+  hipLaunchKernelGGL(slab_sum_kernel, dim3((d + 63) / 64), dim3(1024), 0, st, part, dg, slabs, d);
   RA_HIP(hipGetLastError());
   return RA_OK;
 }

@@ -1,0 +1,33 @@
+"""RMSNorm backward at the edges of its slabs and column chunks, against the fp64 oracle.
+
+Slabs of 32 rows shared by four waves: one row, one row short of and past a slab, several
+slabs; widths at and around the 512-column chunks where a kernel instance ends (1024, 2048,
+4096 columns) and the largest.  dx is bf16 (1e-2 of the larger of 1 and the value), dg a
+float32 sum (1e-2 of its rms)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2310_01889_amd as ra
+from oracle import llama as OL
+from tests.gpu_util import dev, log, np64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d", [(1, 8), (31, 512), (33, 520), (64, 1024), (100, 1032), (300, 2048), (5, 2056),
+                                 (97, 4096), (40, 4104), (65, 8192), (1200, 768)])
+def test_rmsnorm_bwd_slabs(T, d):
+    log("rmsnorm bwd T=%d d=%d" % (T, d))
+    gen = torch.Generator().manual_seed(T + d)
+    x = (torch.randn(T, d, generator=gen) * 3).to(torch.bfloat16)
+    g = (1 + 0.1 * torch.randn(d, generator=gen)).to(torch.bfloat16)
+    dy = torch.randn(T, d, generator=gen)
+    dres = torch.randn(T, d, generator=gen).to(torch.bfloat16)
+    dx, dg = torch.empty(T, d, dtype=torch.bfloat16, device="cuda"), torch.empty(d, device="cuda")
+    ra.rms_norm_bwd(*dev(x, g, dy, dres), dx, dg)
+    torch.cuda.synchronize()
+    dx_ref, dg_ref = OL.rmsnorm_bwd(np64(x), np64(g), dy.numpy())
+    dx_ref = dx_ref + np64(dres)
+    assert np.abs(np64(dx) - dx_ref).max() <= 1e-2 * max(1.0, np.abs(dx_ref).max())
+    assert np.abs(np64(dg) - dg_ref).max() <= 1e-2 * max(1.0, float(np.sqrt(np.mean(dg_ref ** 2))))
