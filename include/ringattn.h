@@ -44,7 +44,8 @@
  *     `stream` from a memory pool the library owns on each device, and freed back to that
  *     pool at the end of the call (stream-ordered).  The pool keeps freed memory cached for
  *     later calls until the process ends or ring_attn_release_workspace() is called; the
- *     device's default memory pool and its settings are not touched.
+ *     device's default memory pool and its settings are not touched.  Blocks of up to 64 MiB
+ *     (256 MiB a device in all) of the NULL stream are kept for its next call instead.
  *   - Return value: RA_OK or an ra_status error code.  Arguments are validated before
  *     anything is enqueued: on error nothing is enqueued and outputs are untouched.
  *     ring_attn_last_error() describes the last error on the calling thread.  NaN or

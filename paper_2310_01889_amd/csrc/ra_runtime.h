@@ -41,9 +41,26 @@ inline int check_aligned(std::initializer_list<const void*> rows16, std::initial
 // device's default pool is left as it is.
 int workspace_pool(hipMemPool_t* out);
 
+// Small workspaces of the default (null) stream are kept between calls: allocating from the
+// pool and freeing cost the host 12 us a call, as much as a short call's kernels.  A block given
+// back after a call goes to the next one: stream order keeps the two apart, and the null
+// stream of a device is never destroyed (another stream's handle can come back as a new
+// stream's, which need not be ordered after the old one's work, so other streams' workspaces
+// go to the pool and back, as does what a capture allocates, the null stream taking part in
+// none).  At most kWsKeepCount blocks a device of at most kWsKeepBlock bytes, kWsKeepTotal in
+// all, are kept; ring_attn_release_workspace() returns them.
+constexpr size_t kWsKeepBlock = (size_t)64 << 20, kWsKeepTotal = (size_t)256 << 20;
+constexpr int kWsKeepCount = 32;
+// A kept block of the device of at least `bytes` (its size in *got), or null.
+void* workspace_take(int dev, size_t bytes, size_t* got);
+// Offers a block whose last use is enqueued on the device's null stream; false: free it.
+bool workspace_give(int dev, void* p, size_t bytes);
+// The current device's kept blocks back to the pool, in the null stream's order; true if any.
+bool workspace_drop_kept();
+
 // Stream-ordered workspace and events owned by one call; released on every exit path.
 // side: the library's side stream when the call enqueued work on it.  Before the workspace
-// goes back to the pool the caller stream waits for everything enqueued on the side stream
+// goes back the caller stream waits for everything enqueued on the side stream
 // so far -- also on an error return in the middle of a call, where the call's own final
 // join was never enqueued -- so that no copy still queued there can write into memory a
 // later call has been given.
@@ -51,6 +68,8 @@ struct CallResources {
   hipStream_t stream;
   hipStream_t side = nullptr;
   void* ws = nullptr;
+  size_t ws_bytes = 0;
+  int keep_dev = -1;  // the device that may keep ws, or -1
   std::vector<hipEvent_t> events;
   explicit CallResources(hipStream_t s) : stream(s) {}
   ~CallResources() {
@@ -64,15 +83,29 @@ struct CallResources {
         (void)hipStreamSynchronize(side);
       }
     }
-    if (ws) (void)hipFreeAsync(ws, stream);
+    if (ws && !(keep_dev >= 0 && workspace_give(keep_dev, ws, ws_bytes))) (void)hipFreeAsync(ws, stream);
     for (hipEvent_t e : events) (void)hipEventDestroy(e);
   }
   int alloc(size_t bytes) {
     if (bytes == 0) return RA_OK;
+    if (stream == nullptr && bytes <= kWsKeepBlock) {
+      RA_HIP(hipGetDevice(&keep_dev));
+      if ((ws = workspace_take(keep_dev, bytes, &ws_bytes))) return RA_OK;
+      // sizes in steps of an eighth of their power of two, so that near sizes share a block
+      size_t step = (size_t)64 << 10;
+      while (step * 16 < bytes) step *= 2;
+      bytes = (bytes + step - 1) / step * step;
+    }
     hipMemPool_t pool;
     int rc = workspace_pool(&pool);
     if (rc) return rc;
-    RA_HIP(hipMallocFromPoolAsync(&ws, bytes, pool, stream));
+    hipError_t e = hipMallocFromPoolAsync(&ws, bytes, pool, stream);
+    if (e == hipErrorOutOfMemory && stream == nullptr && workspace_drop_kept()) {
+      (void)hipGetLastError();
+      e = hipMallocFromPoolAsync(&ws, bytes, pool, stream);
+    }
+    RA_HIP(e);
+    ws_bytes = bytes;
     return RA_OK;
   }
   int event(hipEvent_t* e) {

@@ -92,6 +92,73 @@ int workspace_pool(hipMemPool_t* out) {
 }
 
 // ---------------------------------------------------------------------------------
+// Kept workspaces of the null streams (see ra_runtime.h).
+// ---------------------------------------------------------------------------------
+namespace {
+struct KeptBlock {
+  void* p;
+  size_t bytes;
+  int dev;
+};
+std::mutex g_kept_mu;
+std::vector<KeptBlock> g_kept;
+}  // namespace
+
+void* workspace_take(int dev, size_t bytes, size_t* got) {
+  std::lock_guard<std::mutex> lk(g_kept_mu);
+  int best = -1;
+  for (int i = 0; i < (int)g_kept.size(); ++i) {
+    const KeptBlock& b = g_kept[i];
+    if (b.dev == dev && b.bytes >= bytes && b.bytes <= 2 * bytes + ((size_t)1 << 20) &&
+        (best < 0 || b.bytes < g_kept[best].bytes))
+      best = i;
+  }
+  if (best < 0) return nullptr;
+  void* p = g_kept[best].p;
+  *got = g_kept[best].bytes;
+  g_kept.erase(g_kept.begin() + best);
+  return p;
+}
+
+bool workspace_give(int dev, void* p, size_t bytes) {
+  std::lock_guard<std::mutex> lk(g_kept_mu);
+  int count = 0, first = -1;
+  size_t total = 0;
+  for (int i = 0; i < (int)g_kept.size(); ++i)
+    if (g_kept[i].dev == dev) {
+      if (first < 0) first = i;
+      ++count;
+      total += g_kept[i].bytes;
+    }
+  // full: the block kept longest makes room (the freed memory stays in the pool)
+  if (first >= 0 && (count >= kWsKeepCount || total + bytes > kWsKeepTotal)) {
+    (void)hipFreeAsync(g_kept[first].p, nullptr);
+    total -= g_kept[first].bytes;
+    --count;
+    g_kept.erase(g_kept.begin() + first);
+  }
+  if (count >= kWsKeepCount || total + bytes > kWsKeepTotal) return false;
+  g_kept.push_back({p, bytes, dev});
+  return true;
+}
+
+bool workspace_drop_kept() {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return false;
+  std::lock_guard<std::mutex> lk(g_kept_mu);
+  std::vector<KeptBlock> rest;
+  for (const KeptBlock& b : g_kept) {
+    if (b.dev == dev)
+      (void)hipFreeAsync(b.p, nullptr);
+    else
+      rest.push_back(b);
+  }
+  const bool any = rest.size() != g_kept.size();
+  g_kept.swap(rest);
+  return any;
+}
+
+// ---------------------------------------------------------------------------------
 // Optional per-kernel timing (benchmarks): when enabled, every step-kernel launch is
 // bracketed by timing events on the stream it is launched on.
 // ---------------------------------------------------------------------------------
@@ -650,6 +717,7 @@ int ring_attn_release_workspace(void) {
   hipMemPool_t pool;
   int rc = workspace_pool(&pool);
   if (rc) return rc;
+  (void)workspace_drop_kept();
   RA_HIP(hipMemPoolTrimTo(pool, 0));
   return RA_OK;
 }
