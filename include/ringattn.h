@@ -195,7 +195,7 @@ int ring_attn_decode(const void* q, const void* k_cache, const void* v_cache, vo
  * capture, tight serving loops, harnesses that forbid allocation.  Same arguments, same
  * kernels and the same result as ring_attn_decode, bit for bit, but no allocation of any
  * kind: the chunk partial states live in a fixed 32 MiB device array (8388608 floats) that
- * the library holds on every device it runs on until the process ends.  The call needs
+ * the library holds on every device it runs on until the process ends.  The call is held to
  * B * H * nch * Tq * (D + 2) floats of it, with nch = S / kch chunks, kch = the block
  * S / n_hosts halved while B * H * nch < 4096 and the half stays a multiple of 32 (e.g.
  * B = 1, H = 32, D = 128, S = 262144 over 8 hosts: nch = 128, Tq <= 15); larger shapes

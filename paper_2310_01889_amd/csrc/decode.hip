@@ -227,20 +227,22 @@ struct MergeArgs {
   int B, H, Tq, nch, n_hosts;
 };
 
-// One workgroup of 4 waves per (batch, head, query): combine the chunk partial states in
-// ring order -- blocks n_hosts-1, n_hosts-2, ..., 0, chunks of a block in order.  All
+// One workgroup of 8 waves per (batch, head, query): combine the chunk partial states --
+// blocks n_hosts-1, n_hosts-2, ..., 0 in ring order, chunks of a block in order.  All
 // partials are present, so instead of carrying a running maximum the sum is taken relative
 // to the overall maximum M (found first, in any order):
 //   o = sum_c acc_c 2^(m_c - M) / sum_c l_c 2^(m_c - M),  lse = (M ln 2) + ln(denominator),
 // which is the online-softmax fold of the same partials without its sequential
-// dependence.  Wave w sums the w-th quarter of the ring-ordered sequence of chunks, in
-// order; the four quarter sums are then added in order.  (A single wave walking every
-// chunk was bound by the latency of its dependent loads.)
-constexpr int kMergeWaves = 4;
+// dependence.  The weights 2^(m_c - M) go to LDS first; wave w then sums the w-th eighth of the
+// ring-ordered sequence of chunks, in order, its loads independent of one another; the eighth
+// sums are then added in order.  Bound by memory latency: 128 chunks of 64 dims took 7.6 us with
+// 4 waves that formed each weight on the way.
+constexpr int kMergeWaves = 8;
 
 template <int D>
 __global__ __launch_bounds__(64 * kMergeWaves) void decode_merge_kernel(const MergeArgs a) {
   constexpr int E = D / 64;  // dims per lane
+  extern __shared__ float s_w[];  // weight of each chunk
   __shared__ float s_max[kMergeWaves];
   __shared__ float s_part[kMergeWaves][D + 1];
   const int t = blockIdx.x % a.Tq, bh = blockIdx.x / a.Tq;
@@ -249,26 +251,38 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_merge_kernel(const Me
   const int cpb = a.nch / a.n_hosts;  // chunks per block
   const long long base = (long long)bh * a.nch;
   float mx = -INFINITY;
-  for (int c = tid; c < a.nch; c += 64 * kMergeWaves) mx = fmaxf(mx, a.part_m[(base + c) * a.Tq + t]);
+  for (int c = tid; c < a.nch; c += 64 * kMergeWaves) {
+    const float mc = a.part_m[(base + c) * a.Tq + t];
+    s_w[c] = mc;
+    mx = fmaxf(mx, mc);
+  }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
   if (lane == 0) s_max[wave] = mx;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kMergeWaves; ++w) mx = fmaxf(mx, s_max[w]);
+  float l = 0.f;
+  for (int c = tid; c < a.nch; c += 64 * kMergeWaves) {
+    const float mc = s_w[c];
+    const float w = (mc == -INFINITY) ? 0.f : exp2f(mc - mx);
+    s_w[c] = w;
+    l = fmaf(a.part_l[(base + c) * a.Tq + t], w, l);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) l += __shfl_xor(l, off);
+  __syncthreads();
   // sequence position q (0 .. nch-1) of the ring order is chunk (n_hosts-1-q/cpb)*cpb + q%cpb
   const int q0 = (int)((long long)a.nch * wave / kMergeWaves);
   const int q1 = (int)((long long)a.nch * (wave + 1) / kMergeWaves);
-  float l = 0.f, acc[E];
+  float acc[E];
 #pragma unroll
   for (int e = 0; e < E; ++e) acc[e] = 0.f;
-#pragma unroll 4
+#pragma unroll 8
   for (int q = q0; q < q1; ++q) {
     const int chunk = (a.n_hosts - 1 - q / cpb) * cpb + q % cpb;
     const long long row = (base + chunk) * a.Tq + t;
-    const float mc = a.part_m[row];
-    const float w = (mc == -INFINITY) ? 0.f : exp2f(mc - mx);
-    l = fmaf(a.part_l[row], w, l);
+    const float w = s_w[chunk];
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = fmaf(a.part_acc[row * D + lane + 64 * e], w, acc[e]);
   }
@@ -293,9 +307,24 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_merge_kernel(const Me
   if (lane == 0) a.lse[(long long)bh * a.Tq + t] = mx * kLn2 + logf(lt);
 }
 
-// Keys per chunk: the whole block, halved while the launch has fewer than 4096
-// workgroups (16 per compute unit) and the half stays a multiple of 32.
-int pick_chunk(int B, int H, int S, int c) {
+// Keys per chunk: the whole block, halved while the half stays a multiple of 32 and the launch
+// has fewer than 1024 workgroups (4 per compute unit), or fewer than 4096 of chunks of 256 KB
+// and more of keys and values.  Short chunks pay their workgroup's start, a partial state written and one more
+// term of the merge for little reading; on long caches more loads in flight pay.  us at 1024,
+// 4096 workgroups, tokens x heads: 4096 x 32 (67 MB) 17.4, 27.2; 2 x 4096 x 16 of 64 13.0, 14.3;
+// 65536 x 4 (134 MB) 29.6, 44.9; 4 x 4096 x 32 (268 MB) 44.6, 50.5; 32768 x 32 (537 MB) 100.7, 97.8.
+int pick_chunk(int B, int H, int S, int D, int c) {
+  int kch = c;
+  for (;;) {
+    const long long n = (long long)B * H * (S / kch);
+    if (kch % 64 || n >= 4096 || (n >= 1024 && (long long)kch * D * 4 < (256 << 10))) return kch;
+    kch /= 2;
+  }
+}
+
+// Chunks by which ring_attn_decode_noalloc states what fits its scratch (at least as many as
+// pick_chunk's): 4096 workgroups whatever the length.
+int scratch_chunk(int B, int H, int S, int c) {
   int kch = c;
   while (kch % 64 == 0 && (long long)B * H * (S / kch) < 4096) kch /= 2;
   return kch;
@@ -359,9 +388,9 @@ static int decode_launch(const void* q, const void* k_cache, const void* v_cache
   }));
   MergeArgs ma{da.part_acc, da.part_m, da.part_l, (bf16*)o, lse, B, H, Tq, nch, n_hosts};
   if (D == 128)
-    hipLaunchKernelGGL(decode_merge_kernel<128>, dim3(B * H * Tq), dim3(64 * kMergeWaves), 0, stream, ma);
+    hipLaunchKernelGGL(decode_merge_kernel<128>, dim3(B * H * Tq), dim3(64 * kMergeWaves), nch * 4, stream, ma);
   else
-    hipLaunchKernelGGL(decode_merge_kernel<64>, dim3(B * H * Tq), dim3(64 * kMergeWaves), 0, stream, ma);
+    hipLaunchKernelGGL(decode_merge_kernel<64>, dim3(B * H * Tq), dim3(64 * kMergeWaves), nch * 4, stream, ma);
   RA_HIP(hipGetLastError());
   return RA_OK;
 }
@@ -371,7 +400,7 @@ extern "C" int ring_attn_decode(const void* q, const void* k_cache, const void* 
   g_err.clear();
   int rc = decode_validate(q, k_cache, v_cache, o, lse, B, H, S, D, Tq, n_hosts, causal);
   if (rc) return rc;
-  const int kch = pick_chunk(B, H, S, S / n_hosts);
+  const int kch = pick_chunk(B, H, S, D, S / n_hosts);
   const long long rows = (long long)B * H * (S / kch) * Tq;
   CallResources R(stream);
   if ((rc = R.alloc((size_t)rows * (D + 2) * sizeof(float)))) return rc;
@@ -414,14 +443,15 @@ extern "C" int ring_attn_decode_noalloc(const void* q, const void* k_cache, cons
   g_err.clear();
   int rc = decode_validate(q, k_cache, v_cache, o, lse, B, H, S, D, Tq, n_hosts, causal);
   if (rc) return rc;
-  const int kch = pick_chunk(B, H, S, S / n_hosts);
-  const long long need = (long long)B * H * (S / kch) * Tq * (D + 2);
+  const int lch = scratch_chunk(B, H, S, S / n_hosts);
+  const long long need = (long long)B * H * (S / lch) * Tq * (D + 2);
   if (need > kScratchFloats)
     return set_err(RA_EUNSUPPORTED,
                    "partial state of %lld floats (B*H*(S/%d)*Tq*(D+2)) exceeds the %lld-float scratch of "
                    "ring_attn_decode_noalloc",
-                   need, kch, kScratchFloats);
+                   need, lch, kScratchFloats);
   float* part = nullptr;
   if ((rc = scratch_ptr(&part))) return rc;
-  return decode_launch(q, k_cache, v_cache, o, lse, B, H, S, D, Tq, n_hosts, causal, kch, part, stream);
+  return decode_launch(q, k_cache, v_cache, o, lse, B, H, S, D, Tq, n_hosts, causal,
+                       pick_chunk(B, H, S, D, S / n_hosts), part, stream);
 }

@@ -1,0 +1,26 @@
+"""Ring decode around the chunking rule and the merge's split of the chunks, against the fp64
+oracle: fewer chunks than the merge has waves, chunk counts that do not divide over them, one
+chunk a block, blocks of an odd number of tiles, and caches on both sides of the rule."""
+import pytest
+import torch
+
+import paper_2310_01889_amd as ra
+from oracle import decode as OD
+from paper_2310_01889_amd import synth
+from tests.gpu_util import dev, log, max_err, np64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,S,H,D,Tq,N", [(1, 32, 1, 64, 1, 1), (1, 96, 2, 128, 3, 3), (1, 288, 1, 64, 32, 1),
+                                          (2, 352, 3, 128, 2, 11), (1, 8192, 1, 128, 1, 1), (1, 8192, 2, 64, 5, 64),
+                                          (4, 2048, 300, 64, 1, 2), (1, 65536, 4, 128, 1, 4)])
+def test_decode_chunks(B, S, H, D, Tq, N):
+    log("decode chunks B=%d S=%d H=%d D=%d Tq=%d N=%d" % (B, S, H, D, Tq, N))
+    q, k, v = synth.attention_inputs(S + H, B, Tq, H, D, kv_len=S)
+    o, lse = ra.attention_decode(*dev(q, k, v), N, True)
+    torch.cuda.synchronize()
+    for h in sorted({0, H // 2, H - 1}):
+        hs = slice(h, h + 1)
+        o_ref, l_ref = OD.ring_decode_fwd(np64(q[:, :, hs]), np64(k[:, :, hs]), np64(v[:, :, hs]), N, True)
+        assert max_err(o[:, :, hs], o_ref) <= 2e-2 and max_err(lse[:, hs], l_ref) <= 2e-2
