@@ -219,13 +219,13 @@ struct KeyTile {
   const bf16 *k, *v;
 };
 
-template <class P>
+template <int D, class P>
 __device__ __forceinline__ bool key_tile(const P& p, KeyTile& t) {
   constexpr int kKB = 128, kQB = 32;
   if constexpr (std::is_same_v<P, BwdRing>) {
     const int n_kt = (p.S + kKB - 1) / kKB;
     int tile;
-    if (!ring_item(blockIdx.x, p.B * p.H, n_kt, t.bh, tile)) return false;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_kt, (long long)p.S * (D * 4), t.bh, tile)) return false;
     const int kt = n_kt - 1 - tile;  // under the causal mask the first keys have the most queries
     const int n_q = (p.S + kQB - 1) / kQB;
     t.slot = 0;
@@ -325,7 +325,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dkdv_bf16_kernel(const P p) {
   };
 
   KeyTile kt;
-  if (!key_tile(p, kt)) return;
+  if (!key_tile<D>(p, kt)) return;
   const int b = kt.bh / p.H, h = kt.bh % p.H;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);  // uniform: LDS destinations in scalar registers
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kPT) void bwd_dkdv_split_kernel(const P p) {
   using I3 = std::integral_constant<int, 3>;
 
   KeyTile kt;
-  if (!key_tile(p, kt)) return;
+  if (!key_tile<D>(p, kt)) return;
   const int b = kt.bh / p.H, h = kt.bh % p.H;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hi = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: LDS destinations in scalar registers
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const P p) {
   if constexpr (RING) {
     const int n_qt = (p.S + kQQ - 1) / kQQ;
     int qt;
-    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, bh, qt)) return;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, (long long)p.S * (D * 4), bh, qt)) return;
     q_tile_row = tile_first_q = qt * kQQ;
     host = q_tile_row / p.c;
     k_pos0 = host * p.c;

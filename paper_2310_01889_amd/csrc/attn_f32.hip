@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(const FwdRing p) {
   using T = F32Tile<D>;
   __shared__ __attribute__((aligned(1024))) char lds[2 * T::R * T::BUF];
   int bh, qt;
-  if (!ring_item(blockIdx.x, p.B * p.H, p.S / T::ROWS, bh, qt)) return;
+  if (!ring_item(blockIdx.x, p.B * p.H, p.S / T::ROWS, (long long)p.S * (D * 8), bh, qt)) return;
   const int b = bh / p.H, h = bh % p.H, q0 = qt * T::ROWS;
   const F32Wave<D> w(p.H * D);
   const long long off = (long long)b * p.bstride + h * D;
@@ -274,7 +274,7 @@ __device__ __forceinline__ void bwd_f32_dkdv(const BwdRing& p, int id, char* lds
   using T = F32Tile<D>;
   const int n_kt = p.S / T::ROWS;
   int bh, tile;
-  if (!ring_item(id, p.B * p.H, n_kt, bh, tile)) return;
+  if (!ring_item(id, p.B * p.H, n_kt, (long long)p.S * (D * 8), bh, tile)) return;
   const int b = bh / p.H, h = bh % p.H, key0 = (n_kt - 1 - tile) * T::ROWS;  // first keys have most queries
   const F32Wave<D> w(p.H * D);
   const long long off = (long long)b * p.bstride + h * D;
@@ -358,7 +358,7 @@ template <int D>
 __device__ __forceinline__ void bwd_f32_dq(const BwdRing& p, int id, char* lds) {
   using T = F32Tile<D>;
   int bh, qt;
-  if (!ring_item(id, p.B * p.H, p.S / T::ROWS, bh, qt)) return;
+  if (!ring_item(id, p.B * p.H, p.S / T::ROWS, (long long)p.S * (D * 8), bh, qt)) return;
   const int b = bh / p.H, h = bh % p.H, q0 = qt * T::ROWS;
   const F32Wave<D> w(p.H * D);
   const long long off = (long long)b * p.bstride + h * D;

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
   if constexpr (RING) {
     const int n_qt = (p.S + BM - 1) / BM;
     int qt;
-    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, bh, qt)) return;
+    if (!ring_item(blockIdx.x, p.B * p.H, n_qt, (long long)p.S * (D * 4), bh, qt)) return;
     q_tile_row = tile_first_q = qt * BM;
     host = q_tile_row / p.c;
     k_pos0 = host * p.c;
@@ -321,14 +321,17 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
   // operand reads PF steps ahead, and the vector work of pair u = s * 16 / NSTEP of tile t:
   // its exponentials at that step, its packing one step later, its row-sum term two steps
   // later.
-  auto region = [&](auto Bc, auto NXc, auto PVc, int it) __attribute__((always_inline)) {
+  auto region = [&](auto Bc, auto NXc, auto PVc, auto MCc, int it) __attribute__((always_inline)) {
     constexpr int B = decltype(Bc)::value;
-    constexpr bool NX = decltype(NXc)::value, PV = decltype(PVc)::value;
+    constexpr bool NX = decltype(NXc)::value, PV = decltype(PVc)::value, MC = decltype(MCc)::value;
     if (NX && it + 2 < nt) load_k(Bc);
     load_v(Bc);  // read by region t+1 or, after the last region, by the final products
     const bf16* kt = kbuf(std::integral_constant<int, B ^ 1>{});
     const bf16* vt = vbuf(std::integral_constant<int, B ^ 1>{});
-    if (it >= n_full && it < n_own) mask_tile(s_cur, it);
+    if constexpr (MC) mask_tile(s_cur, it);
+    if constexpr (!PV) {
+      if (it >= n_full && it < n_own) mask_tile(s_cur, it);
+    }
     bf16x8 kop[NS], vop[NP];
     uint32_t w[16];
     float pe[16][2];
@@ -385,15 +388,16 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
   };
 
   // regions [a, e) that have a successor and a predecessor, two at a time so that the
-  // buffer parity is a constant
-  auto run = [&](int a, int e) __attribute__((always_inline)) {
+  // buffer parity is a constant; MC: their tiles need the mask (a branch inside a region
+  // copies the scores' registers on every tile: 1 % at 4096 tokens and up)
+  auto run = [&](auto MCc, int a, int e) __attribute__((always_inline)) {
     int it = a;
-    if ((it & 1) && it < e) region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, it++);
+    if ((it & 1) && it < e) region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, MCc, it++);
     for (; it + 1 < e; it += 2) {
-      region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, it);
-      region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, it + 1);
+      region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, MCc, it);
+      region(std::integral_constant<int, 1>{}, std::true_type{}, std::true_type{}, MCc, it + 1);
     }
-    if (it < e) region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, it);
+    if (it < e) region(std::integral_constant<int, 0>{}, std::true_type{}, std::true_type{}, MCc, it);
   };
   // the last region (no successor): one instance for any parity, mask and predecessor,
   // its two buffers chosen at run time (the compiler then waits for the in-flight load of
@@ -438,8 +442,11 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void fwd_bf16_kernel(
     if (nt > 2) __syncthreads();
     if (nt > 1) {
       // region 0: no predecessor
-      region(std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{}, 0);
-      run(1, nt - 1);
+      region(std::integral_constant<int, 0>{}, std::true_type{}, std::false_type{}, std::false_type{}, 0);
+      const int m0 = max(1, min(nt - 1, n_full)), m1 = max(m0, min(nt - 1, n_own));  // masked: [m0, m1)
+      run(std::false_type{}, 1, m0);
+      run(std::true_type{}, m0, m1);
+      if constexpr (RING) run(std::false_type{}, m1, nt - 1);
     }
     last(nt - 1);
     // O^T += V^T P^T of the last tile, from V(nt-1) in buffer (nt-1) % 2
