@@ -24,3 +24,15 @@ def test_decode_chunks(B, S, H, D, Tq, N):
         hs = slice(h, h + 1)
         o_ref, l_ref = OD.ring_decode_fwd(np64(q[:, :, hs]), np64(k[:, :, hs]), np64(v[:, :, hs]), N, True)
         assert max_err(o[:, :, hs], o_ref) <= 2e-2 and max_err(lse[:, hs], l_ref) <= 2e-2
+
+
+@pytest.mark.parametrize("B,S,H,D,Tq,N", [(2, 4096, 4, 64, 4, 4), (1, 2688, 2, 128, 8, 1)])
+def test_decode_probabilities_carry_two_bf16_parts(B, S, H, D, Tq, N):
+    # each probability is off by at most 2^-17 of itself (7.7e-6 in lse), the float32 sums and
+    # lse's own rounding (values near 9) add a few 1e-6: rounded to bf16 once, probabilities put
+    # errors of 1e-4 on lse
+    log("decode lse precision B=%d S=%d H=%d D=%d Tq=%d N=%d" % (B, S, H, D, Tq, N))
+    q, k, v = synth.attention_inputs(S + D, B, Tq, H, D, kv_len=S)
+    _, lse = ra.attention_decode(*dev(q, k, v), N, True)
+    _, l_ref = OD.ring_decode_fwd(np64(q), np64(k), np64(v), N, True)
+    assert max_err(lse, l_ref) <= 2e-5
