@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -138,7 +139,11 @@ bool workspace_give(int dev, void* p, size_t bytes) {
     g_kept.erase(g_kept.begin() + first);
   }
   if (count >= kWsKeepCount || total + bytes > kWsKeepTotal) return false;
-  g_kept.push_back({p, bytes, dev});
+  try {
+    g_kept.push_back({p, bytes, dev});
+  } catch (const std::bad_alloc&) {  // called from a destructor: nothing may escape
+    return false;
+  }
   return true;
 }
 
@@ -146,15 +151,13 @@ bool workspace_drop_kept() {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return false;
   std::lock_guard<std::mutex> lk(g_kept_mu);
-  std::vector<KeptBlock> rest;
-  for (const KeptBlock& b : g_kept) {
-    if (b.dev == dev)
-      (void)hipFreeAsync(b.p, nullptr);
-    else
-      rest.push_back(b);
-  }
-  const bool any = rest.size() != g_kept.size();
-  g_kept.swap(rest);
+  bool any = false;
+  for (int i = (int)g_kept.size() - 1; i >= 0; --i)
+    if (g_kept[i].dev == dev) {
+      (void)hipFreeAsync(g_kept[i].p, nullptr);
+      g_kept.erase(g_kept.begin() + i);
+      any = true;
+    }
   return any;
 }
 
