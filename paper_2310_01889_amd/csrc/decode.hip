@@ -45,7 +45,7 @@ struct DecodeArgs {
 // the transpose read.  Tiles are double buffered: direct-to-LDS loads of tile it+1 are
 // in flight while tile it is processed.  Lanes of slots >= Tq compute on zero queries
 // and store nothing.
-template <int D>
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(64) void decode_partial_kernel(const DecodeArgs a) {
   constexpr int NKK = D / 16, NDT = D / 32, CPR = D / 8;
   constexpr int ROWS_PER_LOAD = 64 / CPR;        // rows filled by one 1 KB wave load
@@ -173,12 +173,14 @@ __global__ __launch_bounds__(64) void decode_partial_kernel(const DecodeArgs a) 
 #pragma unroll
       for (int i = 0; i < 16; ++i) minit[i] = -m_eff * isl2;
     }
-    // P and O^T += V^T P^T, one 16-key group at a time.  P is the sum of two bf16 numbers, its
-    // rounding and the rounding of what that leaves, each with a product of its own: a longer
-    // chunk has fewer probabilities that are exactly 1 (its running maxima), so with P rounded
-    // once o and lse were further from float64 than in chunks of one tile (2 x 4096 x 16 of 64,
-    // relative: o 2.2e-3 against 2.0e-3).  Now o 1.7e-3, its bf16 storage, and lse below 1e-7; the
-    // matrix cores idle here, so the time stays: 13.8, 14.0 us; 262144 x 32 760, 760.
+    // P (bf16) and O^T += V^T P^T, one 16-key group at a time.  SPLIT: P is the sum of two bf16
+    // numbers, its rounding and the rounding of what that leaves, each with a product of its own.
+    // A longer chunk has fewer probabilities that are exactly 1 (its running maxima), so with P
+    // rounded once o and lse were further from float64 than in the chunks of 4096 workgroups
+    // (2 x 4096 x 16 of 64, relative: o 2.2e-3 against 2.0e-3).  Split, o 1.7e-3, its bf16
+    // storage, and lse below 1e-7, in 14.0 us for 13.8.  Chunks that are no longer than those
+    // keep the single product: where the blocks' odd lengths leave few workgroups the wave's own
+    // chain of work bounds the call (323 us, split 374).
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       u32x4 w, wl;
@@ -186,17 +188,21 @@ __global__ __launch_bounds__(64) void decode_partial_kernel(const DecodeArgs a) 
       for (int j = 0; j < 4; ++j) {
         const float p0 = fast_exp2(s[8 * kb + 2 * j]), p1 = fast_exp2(s[8 * kb + 2 * j + 1]);
         w[j] = pack_bf16x2(p0, p1);
-        wl[j] = pack_bf16x2(p0 - __builtin_bit_cast(float, w[j] << 16),
-                            p1 - __builtin_bit_cast(float, w[j] & 0xffff0000u));
-        l_run = dot2_bf16_ones(wl[j], dot2_bf16_ones(w[j], l_run));
+        l_run = dot2_bf16_ones(w[j], l_run);
+        if constexpr (SPLIT) {
+          wl[j] = pack_bf16x2(p0 - __builtin_bit_cast(float, w[j] << 16),
+                              p1 - __builtin_bit_cast(float, w[j] & 0xffff0000u));
+          l_run = dot2_bf16_ones(wl[j], l_run);
+        }
       }
-      const bf16x8 pb = __builtin_bit_cast(bf16x8, w), pl = __builtin_bit_cast(bf16x8, wl);
+      const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
       for (int dt = 0; dt < NDT; ++dt) {
         const bf16x4 lo = lds_read_tr16(vt + 16 * kb * D + voff[0][dt]);
         const bf16x4 up = lds_read_tr16(vt + 16 * kb * D + voff[1][dt]);
         const bf16x8 vv{lo[0], lo[1], lo[2], lo[3], up[0], up[1], up[2], up[3]};
-        oacc[dt] = mfma32(vv, pl, mfma32(vv, pb, oacc[dt]));
+        oacc[dt] = mfma32(vv, pb, oacc[dt]);
+        if constexpr (SPLIT) oacc[dt] = mfma32(vv, __builtin_bit_cast(bf16x8, wl), oacc[dt]);
       }
     }
   };
@@ -388,11 +394,12 @@ static int decode_launch(const void* q, const void* k_cache, const void* v_cache
   da.causal = causal;
   da.scale = 1.f / sqrtf((float)D);
   const int grid = B * H * nch;
+  // longer chunks than 4096 workgroups would have: split probabilities (see the kernel)
+  const bool split = da.kch > scratch_chunk(B, H, S, S / n_hosts);
+  auto* kern = D == 128 ? (split ? decode_partial_kernel<128, true> : decode_partial_kernel<128, false>)
+                        : (split ? decode_partial_kernel<64, true> : decode_partial_kernel<64, false>);
   RA_HIP(timed_launch(RA_KERNEL_DECODE, stream, [&] {
-    if (D == 128)
-      hipLaunchKernelGGL(decode_partial_kernel<128>, dim3(grid), dim3(64), 0, stream, da);
-    else
-      hipLaunchKernelGGL(decode_partial_kernel<64>, dim3(grid), dim3(64), 0, stream, da);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(64), 0, stream, da);
     return hipGetLastError();
   }));
   MergeArgs ma{da.part_acc, da.part_m, da.part_l, (bf16*)o, lse, B, H, Tq, nch, n_hosts};

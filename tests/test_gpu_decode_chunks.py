@@ -26,7 +26,7 @@ def test_decode_chunks(B, S, H, D, Tq, N):
         assert max_err(o[:, :, hs], o_ref) <= 2e-2 and max_err(lse[:, hs], l_ref) <= 2e-2
 
 
-@pytest.mark.parametrize("B,S,H,D,Tq,N", [(2, 4096, 4, 64, 4, 4), (1, 2688, 2, 128, 8, 1)])
+@pytest.mark.parametrize("B,S,H,D,Tq,N", [(2, 4096, 16, 64, 4, 4), (4, 2048, 16, 128, 8, 1)])
 def test_decode_probabilities_carry_two_bf16_parts(B, S, H, D, Tq, N):
     # each probability is off by at most 2^-17 of itself (7.7e-6 in lse), the float32 sums and
     # lse's own rounding (values near 9) add a few 1e-6: rounded to bf16 once, probabilities put
