@@ -218,13 +218,14 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(const FwdRing p) {
         if (p.causal && k0 == qw0 && 8 * (i / 4) + 4 * w.hi + i % 4 > w.l32) s[i] = -INFINITY;
         mx = fmaxf(mx, s[i]);
       }
-      const float m_new = fmaxf(m, pair_max(mx));
-      const float alpha = expf(m - m_new);
+      // a maximum of -inf (so far only scores of -inf, which weigh 0) would make inf - inf of them
+      const float m_new = fmaxf(m, pair_max(mx)), m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = expf(m - m_use);
       m = m_new;
       l *= alpha;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        s[i] = expf(s[i] - m_new);
+        s[i] = expf(s[i] - m_use);
         l += s[i];
       }
 #pragma unroll
@@ -250,7 +251,8 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(const FwdRing p) {
   float mt = m;
 #pragma unroll
   for (int j = 0; j < T::R - 1; ++j) mt = fmaxf(mt, slots[(j * T::G + w.g) * (SLOT + 64) + D * 32 + w.lane]);
-  const float a0 = expf(m - mt);
+  const float mt_use = mt == -INFINITY ? 0.f : mt;
+  const float a0 = expf(m - mt_use);
   l *= a0;
 #pragma unroll
   for (int dt = 0; dt < T::NDT; ++dt)
@@ -259,7 +261,7 @@ __global__ __launch_bounds__(256) void fwd_f32_kernel(const FwdRing p) {
 #pragma unroll
   for (int j = 0; j < T::R - 1; ++j) {
     const float* s = slots + (j * T::G + w.g) * (SLOT + 64);
-    const float aj = expf(s[D * 32 + w.lane] - mt);
+    const float aj = expf(s[D * 32 + w.lane] - mt_use);
     l = fmaf(s[D * 32 + 64 + w.lane], aj, l);
     w.add(s, acc, aj);
   }
