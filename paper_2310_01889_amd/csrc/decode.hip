@@ -37,6 +37,14 @@ struct DecodeArgs {
   float scale;
 };
 
+// The bf16 numbers next below two non-negative floats (of zero: zero), a in the low half.  What
+// they leave of a number above zero is then above zero as well.
+__device__ __forceinline__ uint32_t bf16x2_below(float a, float b) {
+  const uint32_t x = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, a), 1u);
+  const uint32_t y = __builtin_elementwise_sub_sat(__builtin_bit_cast(uint32_t, b), 1u);
+  return __builtin_amdgcn_perm(y, x, 0x07060302u);
+}
+
 // One wave: the partial state of all Tq queries (lane l % 32 = query slot) over the kch
 // keys of one chunk.  The arithmetic per 32-key tile is that of the forward step kernel:
 // S^T = K Q^T on the matrix cores (K rows from LDS with bits 2 and 3 of the row index
@@ -174,7 +182,9 @@ __global__ __launch_bounds__(64) void decode_partial_kernel(const DecodeArgs a) 
       for (int i = 0; i < 16; ++i) minit[i] = -m_eff * isl2;
     }
     // P (bf16) and O^T += V^T P^T, one 16-key group at a time.  SPLIT: P is the sum of two bf16
-    // numbers, its rounding and the rounding of what that leaves, each with a product of its own.
+    // numbers, the one next below it and the rounding of what that leaves, each with a product of
+    // its own.  Both are above zero where P is: an infinite value has an infinite sum (a part that
+    // is zero or negative would make NaN of it).  The denominator sums P itself.
     // A longer chunk has fewer probabilities that are exactly 1 (its running maxima), so with P
     // rounded once o and lse were further from float64 than in the chunks of 4096 workgroups
     // (2 x 4096 x 16 of 64, relative: o 2.2e-3 against 2.0e-3).  Split, o 1.7e-3, its bf16
@@ -187,13 +197,14 @@ __global__ __launch_bounds__(64) void decode_partial_kernel(const DecodeArgs a) 
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float p0 = fast_exp2(s[8 * kb + 2 * j]), p1 = fast_exp2(s[8 * kb + 2 * j + 1]);
-        w[j] = pack_bf16x2(p0, p1);
-        l_run = dot2_bf16_ones(w[j], l_run);
         if constexpr (SPLIT) {
+          w[j] = bf16x2_below(p0, p1);
           wl[j] = pack_bf16x2(p0 - __builtin_bit_cast(float, w[j] << 16),
                               p1 - __builtin_bit_cast(float, w[j] & 0xffff0000u));
-          l_run = dot2_bf16_ones(wl[j], l_run);
+        } else {
+          w[j] = pack_bf16x2(p0, p1);
         }
+        l_run = SPLIT ? l_run + (p0 + p1) : dot2_bf16_ones(w[j], l_run);
       }
       const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
