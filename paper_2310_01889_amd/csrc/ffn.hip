@@ -66,9 +66,11 @@ int dgrad(const void* dy, const void* w, void* dx, int T, int din, int dout, hip
   return gemm(gemm_args(dy, dout, w, dout, dx, din, T, din, dout), false, true, EPI_BF16, st);
 }
 
-int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, hipStream_t st) {
+int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, int block,
+          hipStream_t st) {
   GemmArgs g = gemm_args(x, din, dy[0], dout, dw[0], dout, din, dout, T);
   g.nb = n;
+  g.kseg = block;
   for (int i = 0; i < n; ++i) {
     g.A[i] = x;
     g.B[i] = dy[i];
@@ -86,6 +88,7 @@ int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void*
     g.B[i] = w[i];
   }
   g.residual = residual;
+  if (dx32) g.kseg = dout;
   return gemm(g, false, true, dx32 ? EPI_F32 : EPI_BF16, st);
 }
 
@@ -158,11 +161,13 @@ int ffn_backward(const void* x, const void* w1, const void* b1, const void* w2, 
     // dW2 (+)= A^T dy
     GemmArgs gw2 = gemm_args(a, d_ff, dyb, d_model, dw2, d_model, d_ff, d_model, m);
     gw2.accumulate = r0 > 0;
+    gw2.kseg = block;
     if ((rc = gemm(gw2, true, false, EPI_F32, stream))) return rc;
     if (db2) RA_HIP(launch_colsum_bf16(dyb, parts, db2, m, d_model, r0 > 0, stream));
     // dW1 (+)= x^T dH
     GemmArgs gw1 = gemm_args(xb, d_model, dh, d_ff, dw1, d_ff, d_model, d_ff, m);
     gw1.accumulate = r0 > 0;
+    gw1.kseg = block;
     if ((rc = gemm(gw1, true, false, EPI_F32, stream))) return rc;
     if (db1) RA_HIP(launch_colsum_bf16(dh, parts, db1, m, d_ff, r0 > 0, stream));
     // dx = dH W1^T
@@ -220,7 +225,7 @@ int blockwise_linear_bwd(const void* x, const void* w, const void* dy, void* dx,
   int rc = check_gemm_dims(T, d_in, d_out, block);
   if (rc) return rc;
   if (dx && (rc = dgrad(dy, w, dx, T, d_in, d_out, stream))) return rc;
-  return wgrad(x, &dy, &dw, 1, T, d_in, d_out, stream);
+  return wgrad(x, &dy, &dw, 1, T, d_in, d_out, block, stream);
 }
 
 }  // extern "C"

@@ -108,7 +108,7 @@ int ring_layer_bwd(const void* x, const void* wq, const void* wk, const void* wv
     return rc;
   // Y = X + A Wo:  dWo = A^T dY,  dA = dY Wo^T
   const void* const dY = dy;
-  if ((rc = wgrad(a.o, &dY, &dwo, 1, S, dm, dm, stream))) return rc;
+  if ((rc = wgrad(a.o, &dY, &dwo, 1, S, dm, dm, c, stream))) return rc;
   if ((rc = dgrad(dy, wo, dO, S, dm, dm, stream))) return rc;
   // ring attention backward
   if ((rc = ring_attn_bwd(a.q, a.k, a.v, a.o, a.lse, dO, dq, dk, dv, 1, H, S, dm / H, n_hosts, causal, stream)))
@@ -117,7 +117,7 @@ int ring_layer_bwd(const void* x, const void* wq, const void* wk, const void* wv
   const void* const dqkv[3] = {dq, dk, dv};
   const void* const w[3] = {wq, wk, wv};
   float* const dw[3] = {dwq, dwk, dwv};
-  if ((rc = wgrad(x, dqkv, dw, 3, S, dm, dm, stream))) return rc;
+  if ((rc = wgrad(x, dqkv, dw, 3, S, dm, dm, c, stream))) return rc;
   return dgrad3(dqkv, w, nullptr, dy, dx, S, dm, dm, stream);
 }
 

@@ -336,6 +336,7 @@ static int swiglu_backward(const void* x, const void* w1, const void* w3, const 
     // dW2 (+)= gte^T dy
     GemmArgs g2 = gemm_args(gte, dff, dyb, dm, dw2, dm, dff, dm, m);
     g2.accumulate = r0 > 0;
+    g2.kseg = block;
     if ((rc = gemm(g2, true, false, EPI_F32, st))) return rc;
     // dgte = dy W2^T  ->  du = dgte w silu'(u),  dw = dgte silu(u)
     GemmArgs gg = gemm_args(dyb, dm, w2, dm, du, dff, m, dff, dm);
@@ -350,12 +351,14 @@ static int swiglu_backward(const void* x, const void* w1, const void* w3, const 
     g1.B[1] = dw;
     g1.C[1] = dw3;
     g1.accumulate = r0 > 0;
+    g1.kseg = block;
     if ((rc = gemm(g1, true, false, EPI_F32, st))) return rc;
     // dx = du W1^T + dw W3^T
     GemmArgs gx = gemm_args(du, dff, w1, dff, dx32 ? (void*)(dx32 + off) : (char*)dx16 + off * 2, dm, m, dm, dff);
     gx.ns = 2;
     gx.A[1] = dw;
     gx.B[1] = w3;
+    if (dx32) gx.kseg = dff;
     if ((rc = gemm(gx, false, true, dx32 ? EPI_F32 : EPI_BF16, st))) return rc;
   }
   return RA_OK;
@@ -442,7 +445,7 @@ static int llama_backward(const void* x, const void* const* p, const void* dz, v
   if ((rc = norm_bwd(a.h, g2, dn32, dz, dh, dg2, part, S, dm, st))) return rc;
   // h = x + o Wo:  dWo = o^T dh,  dO = dh Wo^T
   const void* const dH = dh;
-  if ((rc = wgrad(a.o, &dH, &dwo, 1, S, dm, dm, st))) return rc;
+  if ((rc = wgrad(a.o, &dH, &dwo, 1, S, dm, dm, c, st))) return rc;
   if ((rc = dgrad(dh, wo, dO, S, dm, dm, st))) return rc;
   if ((rc = ring_attn_bwd(a.q, a.k, a.v, a.o, a.lse, dO, dq, dk, dv, 1, H, S, D, N, causal, st))) return rc;
   // undo the rotation on the gradients of the rotated q and k (its transpose)
@@ -451,7 +454,7 @@ static int llama_backward(const void* x, const void* const* p, const void* dz, v
   const void* const dqkv[3] = {dq, dk, dv};
   const void* const w[3] = {wq, wk, wv};
   float* const dw[3] = {dwq, dwk, dwv};
-  if ((rc = wgrad(a.n1, dqkv, dw, 3, S, dm, dm, st))) return rc;
+  if ((rc = wgrad(a.n1, dqkv, dw, 3, S, dm, dm, c, st))) return rc;
   if ((rc = dgrad3(dqkv, w, dn32, nullptr, nullptr, S, dm, dm, st))) return rc;
   // dx = dh + RMSNorm'(x)^T dn1
   return norm_bwd(x, g1, dn32, dh, dx, dg1, part, S, dm, st);

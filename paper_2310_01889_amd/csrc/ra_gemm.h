@@ -30,9 +30,11 @@ struct GemmArgs {
   long long lda, ldb, ldc;
   int M, N, K, act, accumulate;
   int nb = 1, ns = 1;
+  int kseg = 0;           // EPI_F32: terms of K (of all pairs in turn) summed by themselves; 0: all
 };
 
-// ta: A stored as [K][M]; tb: B stored as [N][K].  M % 256, N % 256, K % 32 must be 0.
+// ta: A stored as [K][M]; tb: B stored as [N][K].  M % 256, N % 256, K % 32, kseg % 256 and
+// K ns % kseg must be 0, K at least 256.
 hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st);
 
 // out[n] (+)= sum_m x[m][n] for bf16 x [M][N]; part: colsum_workspace_floats(N) floats.

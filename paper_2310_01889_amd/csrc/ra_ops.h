@@ -19,11 +19,13 @@ GemmArgs gemm_args(const void* A, long long lda, const void* B, long long ldb, v
 // Row-wise products of bf16 operands (x [T, din], dy and y [T, dout], w [din, dout]).  They have
 // no intermediate, so all row blocks go in one launch:
 //   proj:  y (bf16) = x w (+ residual)       dgrad: dx (bf16) = dy w^T
-//   wgrad: dw (f32, overwritten) = x^T dy    (n of them with one x: n <= 3)
+//   wgrad: dw (f32, overwritten) = x^T dy, the sums of blocks of `block` rows added up (n of
+//          them with one x: n <= 3)
 int proj(const void* x, const void* w, const void* residual, void* y, int T, int din, int dout, hipStream_t st);
 int proj3(const void* x, const void* const* w, void* const* y, int T, int din, int dout, hipStream_t st);
 int dgrad(const void* dy, const void* w, void* dx, int T, int din, int dout, hipStream_t st);
-int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, hipStream_t st);
+int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, int block,
+          hipStream_t st);
 // The input gradient of three projections of one input: dq wq^T + dk wk^T + dv wv^T as one
 // product, either float32 (dx32) or bf16 with a residual added before the one rounding (dx).
 int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void* residual, void* dx, int T, int din,

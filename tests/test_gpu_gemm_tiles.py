@@ -1,11 +1,11 @@
-"""Products on both sides of the tile-size rule, and row groups of unequal size.
+"""Products on both sides of the tile-size rule, weight gradients block by block, and row groups.
 
 The GEMM takes 128 x 128 tiles where 256 x 256 ones would leave the chip part empty; the
 smallest shapes, and shapes with just under and just over one round of big tiles, are
 compared with float32 products of the same bf16 values (errors: bf16 output 2^-9 relative,
-float32 sums of K terms).  The feed-forward networks work on as many whole blocks at a time as
-their workspace limit holds: a length of five blocks, cut 3 + 2, against the two calls it is
-cut into.
+float32 sums of K terms).  A weight gradient is the sum of its blocks' own, added up in order:
+the same, bit for bit, as calls on one block each.  The feed-forward networks work on several
+whole blocks at a time: a length of five blocks, cut into groups, against the same calls.
 """
 import pytest
 import torch
@@ -25,7 +25,7 @@ def _rand(seed, *shape, std=1.0):
 
 def _close(got, ref, tol):
     # relative to the row of sums' own scale: entries of a random product are near its rms
-    err = (got.float() - ref).abs().max().item() / ref.pow(2).mean().sqrt().item()
+    err = (got.to(ref.dtype) - ref).abs().max().item() / ref.pow(2).mean().sqrt().item()
     assert err <= tol, err
 
 
@@ -42,15 +42,30 @@ def test_linear_tiles(T, di, do):
     # one bf16 rounding of values up to ~5 rms: half an ulp 2^-9 * 8 = 1.6e-2 rms
     _close(y, x.float() @ w.float() + res.float(), 2e-2)
     _close(dx, dy.float() @ w.float().t(), 2e-2)
-    # float32 output, sums of T terms in another order: T * 2^-24 times a few rms
-    _close(dw, x.float().t() @ dy.float(), 1e-3)
+    # float32 sums: T / 16 products and T / 256 blocks each round a partial sum of up to ~5 rms by
+    # at most 2^-24 of it, which adds up as a random walk: sqrt(289) * 5 * 6e-8 = 5e-6 rms
+    _close(dw.double(), x.double().t().contiguous() @ dy.double(), 1e-5)
+
+
+# big and small tiles, one to 18 blocks of 8 to 64 steps, several products of one input
+@pytest.mark.parametrize("T,di,do,blk", [(512, 256, 256, 512), (1024, 256, 512, 512), (4608, 256, 256, 256),
+                                         (3840, 1280, 512, 768), (6144, 4096, 4096, 2048), (1280, 4096, 4096, 256)])
+def test_weight_gradient_adds_up_blocks(T, di, do, blk):
+    log("wgrad T=%d d_in=%d d_out=%d block=%d" % (T, di, do, blk))
+    x, w, dy = _rand(1, T, di), _rand(2, di, do, std=0.02), _rand(4, T, do)
+    dw, one, ref = (torch.empty(di, do, device="cuda") for _ in range(3))
+    ra.blockwise_linear_bwd(x, w, dy, None, dw, blk)
+    for r in range(0, T, blk):
+        ra.blockwise_linear_bwd(x[r:r + blk], w, dy[r:r + blk], None, one, blk)
+        ref = one.clone() if r == 0 else ref + one
+    assert torch.equal(dw, ref)
 
 
 @pytest.mark.parametrize("glu", [False, True])
 def test_row_groups_of_unequal_size(glu):
     blk, dm = 8192, 256
-    dff = 8192 if glu else 16384  # five blocks are cut 3 + 2 in the backward of both
-    T, cut = 5 * blk, 3 * blk
+    dff = 8192 if glu else 16384  # two groups or more in the backward of both
+    T = 5 * blk
     x, dy = _rand(5, T, dm), _rand(6, T, dm)
     w1, w3, w2 = _rand(7, dm, dff, std=0.02), _rand(8, dm, dff, std=0.02), _rand(9, dff, dm, std=0.02)
 
@@ -69,8 +84,10 @@ def test_row_groups_of_unequal_size(glu):
         return y, dx, dws
 
     y, dx, dws = call(0, T)
-    ya, dxa, dwa = call(0, cut)
-    yb, dxb, dwb = call(cut, T)
-    assert torch.equal(y, torch.cat([ya, yb])) and torch.equal(dx, torch.cat([dxa, dxb]))
-    for d, a, b in zip(dws, dwa, dwb):
-        assert torch.equal(d, a + b)  # the second group's sums are added to the first's
+    ys, dxs, sums = zip(*(call(r, r + blk) for r in range(0, T, blk)))
+    assert torch.equal(y, torch.cat(ys)) and torch.equal(dx, torch.cat(dxs))
+    for i, d in enumerate(dws):
+        ref = sums[0][i]
+        for s in sums[1:]:
+            ref = ref + s[i]
+        assert torch.equal(d, ref)
