@@ -466,7 +466,9 @@ __global__ __launch_bounds__(T == 256 ? 512 : 256, T == 256 ? 1 : 2) void gemm_k
 
 // Column sums of a bf16 [M, N] matrix (N a multiple of 8), deterministic two-pass reduction:
 // pass 1 writes partial sums of row slabs, a thread taking 8 columns (16-byte loads) of every
-// fourth row of its slab; pass 2 adds the slabs into out (+= or =).  HBM-bound.
+// fourth row of its slab, in turn into four sums; pass 2 adds the slabs, in eight sums, into out
+// (+= or =).  HBM-bound.  Short chains of sums keep the error near one rounding (16384 rows of
+// N(0, 1), relative: 5.5e-8, in one chain a thread 1.1e-7).
 constexpr int kCS = 64;  // row slabs
 __global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16* x, float* part, int M, int N) {
   __shared__ float red[4][64][9];
@@ -475,15 +477,22 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16* x, floa
   const int slab = blockIdx.y;
   const int rows = (M + kCS - 1) / kCS;
   const int r0 = slab * rows, r1 = min(M, r0 + rows);
-  float s[8] = {};
+  float s[4][8] = {};
   if (n < N)
-    for (int r = r0 + wave; r < r1; r += 4) {
-      const bf16x8 v = *(const bf16x8*)(x + (long long)r * N + n);
+    for (int r = r0 + wave; r < r1; r += 16) {
+      bf16x8 v[4];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s[e] += (float)v[e];
+      for (int j = 0; j < 4; ++j)  // past the slab: its last row, not added
+        v[j] = *(const bf16x8*)(x + (long long)min(r + 4 * j, r1 - 1) * N + n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (j == 0 || r + 4 * j < r1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[j][e] += (float)v[j][e];
+        }
     }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[wave][lane][e] = s[e];
+  for (int e = 0; e < 8; ++e) red[wave][lane][e] = (s[0][e] + s[1][e]) + (s[2][e] + s[3][e]);
   __syncthreads();
   for (int i = threadIdx.x; i < 512; i += 256) {
     const int l = i >> 3, e = i & 7, c = blockIdx.x * 512 + i;
@@ -493,9 +502,14 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const bf16* x, floa
 __global__ __launch_bounds__(256) void colsum_final_kernel(const float* part, float* out, int N, int accumulate) {
   const int n = blockIdx.x * 256 + threadIdx.x;
   if (n >= N) return;
-  float s = 0.f;
-#pragma unroll 8
-  for (int sl = 0; sl < kCS; ++sl) s += part[(long long)sl * N + n];
+  float p[8] = {};
+  float v[kCS];
+#pragma unroll
+  for (int sl = 0; sl < kCS; ++sl) v[sl] = part[(long long)sl * N + n];
+  __builtin_amdgcn_sched_barrier(0);  // all loads in flight at once: few waves, one memory latency
+#pragma unroll
+  for (int sl = 0; sl < kCS; ++sl) p[sl % 8] += v[sl];
+  const float s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
   out[n] = accumulate ? out[n] + s : s;
 }
 
