@@ -79,17 +79,25 @@ int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, 
   return gemm(g, true, false, EPI_F32, st);
 }
 
-int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void* residual, void* dx, int T, int din,
-           int dout, hipStream_t st) {
+int dgrad_pairs(const void* const* dy, const void* const* w, int n, float* dx32, const void* residual, void* dx, int T,
+                int din, int dout, hipStream_t st) {
   GemmArgs g = gemm_args(dy[0], dout, w[0], dout, dx32 ? (void*)dx32 : dx, din, T, din, dout);
-  g.ns = 3;
-  for (int i = 0; i < 3; ++i) {
-    g.A[i] = dy[i];
-    g.B[i] = w[i];
+  if (!dx32) {
+    g.ns = n;
+    for (int i = 0; i < n; ++i) {
+      g.A[i] = dy[i];
+      g.B[i] = w[i];
+    }
+    g.residual = residual;
+    return gemm(g, false, true, EPI_BF16, st);
   }
-  g.residual = residual;
-  if (dx32) g.kseg = dout;
-  return gemm(g, false, true, dx32 ? EPI_F32 : EPI_BF16, st);
+  for (int i = 0; i < n; ++i) {
+    g.A[0] = dy[i];
+    g.B[0] = w[i];
+    g.accumulate = i > 0;
+    if (int rc = gemm(g, false, true, EPI_F32, st)) return rc;
+  }
+  return RA_OK;
 }
 
 int alloc_row_groups(CallResources& R, int T, int block, size_t row_bytes, size_t fixed, int* rows) {

@@ -118,7 +118,7 @@ int ring_layer_bwd(const void* x, const void* wq, const void* wk, const void* wv
   const void* const w[3] = {wq, wk, wv};
   float* const dw[3] = {dwq, dwk, dwv};
   if ((rc = wgrad(x, dqkv, dw, 3, S, dm, dm, c, stream))) return rc;
-  return dgrad3(dqkv, w, nullptr, dy, dx, S, dm, dm, stream);
+  return dgrad_pairs(dqkv, w, 3, nullptr, dy, dx, S, dm, dm, stream);
 }
 
 }  // extern "C"

@@ -354,12 +354,11 @@ static int swiglu_backward(const void* x, const void* w1, const void* w3, const 
     g1.kseg = block;
     if ((rc = gemm(g1, true, false, EPI_F32, st))) return rc;
     // dx = du W1^T + dw W3^T
-    GemmArgs gx = gemm_args(du, dff, w1, dff, dx32 ? (void*)(dx32 + off) : (char*)dx16 + off * 2, dm, m, dm, dff);
-    gx.ns = 2;
-    gx.A[1] = dw;
-    gx.B[1] = w3;
-    if (dx32) gx.kseg = dff;
-    if ((rc = gemm(gx, false, true, dx32 ? EPI_F32 : EPI_BF16, st))) return rc;
+    const void* const duw[2] = {du, dw};
+    const void* const w13[2] = {w1, w3};
+    if ((rc = dgrad_pairs(duw, w13, 2, dx32 ? dx32 + off : nullptr, nullptr, dx16 ? (char*)dx16 + off * 2 : nullptr, m,
+                          dm, dff, st)))
+      return rc;
   }
   return RA_OK;
 }
@@ -455,7 +454,7 @@ static int llama_backward(const void* x, const void* const* p, const void* dz, v
   const void* const w[3] = {wq, wk, wv};
   float* const dw[3] = {dwq, dwk, dwv};
   if ((rc = wgrad(a.n1, dqkv, dw, 3, S, dm, dm, c, st))) return rc;
-  if ((rc = dgrad3(dqkv, w, dn32, nullptr, nullptr, S, dm, dm, st))) return rc;
+  if ((rc = dgrad_pairs(dqkv, w, 3, dn32, nullptr, nullptr, S, dm, dm, st))) return rc;
   // dx = dh + RMSNorm'(x)^T dn1
   return norm_bwd(x, g1, dn32, dh, dx, dg1, part, S, dm, st);
 }

@@ -13,7 +13,8 @@ enum GemmEpilogue {
   EPI_ACT_GRAD_BF16 = 3,  // C = acc * act'(aux_f32[m][n]), stored bf16
   EPI_F32 = 4,            // C = acc (or C += acc if accumulate), float32
   EPI_GLU_BF16 = 5,       // with u = A B[0], w = A B[1]: C = silu(u) * w, bf16; aux_f32 = u, aux2_f32 = w unless null
-  EPI_GLU_GRAD = 6        // with u = aux_f32, w = aux2_f32: C = acc * w * silu'(u), C2 = acc * silu(u) (bf16)
+  EPI_GLU_GRAD = 6,       // with u = aux_f32, w = aux2_f32: C = acc * w * silu'(u), C2 = acc * silu(u) (bf16)
+  EPI_F32_SEGMENTS = 7    // EPI_F32 with kseg < K (launch_gemm's choice)
 };
 
 struct GemmArgs {
@@ -30,11 +31,11 @@ struct GemmArgs {
   long long lda, ldb, ldc;
   int M, N, K, act, accumulate;
   int nb = 1, ns = 1;
-  int kseg = 0;           // EPI_F32: terms of K (of all pairs in turn) summed by themselves; 0: all
+  int kseg = 0;           // EPI_F32: terms of K summed by themselves (0: all); not with ns > 1
 };
 
-// ta: A stored as [K][M]; tb: B stored as [N][K].  M % 256, N % 256, K % 32, kseg % 256 and
-// K ns % kseg must be 0, K at least 256.
+// ta: A stored as [K][M]; tb: B stored as [N][K].  M, N, K and kseg must be multiples of 256,
+// K one of kseg.
 hipError_t launch_gemm(const GemmArgs& g, bool ta, bool tb, int epi, hipStream_t st);
 
 // out[n] (+)= sum_m x[m][n] for bf16 x [M][N]; part: colsum_workspace_floats(N) floats.

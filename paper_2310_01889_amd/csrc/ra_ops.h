@@ -26,10 +26,12 @@ int proj3(const void* x, const void* const* w, void* const* y, int T, int din, i
 int dgrad(const void* dy, const void* w, void* dx, int T, int din, int dout, hipStream_t st);
 int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, int din, int dout, int block,
           hipStream_t st);
-// The input gradient of three projections of one input: dq wq^T + dk wk^T + dv wv^T as one
-// product, either float32 (dx32) or bf16 with a residual added before the one rounding (dx).
-int dgrad3(const void* const* dy, const void* const* w, float* dx32, const void* residual, void* dx, int T, int din,
-           int dout, hipStream_t st);
+// The input gradient of n (2 or 3) products of one input, the sum of dy[i] w[i]^T: bf16 with a
+// residual added before the one rounding (dx), one launch that sums all pairs in its
+// accumulators, or float32 (dx32), a launch a pair: a chain of sums is then no longer than a
+// pair's (float32 tiles that hold two sets of sums would cost more than reading dx32 again).
+int dgrad_pairs(const void* const* dy, const void* const* w, int n, float* dx32, const void* residual, void* dx, int T,
+                int din, int dout, hipStream_t st);
 
 // Workspace of a feed-forward network: row_bytes of intermediates per row plus fixed bytes.
 // The rows are worked on in groups of whole blocks, as many as kGroupBytes hold (more rows per
