@@ -211,9 +211,11 @@ int ring_attn_decode_noalloc(const void* q, const void* k_cache, const void* v_c
 /*
  * Blockwise feed-forward network (Section 2 equation and "Blockwise Parallel
  * Transformers"; Algorithm 1's feed-forward step), bf16:
- *   y = act(x W1 + b1) W2 + b2, computed in groups of whole `block`s, as many as 4 GiB of
- *   [rows, d_ff] intermediates hold (one block at least): 2 bytes a hidden unit and row here,
- *   8 in the backward; 2 and 14 in swiglu_ffn and its backward.
+ *   y = act(x W1 + b1) W2 + b2, computed in groups of whole `block`s: as many as fill the chip
+ *   twice, 2^25 / min(d_model, d_ff) rows, and 1.25 GiB of [rows, d_ff] intermediates hold,
+ *   one block at least.  The intermediates are 2 bytes a hidden unit and row here, 8 in the
+ *   backward; 2 and 14 in swiglu_ffn and its backward.  Weight gradients sum each block by
+ *   itself and add up the blocks in order, whatever the groups.
  *   x  in bf16 [T, d_model];  w1 in bf16 [d_model, d_ff];  b1 in bf16 [d_ff] or NULL
  *   w2 in bf16 [d_ff, d_model];  b2 in bf16 [d_model] or NULL;  y out bf16 [T, d_model]
  *   act: an ra_act value.   T % block == 0, block % 256 == 0, d_model % 256 == 0,

@@ -6,6 +6,8 @@
 // runs in the bf16 matrix-core GEMM; bias, activation, residual and activation-derivative are
 // fused into its epilogue.  The backward pass recomputes each group's pre-activation
 // (gradient checkpointing) and accumulates weight gradients in float32.
+#include <algorithm>
+
 #include "ra_gemm.h"
 #include "ra_ops.h"
 #include "ra_runtime.h"
@@ -100,10 +102,12 @@ int dgrad_pairs(const void* const* dy, const void* const* w, int n, float* dx32,
   return RA_OK;
 }
 
-int alloc_row_groups(CallResources& R, int T, int block, size_t row_bytes, size_t fixed, int* rows) {
+int alloc_row_groups(CallResources& R, int T, int d_model, int d_ff, int block, size_t row_bytes, size_t fixed,
+                     int* rows) {
   const int blocks = T / block;
-  int per = (int)(kGroupBytes / ((size_t)block * row_bytes));
-  per = per < 1 ? 1 : per > blocks ? blocks : per;
+  const long long fill = (long long)kFillRounds * 256 * 256 * 256 / std::min(d_model, d_ff);
+  const long long fit = (long long)(kGroupBytes / ((size_t)block * row_bytes));
+  int per = (int)std::max(1ll, std::min({(fill + block - 1) / block, fit, (long long)blocks}));
   const int groups = (blocks + per - 1) / per;
   per = (blocks + groups - 1) / groups;  // groups of equal size
   int rc = R.alloc((size_t)per * block * row_bytes + fixed);
@@ -121,7 +125,7 @@ int ffn_forward(const void* x, const void* w1, const void* b1, const void* w2, c
                 void* y, int T, int d_model, int d_ff, int block, int act, hipStream_t stream) {
   CallResources R(stream);
   int rows, rc;
-  if ((rc = alloc_row_groups(R, T, block, (size_t)d_ff * 2, 0, &rows))) return rc;
+  if ((rc = alloc_row_groups(R, T, d_model, d_ff, block, (size_t)d_ff * 2, 0, &rows))) return rc;
   void* a = R.ws;  // activation of one group of blocks, bf16 [rows, d_ff]
   for (int r0 = 0; r0 < T; r0 += rows) {
     const int m = T - r0 < rows ? T - r0 : rows;
@@ -144,7 +148,7 @@ int ffn_backward(const void* x, const void* w1, const void* b1, const void* w2, 
   const size_t part = colsum_workspace_floats(d_ff > d_model ? d_ff : d_model);
   CallResources R(stream);
   int rows, rc;
-  if ((rc = alloc_row_groups(R, T, block, (size_t)d_ff * 8, part * 4, &rows))) return rc;
+  if ((rc = alloc_row_groups(R, T, d_model, d_ff, block, (size_t)d_ff * 8, part * 4, &rows))) return rc;
   const size_t nb = (size_t)rows * d_ff;
   float* h = (float*)R.ws;                       // pre-activation, float32 [rows, d_ff]
   void* a = (char*)R.ws + nb * 4;                // activation, bf16

@@ -292,7 +292,7 @@ static int swiglu_forward(const void* x, const void* w1, const void* w3, const v
                           int T, int dm, int dff, int block, hipStream_t st) {
   CallResources R(st);
   int rows, rc;
-  if ((rc = alloc_row_groups(R, T, block, (size_t)dff * 2, 0, &rows))) return rc;
+  if ((rc = alloc_row_groups(R, T, dm, dff, block, (size_t)dff * 2, 0, &rows))) return rc;
   void* gte = R.ws;  // gate output, bf16 [rows, d_ff]
   for (int r0 = 0; r0 < T; r0 += rows) {
     const int m = T - r0 < rows ? T - r0 : rows;
@@ -315,7 +315,7 @@ static int swiglu_backward(const void* x, const void* w1, const void* w3, const 
                            hipStream_t st) {
   CallResources R(st);
   int rows, rc;
-  if ((rc = alloc_row_groups(R, T, block, (size_t)dff * 14, 0, &rows))) return rc;
+  if ((rc = alloc_row_groups(R, T, dm, dff, block, (size_t)dff * 14, 0, &rows))) return rc;
   const size_t nb = (size_t)rows * dff;
   float* u = (float*)R.ws;
   float* w = u + nb;

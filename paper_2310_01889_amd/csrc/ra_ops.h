@@ -33,14 +33,19 @@ int wgrad(const void* x, const void* const* dy, float* const* dw, int n, int T, 
 int dgrad_pairs(const void* const* dy, const void* const* w, int n, float* dx32, const void* residual, void* dx, int T,
                 int din, int dout, hipStream_t st);
 
-// Workspace of a feed-forward network: row_bytes of intermediates per row plus fixed bytes.
-// The rows are worked on in groups of whole blocks, as many as kGroupBytes hold (more rows per
-// launch fill the chip: at 4096 x 11008 a 2048-row block is 128 to 344 tiles of 256 x 256 for
-// 256 CUs); one block at a time where a block needs more or memory is short.  *rows: rows of a
-// group (the last one may have fewer).
-constexpr size_t kGroupBytes = (size_t)4 << 30;
+// Workspace of a feed-forward network of d_model x d_ff: row_bytes of intermediates per row plus
+// fixed bytes.  The rows are worked on in groups of whole blocks.  256 tiles of 256 x 256 fill the
+// chip, so a group is the rows that give the narrower product kFillRounds times as many (4096
+// wide: 8192 rows, the intermediates of a backward at d_ff = 4 d_model then 1 GiB), but no more
+// than kGroupBytes hold; one block where that is more, or where memory is short.  Forward +
+// backward in groups of one round, two, four, ms: 8192 x 4096 x 16384 7.35, 7.08, 7.07; 16384 x
+// 2048 x 5120 2.86, 2.65, 2.65; LLaMA step of 16384 x 4096 x 11008 70.1, 68.6, 68.8.
+// *rows: rows of a group (the last one may have fewer).
+constexpr int kFillRounds = 2;
+constexpr size_t kGroupBytes = (size_t)5 << 28;
 struct CallResources;
-int alloc_row_groups(CallResources& R, int T, int block, size_t row_bytes, size_t fixed, int* rows);
+int alloc_row_groups(CallResources& R, int T, int d_model, int d_ff, int block, size_t row_bytes, size_t fixed,
+                     int* rows);
 
 // Blockwise FFN forward: y = act(x W1 + b1) W2 + b2 (+ residual); arguments validated.
 int ffn_forward(const void* x, const void* w1, const void* b1, const void* w2, const void* b2, const void* residual,

@@ -5,7 +5,7 @@ smallest shapes, and shapes with just under and just over one round of big tiles
 compared with float32 products of the same bf16 values (errors: bf16 output 2^-9 relative,
 float32 sums of K terms).  A weight gradient is the sum of its blocks' own, added up in order:
 the same, bit for bit, as calls on one block each.  The feed-forward networks work on several
-whole blocks at a time: a length of five blocks, cut into groups, against the same calls.
+whole blocks at a time: a length of seven, cut into groups, against the same calls.
 """
 import pytest
 import torch
@@ -81,9 +81,9 @@ def test_bias_gradient_precision(T, blk):
 
 @pytest.mark.parametrize("glu", [False, True])
 def test_row_groups_of_unequal_size(glu):
-    blk, dm = 8192, 256
-    dff = 8192 if glu else 16384  # two groups or more in the backward of both
-    T = 5 * blk
+    blk, dm = 2048, 256
+    dff = 8192 if glu else 16384  # five blocks fit in the backward of both: groups of 4 + 3
+    T = 7 * blk
     x, dy = _rand(5, T, dm), _rand(6, T, dm)
     w1, w3, w2 = _rand(7, dm, dff, std=0.02), _rand(8, dm, dff, std=0.02), _rand(9, dff, dm, std=0.02)
 
@@ -109,3 +109,19 @@ def test_row_groups_of_unequal_size(glu):
         for s in sums[1:]:
             ref = ref + s[i]
         assert torch.equal(d, ref)
+
+
+def test_row_groups_hold_little_memory():
+    """The intermediates of a long, narrow network stay within the header's 1.25 GiB."""
+    T, dm, dff, blk = 32768, 256, 16384, 1024
+    x, dy, w1, w2 = _rand(1, T, dm), _rand(2, T, dm), _rand(3, dm, dff, std=0.02), _rand(4, dff, dm, std=0.02)
+    dx, dw1, dw2 = torch.empty_like(x), torch.empty(dm, dff, device="cuda"), torch.empty(dff, dm, device="cuda")
+    torch.cuda.synchronize()
+    ra.release_workspace()
+    free = torch.cuda.mem_get_info()[0]
+    ra.blockwise_ffn_bwd(x, w1, None, w2, dy, dx, dw1, None, dw2, None, blk)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    ra.release_workspace()
+    log("  workspace %.3f GiB" % (used / 2 ** 30))
+    assert 0 < used <= 1.25 * 2 ** 30 + 64 * 2 ** 20  # column sums and the pool's granularity
