@@ -364,7 +364,8 @@ const char* ring_attn_last_error(void);
 /*
  * Return the cached workspace of the current device's library pool to the driver
  * (hipMemPoolTrimTo to zero bytes).  Memory still in use by calls whose stream has not
- * reached the end of the call stays allocated.  Not part of the method.  Returns RA_OK,
+ * reached the end of the call stays allocated, except on the NULL stream, which is waited for
+ * if blocks of it are kept.  Not part of the method.  Returns RA_OK,
  * or RA_EHIP if the pool cannot be created or trimmed.
  */
 int ring_attn_release_workspace(void);

@@ -55,7 +55,8 @@ constexpr int kWsKeepCount = 32;
 void* workspace_take(int dev, size_t bytes, size_t* got);
 // Offers a block whose last use is enqueued on the device's null stream; false: free it.
 bool workspace_give(int dev, void* p, size_t bytes);
-// The current device's kept blocks back to the pool, in the null stream's order; true if any.
+// Gives the current device's kept blocks, and what else the pool has free, back to the driver;
+// true if there were any.  Waits for the null stream if so.
 bool workspace_drop_kept();
 
 // Stream-ordered workspace and events owned by one call; released on every exit path.

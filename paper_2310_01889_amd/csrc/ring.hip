@@ -21,7 +21,6 @@
 
 #include <algorithm>
 #include <mutex>
-#include <new>
 #include <string>
 #include <vector>
 
@@ -46,7 +45,7 @@ int set_err(int code, const char* fmt, ...) {
 
 
 // ---------------------------------------------------------------------------------
-// Per-device side stream (created once, default priority) and memory-pool setting.
+// Per-device side stream (created once, default priority).
 // ---------------------------------------------------------------------------------
 namespace {
 std::mutex g_mu;
@@ -61,104 +60,6 @@ int side_stream(hipStream_t* out) {
   if (!g_side[dev]) RA_HIP(hipStreamCreateWithFlags(&g_side[dev], hipStreamNonBlocking));
   *out = g_side[dev];
   return RA_OK;
-}
-
-namespace {
-hipMemPool_t g_pool[64];
-}  // namespace
-
-int workspace_pool(hipMemPool_t* out) {
-  int dev = 0;
-  RA_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= 64) return set_err(RA_EHIP, "device index %d out of range", dev);
-  std::lock_guard<std::mutex> lk(g_mu);
-  if (!g_pool[dev]) {
-    hipMemPoolProps props{};
-    props.allocType = hipMemAllocationTypePinned;
-    props.handleTypes = hipMemHandleTypeNone;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
-    hipMemPool_t pool;
-    RA_HIP(hipMemPoolCreate(&pool, &props));
-    uint64_t thr = ~0ull;
-    hipError_t e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-    if (e != hipSuccess) {
-      (void)hipMemPoolDestroy(pool);
-      return set_err(RA_EHIP, "hipMemPoolSetAttribute failed: %s", hipGetErrorString(e));
-    }
-    g_pool[dev] = pool;
-  }
-  *out = g_pool[dev];
-  return RA_OK;
-}
-
-// ---------------------------------------------------------------------------------
-// Kept workspaces of the null streams (see ra_runtime.h).
-// ---------------------------------------------------------------------------------
-namespace {
-struct KeptBlock {
-  void* p;
-  size_t bytes;
-  int dev;
-};
-std::mutex g_kept_mu;
-std::vector<KeptBlock> g_kept;
-}  // namespace
-
-void* workspace_take(int dev, size_t bytes, size_t* got) {
-  std::lock_guard<std::mutex> lk(g_kept_mu);
-  int best = -1;
-  for (int i = 0; i < (int)g_kept.size(); ++i) {
-    const KeptBlock& b = g_kept[i];
-    if (b.dev == dev && b.bytes >= bytes && b.bytes <= 2 * bytes + ((size_t)1 << 20) &&
-        (best < 0 || b.bytes < g_kept[best].bytes))
-      best = i;
-  }
-  if (best < 0) return nullptr;
-  void* p = g_kept[best].p;
-  *got = g_kept[best].bytes;
-  g_kept.erase(g_kept.begin() + best);
-  return p;
-}
-
-bool workspace_give(int dev, void* p, size_t bytes) {
-  std::lock_guard<std::mutex> lk(g_kept_mu);
-  int count = 0, first = -1;
-  size_t total = 0;
-  for (int i = 0; i < (int)g_kept.size(); ++i)
-    if (g_kept[i].dev == dev) {
-      if (first < 0) first = i;
-      ++count;
-      total += g_kept[i].bytes;
-    }
-  // full: the block kept longest makes room (the freed memory stays in the pool)
-  if (first >= 0 && (count >= kWsKeepCount || total + bytes > kWsKeepTotal)) {
-    (void)hipFreeAsync(g_kept[first].p, nullptr);
-    total -= g_kept[first].bytes;
-    --count;
-    g_kept.erase(g_kept.begin() + first);
-  }
-  if (count >= kWsKeepCount || total + bytes > kWsKeepTotal) return false;
-  try {
-    g_kept.push_back({p, bytes, dev});
-  } catch (const std::bad_alloc&) {  // called from a destructor: nothing may escape
-    return false;
-  }
-  return true;
-}
-
-bool workspace_drop_kept() {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return false;
-  std::lock_guard<std::mutex> lk(g_kept_mu);
-  bool any = false;
-  for (int i = (int)g_kept.size() - 1; i >= 0; --i)
-    if (g_kept[i].dev == dev) {
-      (void)hipFreeAsync(g_kept[i].p, nullptr);
-      g_kept.erase(g_kept.begin() + i);
-      any = true;
-    }
-  return any;
 }
 
 // ---------------------------------------------------------------------------------
@@ -720,7 +621,7 @@ int ring_attn_release_workspace(void) {
   hipMemPool_t pool;
   int rc = workspace_pool(&pool);
   if (rc) return rc;
-  (void)workspace_drop_kept();
+  (void)workspace_drop_kept();  // trims as well, where blocks were kept
   RA_HIP(hipMemPoolTrimTo(pool, 0));
   return RA_OK;
 }
