@@ -101,7 +101,7 @@ struct CallResources {
     int rc = workspace_pool(&pool);
     if (rc) return rc;
     hipError_t e = hipMallocFromPoolAsync(&ws, bytes, pool, stream);
-    if (e == hipErrorOutOfMemory && stream == nullptr && workspace_drop_kept()) {
+    if (e == hipErrorOutOfMemory && workspace_drop_kept()) {  // whichever stream asks
       (void)hipGetLastError();
       e = hipMallocFromPoolAsync(&ws, bytes, pool, stream);
     }

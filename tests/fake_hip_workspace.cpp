@@ -127,8 +127,8 @@ static void release() {
 
 // Kept blocks make room for a workspace of any stream.
 static void short_of_memory() {
-
-  for (hipStream_t s : {(hipStream_t) nullptr}) {
+  hipStream_t other = (hipStream_t)0x30;
+  for (hipStream_t s : {(hipStream_t) nullptr, other}) {
     {
       CallResources A(nullptr), B(nullptr), C(nullptr);
       for (auto* r : {&A, &B, &C}) check(r->alloc(60 * kMiB) == RA_OK, "allocation");
