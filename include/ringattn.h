@@ -13,9 +13,7 @@
  *
  * On one GPU the ring is virtual: all hosts' blocks live in device memory.  Calls over
  * the whole ring are one launch (bf16 backward: one for dK/dV, one for dQ) that folds every
- * host's blocks, in ring order, where they lie; bf16 ones, while ring_attn_timing_enable is
- * on, one launch a ring step.  Every other
- * call runs n_hosts ring steps, each one kernel launch covering every host that has work at
+ * host's blocks, in ring order, where they lie.  Every other call runs n_hosts ring steps, each one kernel launch covering every host that has work at
  * that step, and the block each host needs at the next step reaches its per-host receive
  * buffer (double buffer) during the current step by device-to-device copies on a
  * library-owned side stream, overlapping the compute of the current step.
@@ -373,7 +371,8 @@ int ring_attn_release_workspace(void);
 /*
  * Kernel timing for benchmarks and profiling (not part of the method).
  * ring_attn_timing_enable(1) makes every later launch of the library's hot kernels be
- * bracketed by timing events on the stream it runs on; ring_attn_timing_read(kind, ...)
+ * bracketed by timing events on the stream it runs on (an attention backward's two as one);
+ * what is launched does not change. ring_attn_timing_read(kind, ...)
  * waits for the recorded launches of that kind, returns their summed duration in
  * milliseconds and their number, and forgets them.  Kinds:
  */

@@ -118,34 +118,25 @@ struct CallResources {
 
 // Kernel timing (ring_attn_timing_enable): true when launches are to be bracketed.
 bool timing_on();
-// own_a: the start event belongs to this entry (false when it is the end event of the
-// entry before it)
-void timing_push(int kind, hipEvent_t a, hipEvent_t b, bool own_a);
+void timing_push(int kind, hipEvent_t a, hipEvent_t b);
 
 // Runs f() (which enqueues kernels on st) between two timing events when timing is on.
-// chain, if given, carries the end event of the previous launch of a sequence that has
-// nothing else enqueued between its launches: that event then also starts this launch,
-// so one event, not two, separates consecutive launches (each costs a few microseconds
-// of idle time between the kernels).
 template <class F>
-hipError_t timed_launch(int kind, hipStream_t st, F&& f, hipEvent_t* chain = nullptr) {
+hipError_t timed_launch(int kind, hipStream_t st, F&& f) {
   if (!timing_on()) return f();
   // no system-scope fences: the events only carry timestamps, and the fences of a default
   // event widen the gap between consecutive launches by about 3 us per event
-  hipEvent_t a = chain ? *chain : nullptr, b;
-  const bool own_a = a == nullptr;
-  hipError_t e;
-  if (own_a) {
-    e = hipEventCreateWithFlags(&a, hipEventDisableSystemFence);
-    if (e != hipSuccess) return e;
-    (void)hipEventRecord(a, st);
-  }
-  e = hipEventCreateWithFlags(&b, hipEventDisableSystemFence);
+  hipEvent_t a, b;
+  hipError_t e = hipEventCreateWithFlags(&a, hipEventDisableSystemFence);
   if (e != hipSuccess) return e;
+  if ((e = hipEventCreateWithFlags(&b, hipEventDisableSystemFence)) != hipSuccess) {
+    (void)hipEventDestroy(a);
+    return e;
+  }
+  (void)hipEventRecord(a, st);
   e = f();
   (void)hipEventRecord(b, st);
-  timing_push(kind, a, b, own_a);
-  if (chain) *chain = b;
+  timing_push(kind, a, b);
   return e;
 }
 

@@ -69,7 +69,7 @@ int side_stream(hipStream_t* out) {
 namespace {
 std::mutex g_tmu;
 bool g_timing = false;
-struct TimedLaunch { int kind; hipEvent_t a, b; bool own_a; };
+struct TimedLaunch { int kind; hipEvent_t a, b; };
 std::vector<TimedLaunch> g_timed;
 }  // namespace
 
@@ -78,9 +78,9 @@ bool timing_on() {
   return g_timing;
 }
 
-void timing_push(int kind, hipEvent_t a, hipEvent_t b, bool own_a) {
+void timing_push(int kind, hipEvent_t a, hipEvent_t b) {
   std::lock_guard<std::mutex> lk(g_tmu);
-  g_timed.push_back({kind, a, b, own_a});
+  g_timed.push_back({kind, a, b});
 }
 
 static bool env_flag(const char* name) {
@@ -130,16 +130,15 @@ static int copy_block(const RingProblem& P, const void* src_all, char* dst, int 
   return RA_OK;
 }
 
-// Enqueue the whole ring: `launch(t, hosts_of_step, ..., contiguous)` is called once
+// Enqueue the whole ring: `launch(t, hosts_of_step, ...)` is called once
 // per step with, for every active host, (host, block, kv pointers, batch stride, first/last
-// flags); `contiguous` says that nothing was enqueued on the stream since the previous step.
+// flags).
 //
-// inplace: every step reads the blocks where they lie.  Otherwise each step's blocks are
-// copied from their home rows into the receive slots by device-to-device copies, on a side
-// stream two steps ahead (or, with RINGATTN_SERIAL_COPY set, serially on the caller stream).
+// Each step's blocks are copied from their home rows into the receive slots by
+// device-to-device copies, on a side stream two steps ahead (or, with RINGATTN_SERIAL_COPY
+// set, serially on the caller stream).
 template <class Launch>
-static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, bool inplace,
-                    Launch&& launch) {
+static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, char* recv_base, Launch&& launch) {
   const int N = P.N;
   const int nh = (int)P.hosts.size();
   RecvBuffers rb;
@@ -158,7 +157,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 
   const bool serial = env_flag("RINGATTN_SERIAL_COPY");
   const bool poison = env_flag("RINGATTN_POISON");
-  const bool copies = N > 1 && !inplace;
+  const bool copies = N > 1;
   hipStream_t side = stream;
   if (!serial && copies) {
     int rc = side_stream(&side);
@@ -214,7 +213,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       const int i = P.hosts[s], j = P.blk(i, t);
       if (!P.active(i, j)) continue;
       StepHost h{};
-      if (t == 0 || inplace) {
+      if (t == 0) {
         h.k = (const char*)P.k + (size_t)j * P.c() * rowe * P.elt;
         h.v = (const char*)P.v + (size_t)j * P.c() * rowe * P.elt;
         h.kv_bstride = (long long)P.S * rowe;
@@ -232,8 +231,7 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
       host_ids.push_back(i);
       blk_ids.push_back(j);
     }
-    // contiguous: nothing has been enqueued on the stream since the previous step's launch
-    int rc = launch(t, hs, host_ids, blk_ids, t > 0 && inplace);
+    int rc = launch(t, hs, host_ids, blk_ids);
     if (rc) return rc;
     if (!serial && copies && t >= 1 && t + 2 < N) {
       hipEvent_t done;
@@ -260,15 +258,13 @@ static int run_ring(const RingProblem& P, hipStream_t stream, CallResources& R, 
 // ---------------------------------------------------------------------------------
 // Whole ring in ring order: all blocks are on this device, so nothing is exchanged and
 // one launch walks each query tile over its host's blocks (launch_fwd_ring_*): no receive
-// buffers, no state between steps, one grid instead of N, each with its own tail.  While
-// launches are being timed a bf16 call runs as one launch a ring step, reading in place, so that
-// every step has its entry; RINGATTN_SERIAL_COPY / RINGATTN_POISON ask, in bf16, for the
-// exchange by copies.  All give the same bits.
+// buffers, no state between steps, one grid instead of N, each with its own tail.
+// RINGATTN_SERIAL_COPY / RINGATTN_POISON ask, in bf16, for the exchange by copies, one launch a
+// ring step.  Both give the same bits.
 static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream) {
   const int nh = (int)P.hosts.size();
   const bool f32 = P.elt == 4;  // always one launch
-  const bool inplace = f32 || P.whole() && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON");
-  if (f32 || (inplace && !timing_on())) {
+  if (f32 || (P.whole() && !env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON"))) {
     FwdRing a{};
     a.q = P.q;
     a.k = P.k;
@@ -288,7 +284,7 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
     }));
     return RA_OK;
   }
-  const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
+  const size_t recv = P.N > 1 ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
   const int Sp = P.whole() ? P.N * P.c() : P.Sq;
   const size_t nrow = (size_t)P.B * P.H * Sp;
   const bool need_state = P.N > 1;
@@ -316,13 +312,11 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
   st.c = P.c();
   st.causal = P.causal;
   st.scale = 1.0f / sqrtf((float)P.D);
-  hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  return run_ring(P, stream, R, base, inplace, [&](int, const std::vector<StepHost>& hs, const std::vector<int>&,
-                                                  const std::vector<int>&, bool contiguous) -> int {
+  return run_ring(P, stream, R, base, [&](int, const std::vector<StepHost>& hs, const std::vector<int>&,
+                                         const std::vector<int>&) -> int {
     st.n_slots = (int)hs.size();
     for (size_t s = 0; s < hs.size(); ++s) st.host[s] = hs[s];
-    if (!contiguous) chain = nullptr;
-    RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] { return launch_fwd_bf16(st, P.D, stream); }, &chain));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_FWD, stream, [&] { return launch_fwd_bf16(st, P.D, stream); }));
     return RA_OK;
   });
 }
@@ -332,17 +326,16 @@ static int run_fwd(const RingProblem& P, void* o, float* lse, hipStream_t stream
 // ---------------------------------------------------------------------------------
 // bf16: as in the forward, the whole ring runs as one launch for dK/dV and one for dQ, each
 // workgroup's accumulators staying in registers for the whole ring (no float32 gradients in
-// memory, no receive buffers); step by step while launches are being timed or when the
-// exchange by copies is asked for, the accumulators saved between steps.
+// memory, no receive buffers); step by step, the accumulators saved between steps, when the
+// exchange by copies is asked for.
 static int run_bwd(const RingProblem& P, const void* o, const float* lse, const void* dO, void* dq,
                    void* dk, void* dv, hipStream_t stream) {
   const int nh = (int)P.hosts.size();
   const size_t nrow = (size_t)P.B * P.H * P.Sq;
   const size_t telems = (size_t)P.B * P.S * P.H * P.D;
   const bool f32 = P.elt == 4;  // always one launch
-  const bool inplace = f32 || (!env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON"));
-  const bool one = f32 || (inplace && !timing_on());
-  const size_t recv = P.N > 1 && !inplace ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
+  const bool one = f32 || (!env_flag("RINGATTN_SERIAL_COPY") && !env_flag("RINGATTN_POISON"));
+  const size_t recv = P.N > 1 && !one ? RecvBuffers::bytes((size_t)P.B * P.c() * P.H * P.D * P.elt, nh) : 0;
   const size_t grads = one ? 0 : 3 * telems * sizeof(float);
   CallResources R(stream);
   int rc = R.alloc(recv + 2 * nrow * sizeof(float) + grads);
@@ -411,9 +404,8 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
   st.dq_out = dq;
   st.dk_out = dk;
   st.dv_out = dv;
-  hipEvent_t chain = nullptr;  // end event of the previous step's launch (timing)
-  return run_ring(P, stream, R, base, inplace, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
-                                                  const std::vector<int>& blks, bool contiguous) -> int {
+  return run_ring(P, stream, R, base, [&](int t, const std::vector<StepHost>& hs, const std::vector<int>&,
+                                         const std::vector<int>& blks) -> int {
     st.n_slots = (int)hs.size();
     for (size_t s = 0; s < hs.size(); ++s) {
       st.host[s] = hs[s];
@@ -421,8 +413,7 @@ static int run_bwd(const RingProblem& P, const void* o, const float* lse, const 
       st.dkv_flags[s] =
           (unsigned char)((t == blk_first[blks[s]] ? kFirst : 0) | (t == blk_last[blks[s]] ? kLast : 0));
     }
-    if (!contiguous) chain = nullptr;
-    RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] { return launch_bwd_bf16(st, P.D, stream); }, &chain));
+    RA_HIP(timed_launch(RA_KERNEL_ATTN_BWD, stream, [&] { return launch_bwd_bf16(st, P.D, stream); }));
     return RA_OK;
   });
 }
@@ -650,11 +641,7 @@ int ring_attn_timing_read(int kind, double* total_ms, int* launches) {
       if (e != hipSuccess) rc = set_err(RA_EHIP, "timing event: %s", hipGetErrorString(e));
     }
     sum += ms;
-  }
-  // an entry's start event may be the end event of the entry before it: destroy once all
-  // durations are read
-  for (const TimedLaunch& t : mine) {
-    if (t.own_a) (void)hipEventDestroy(t.a);
+    (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
   }
   *total_ms = sum;

@@ -170,11 +170,10 @@ def test_bf16_one_host_share(host):
 @pytest.mark.parametrize("causal", [0, 1])
 @pytest.mark.parametrize("env", ["RINGATTN_SERIAL_COPY", "RINGATTN_POISON"])
 def test_bf16_copy_modes_match(env, causal, monkeypatch):
-    """The key/value blocks reach every host's receive slot by side-stream copies (forward)
-    or by the backward step kernels forwarding the block they hold to the next host.
-    Receive slots poisoned with NaN before they are to be filled, or copies serialised on
-    the caller stream (which also replaces the backward's forwarding by copies), give
-    bit-identical forward and backward results to the default."""
+    """The default call folds every block where it lies, in one launch.  The exchange step by step
+    -- each host's blocks copied into its receive slots, poisoned with NaN before they are to be
+    filled, by the side stream, or serialised on the caller stream -- gives the same bits,
+    forward and backward."""
     B, S, H, D, N = 1, 2048, 2, 128, 8
     q, k, v, do = dev(*synth.attention_inputs(8, B, S, H, D, with_grad=True))
     o0, l0 = ra.attention_fwd(q, k, v, N, causal)
@@ -309,12 +308,18 @@ def test_errors_leave_outputs_untouched():
 
 @pytest.mark.parametrize("n_hosts", [8, 1])
 def test_launch_timing_counts_and_bounds(n_hosts):
-    """ring_attn_timing_*: one timed entry per ring step (consecutive steps share their
-    boundary event), durations positive and together within the call's own duration."""
+    """ring_attn_timing_*: one timed entry per launch an untimed call makes -- one for the whole
+    ring, one a ring step for a host's share -- the same bits, durations positive and
+    together within the call's own duration."""
     log("timing case n_hosts=%d" % n_hosts)
     q, k, v = dev(*synth.attention_inputs(5, 1, 2048, 2, 128, torch.bfloat16))
-    o, lse = ra.attention_fwd(q, k, v, n_hosts, True)  # warm-up
     dO = torch.ones_like(q)
+    c = 2048 // n_hosts
+    qb = q[:, -c:].contiguous()
+    ob, lb = torch.empty_like(qb), torch.empty((1, 2, c), dtype=torch.float32, device="cuda")
+    ref = ra.attention_fwd(q, k, v, n_hosts, True)  # warm-up
+    ref += ra.attention_bwd(q, k, v, *ref, dO, n_hosts, True)
+    ra.ring_attn_fwd_host(qb, k, v, ob, lb, n_hosts, n_hosts - 1, True)
     torch.cuda.synchronize()
     for kind in (ra.KERNEL_ATTN_FWD, ra.KERNEL_ATTN_BWD):
         ra.timing_read(kind)
@@ -327,12 +332,21 @@ def test_launch_timing_counts_and_bounds(n_hosts):
         ra.attention_bwd(q, k, v, o, lse, dO, n_hosts, True)
         e[2].record()
         torch.cuda.synchronize()
+        got = (o, lse, *ra.attention_bwd(q, k, v, o, lse, dO, n_hosts, True))
+        assert all(torch.equal(a, b) for a, b in zip(ref, got))
+        ra.timing_enable(False)
+        kinds = [(ra.KERNEL_ATTN_FWD, 0, 1), (ra.KERNEL_ATTN_BWD, 1, 2)]
+        reads = {kind: ra.timing_read(kind) for kind, _, _ in kinds}
+        ra.timing_enable(True)
+        ra.ring_attn_fwd_host(qb, k, v, ob, lb, n_hosts, n_hosts - 1, True)
+        torch.cuda.synchronize()
+        assert ra.timing_read(ra.KERNEL_ATTN_FWD)[1] == n_hosts
     finally:
         ra.timing_enable(False)
-    for kind, i in ((ra.KERNEL_ATTN_FWD, 0), (ra.KERNEL_ATTN_BWD, 1)):
-        ms, n = ra.timing_read(kind)
-        assert n == n_hosts
-        assert 0 < ms <= e[i].elapsed_time(e[i + 1]) * 1.01 + 0.01
+    for kind, i, calls in kinds:
+        ms, n = reads[kind]
+        assert n == calls
+        assert 0 < ms <= calls * (e[i].elapsed_time(e[i + 1]) * 1.01 + 0.01)
         assert ra.timing_read(kind) == (0.0, 0)
 
 

@@ -1,7 +1,8 @@
 """The whole ring in one launch against the same call made of one launch a ring step.
 
-Under ring_attn_timing_enable a whole-ring bf16 call, forward or backward, runs step by step;
-both forms fold the same tiles in the same order, so their results are equal bit for bit.  The shapes sit where
+With RINGATTN_SERIAL_COPY a whole-ring bf16 call, forward or backward, runs step by step, its
+blocks copied from host to host; both forms fold the same tiles in the same order, so their
+results are equal bit for bit.  The shapes sit where
 the one-launch form can go wrong: (batch, head) groups that do not divide over the 8 XCDs,
 one tile per workgroup, blocks of one tile row, more hosts than full blocks, ragged ends one
 row past and one row short of a tile, the eight-wave kernel.
@@ -39,22 +40,17 @@ SHAPES = [
 
 
 @pytest.mark.parametrize("B,S,H,D,N,causal", SHAPES)
-def test_one_launch_equals_steps(B, S, H, D, N, causal):
+def test_one_launch_equals_steps(B, S, H, D, N, causal, monkeypatch):
     log("one launch B=%d S=%d H=%d D=%d N=%d causal=%d" % (B, S, H, D, N, causal))
     q, k, v, do = synth.attention_inputs(S + H, B, S, H, D, with_grad=True)
     qd, kd, vd, dod = dev(q, k, v, do)
     o, lse = ra.attention_fwd(qd, kd, vd, N, causal)
     grads = ra.attention_bwd(qd, kd, vd, o, lse, dod, N, causal)
     torch.cuda.synchronize()
-    ra.timing_enable(True)
-    try:
-        o1, lse1 = ra.attention_fwd(qd, kd, vd, N, causal)
-        grads1 = ra.attention_bwd(qd, kd, vd, o, lse, dod, N, causal)
-        torch.cuda.synchronize()
-    finally:
-        ra.timing_enable(False)
-        ra.timing_read(ra.KERNEL_ATTN_FWD)
-        ra.timing_read(ra.KERNEL_ATTN_BWD)
+    monkeypatch.setenv("RINGATTN_SERIAL_COPY", "1")
+    o1, lse1 = ra.attention_fwd(qd, kd, vd, N, causal)
+    grads1 = ra.attention_bwd(qd, kd, vd, o, lse, dod, N, causal)
+    torch.cuda.synchronize()
     assert torch.equal(o, o1) and torch.equal(lse, lse1)
     for g, g1 in zip(grads, grads1):
         assert torch.equal(g, g1)
