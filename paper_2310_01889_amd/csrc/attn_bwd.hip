@@ -287,8 +287,8 @@ __device__ __forceinline__ bool key_tile(const P& p, KeyTile& t) {
 //   dS = P * dP
 //   dV^T += dO^T P        (A = dO^T by LDS transpose read, B = P)
 //   dK^T += Q^T dS        (A = Q^T by LDS transpose read, B = dS)
-// Q and dO tiles (XOR-swizzled rows) and the tile's lse*log2e and Delta are filled by
-// direct-to-LDS buffer loads into a ring of three buffers (48 KB for D = 128, so every
+// Q and dO tiles (XOR-swizzled rows) and the tile's -lse sqrt(D) and -Delta are filled by
+// direct-to-LDS buffer loads into a ring of three buffers (25.5 KB for D = 64, so every
 // LDS address fits the reads' immediate offsets).  The loop is software pipelined: while
 // tile t's P and dS are formed on the vector ALUs and its dV, dK products run, the S' and
 // dP products of tile t+1 are issued and tile t+2 streams in.
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dkdv_bf16_kernel(const P p) {
   __shared__ __attribute__((aligned(1024))) bf16 sO0[kQB * D];  // dO tiles
   __shared__ __attribute__((aligned(1024))) bf16 sO1[kQB * D];
   __shared__ __attribute__((aligned(1024))) bf16 sO2[kQB * D];
-  // lse * log2e and Delta: 64 floats each, as a one-wave 4-byte load writes 256 bytes
+  // -lse sqrt(D) and -Delta: 64 floats each, as a one-wave 4-byte load writes 256 bytes
   // (lanes past the tile read zero)
   __shared__ __attribute__((aligned(256))) float sL0[64];  // -lse sqrt(D)
   __shared__ __attribute__((aligned(256))) float sL1[64];
@@ -820,7 +820,6 @@ __global__ __launch_bounds__(kBT, 2) void bwd_dq_bf16_kernel(const P p) {
   constexpr bool RING = std::is_same_v<P, BwdRing>;
   constexpr int NKK = D / 16, NDT = D / 32, CPR = D / 8;
   constexpr int ROWS_PER_LOAD = 64 / CPR, LOADS = kKK / 4 / ROWS_PER_LOAD;
-  // one LDS object per buffer (see the dK/dV kernel)
   // one LDS array (K0, K1, V0, V1 tiles), filled by direct-to-LDS loads the compiler does
   // not track (each tile's loads are waited for before the barrier that ends the tile), so
   // that every read address is one register plus an immediate offset

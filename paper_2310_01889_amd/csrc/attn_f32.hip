@@ -9,7 +9,7 @@
 // cycles (64 a product), so short sequences need the split to fill the chip and a causal
 // launch needs short workgroups to balance, while the matrix cores leave the L2 idle enough
 // (about 8 bytes a cycle and CU) that sharing a tile between fewer rows costs nothing.
-// D = 128: G = 2, R = 2; D = 64: G = 1, R = 4 (128 KB of LDS each, double buffered).
+// D = 128: G = 2, R = 2; D = 64: G = 1, R = 4 (130 and 132 KB of LDS, double buffered).
 //
 // Lane layouts: S^T = K Q^T takes A = K rows from LDS (16-byte chunks, lane half h holding dims
 // 8 u + 4 h + e) and B = Q in registers in the same order; register i of the result holds key

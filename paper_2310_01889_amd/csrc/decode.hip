@@ -338,7 +338,8 @@ __global__ __launch_bounds__(64 * kMergeWaves) void decode_merge_kernel(const Me
 // and more of keys and values.  Short chunks pay their workgroup's start, a partial state written and one more
 // term of the merge for little reading; on long caches more loads in flight pay.  us at 1024,
 // 4096 workgroups, tokens x heads: 4096 x 32 (67 MB) 17.4, 27.2; 2 x 4096 x 16 of 64 13.0, 14.3;
-// 65536 x 4 (134 MB) 29.6, 44.9; 4 x 4096 x 32 (268 MB) 44.6, 50.5; 32768 x 32 (537 MB) 100.7, 97.8.
+// 65536 x 4 (134 MB) 29.6, 44.9; 4 x 4096 x 32 (268 MB, chunks of just 256 KB at 1024) 45.5, 50.5
+// and 44.8 at the 2048 taken; 32768 x 32 (537 MB) 100.7, 97.8.
 int pick_chunk(int B, int H, int S, int D, int c) {
   int kch = c;
   for (;;) {

@@ -98,7 +98,7 @@ __device__ __forceinline__ float act_grad(float h) {
 
 // ACT: the activation of the ACT epilogues (an ra_act value, fixed at compile time so
 // that each kernel holds the code of one activation only).
-// EPI_GLU_BF16 (T = 256, TB = 0) forms two products over the same A at once: the B tile is 128
+// EPI_GLU_BF16 (256 x 256, TB = 0) forms two products over the same A at once: the B tile is 128
 // columns of B[0] beside the same 128 columns of B[1], two k-major [32][128] tiles, so that the
 // epilogue finds u = A B[0] and w = A B[1] of an element in one row of the transposed tile.
 // EPI_F32_SEGMENTS (SUMS, TN = 128) sums K in segments of g.kseg, each by itself, and adds up
