@@ -7,7 +7,8 @@
 // keeps the matrix core busy.  K advances 32 at a time through a ring of five LDS stages
 // (all 160 KB of the CU's LDS) filled by direct-to-LDS buffer loads four steps ahead of
 // their use.  Products with too few such tiles for the chip's 256 CUs take 128 x 128 tiles,
-// 4 waves of 64 x 64, two workgroups a CU (see tile_size).  Tiles are kept in their
+// 4 waves of 64 x 64, two workgroups a CU (see tile_size); weight gradients of several row blocks
+// these or 256 x 128 (see small_sums).  Tiles are kept in their
 // memory layout, unpadded, with 16-byte chunks XOR-swizzled per row so that both the row
 // reads and the transpose reads (an operand whose registers must run along its contiguous
 // dimension) are free of bank conflicts.  Each wave computes C^T = B^T A^T so that a lane

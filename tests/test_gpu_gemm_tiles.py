@@ -79,9 +79,10 @@ def test_bias_gradient_precision(T, blk):
     assert err <= 1.25 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("dm", [256, 512])  # weight gradients in 128 x 128 and in 256 x 128 tiles
 @pytest.mark.parametrize("glu", [False, True])
-def test_row_groups_of_unequal_size(glu):
-    blk, dm = 2048, 256
+def test_row_groups_of_unequal_size(glu, dm):
+    blk = 2048
     dff = 8192 if glu else 16384  # five blocks fit in the backward of both: groups of 4 + 3
     T = 7 * blk
     x, dy = _rand(5, T, dm), _rand(6, T, dm)
